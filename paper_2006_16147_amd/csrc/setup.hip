@@ -90,7 +90,13 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_local(const int32_t *in, in
   if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t nb) {
+// (with `from`: the total and kCtl words from there also go to `to`, pinned
+// host memory that the caller reads after waiting for the stream, which saves
+// a copy of its own)
+constexpr int kCtl = 16;
+__global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t nb,
+                                                          const int32_t *from = nullptr,
+                                                          int32_t *to = nullptr) {
   int32_t carry = 0;
   for (int32_t c0 = 0; c0 < nb; c0 += kScanBlock * kScanPer) {
     const int32_t base = c0 + threadIdx.x * kScanPer;
@@ -110,6 +116,10 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t
     __syncthreads();
   }
   if (threadIdx.x == 0) bsum[nb] = carry;
+  if (to) {
+    if (threadIdx.x < kCtl) to[threadIdx.x] = from[threadIdx.x];
+    if (threadIdx.x == 0) to[kCtl] = carry;
+  }
 }
 
 __global__ void k_scan_add(int32_t *out, const int32_t *bsum, int32_t n, int32_t nb) {
@@ -205,375 +215,630 @@ __global__ void k_smooth_w(int32_t n, const int32_t *rp, const int32_t *ci, cons
   w_out[i] = w[i] - t / m[i];
 }
 
-// position of the diagonal entry of each row
-__global__ void k_diag_pos(int32_t n, const int32_t *rp, const int32_t *ci, int32_t *dpos) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  dpos[i] = (int32_t)find_col(ci, rp[i], rp[i + 1], i);
-}
-
 // ---------------------------------------------------------------------------
-// 1. eq. (weights)
+// 1. eq. (weights) and every row's neighbours in order of preference
 // ---------------------------------------------------------------------------
-
+//
 // c = 1 - ((2 a) w_lo w_hi) / ((a_lolo w_lo) w_lo + (a_hihi w_hi) w_hi) for
 // each stored off-diagonal entry, computed in (lo, hi) order so that both
 // copies of an edge carry the same bits (A is bitwise symmetric).
-__global__ void k_weights(int32_t n, const int32_t *rp, const int32_t *ci, const double *val,
-                          const int32_t *dpos, const double *w, double *c) {
+//
+// The matching's strict key (c descending, lo ascending, hi ascending) orders
+// the neighbours j of one vertex v by (c descending, j ascending): those below
+// v have lo = j < v, those above lo = v and hi = j. Each row's neighbours are
+// sorted once in that order (pref, laid out like the row's entries, the unused
+// slot of the diagonal closed by -1); the matching then walks each list once
+// and reads no weight again.
+
+// Rows of a sweep's matrix: row i holds the entries [b[i], e[i]) of ci / val.
+// A level's CSR is {rp, rp + 1}; the matrices between the sweeps of a level
+// keep their rows where the Galerkin product put them, with gaps.
+struct RowsOf {
+  const int32_t *b, *e, *ci;
+  const double *val;
+};
+
+// the weight as an unsigned key that orders like it (NaN below every number)
+__device__ __forceinline__ uint64_t weight_key(double c) {
+  if (!(c == c)) return 0;
+  const uint64_t u = (uint64_t)__double_as_longlong(c + 0.0);
+  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+
+__device__ __forceinline__ uint64_t edge_key(int32_t i, int32_t j, double a, double wi, double wj,
+                                             double di, double dj) {
+  const double wl = i < j ? wi : wj, wh = i < j ? wj : wi;
+  const double dl = i < j ? di : dj, dh = i < j ? dj : di;
+  const double num = ((2.0 * a) * wl) * wh;
+  const double den = (dl * wl) * wl + (dh * wh) * wh;
+  return weight_key(1.0 - num / den);
+}
+
+// diagonal entry of each row
+__global__ void k_diag(int32_t n, RowsOf A, double *dg) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-    const int32_t j = ci[k];
-    if (j == i) {
-      c[k] = 0.0;
+  const int64_t k = find_col(A.ci, A.b[i], A.e[i], i);
+  dg[i] = k >= 0 ? A.val[k] : 0.0;
+}
+
+// Matching state of a vertex, one 64-bit word (read and written whole):
+// the low half says whether it is free and proposes to a neighbour (>= 0),
+// is a singleton (kDead) or matched to u (kMatched - u); the high half is the
+// round in which it came to propose or was settled, see k_match.
+constexpr int32_t kMatched = -3;
+__device__ __forceinline__ uint64_t pack_state(int32_t round, int32_t s) {
+  return ((uint64_t)(uint32_t)round << 32) | (uint32_t)s;
+}
+__device__ __forceinline__ int32_t state_of(uint64_t w) { return (int32_t)(uint32_t)w; }
+__device__ __forceinline__ int32_t round_of(uint64_t w) { return (int32_t)(w >> 32); }
+
+// G lanes per row, two entries per lane: a row of at most 2 G entries is
+// ranked in registers, every lane counting the entries ahead of its own while
+// each in turn is broadcast. Longer rows are listed for k_pref_long. The
+// entries of a wave's rows are consecutive, so its loads are coalesced, and
+// every lane has one division; a thread per row measured 120 us a sweep on
+// average over a 192^3 setup for the weights alone, stored as 8 bytes each.
+// Also the first proposal of every vertex: its first choice.
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_pref(int32_t n, RowsOf A, const double *__restrict__ w,
+                                                 const double *__restrict__ dg,
+                                                 int32_t *__restrict__ pref,
+                                                 uint64_t *__restrict__ st, int32_t *ovf,
+                                                 int32_t *novf) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t i = (int32_t)(t / G);
+  const int lane = (int)(t % G);
+  if (t / G >= n) return;  // whole groups: no lane of a live group is missing
+  const int32_t b = A.b[i], len = A.e[i] - b;
+  if (len > 2 * G) {
+    if (lane == 0) ovf[atomicAdd(novf, 1)] = i;
+    return;
+  }
+  const double wi = w[i], di = dg[i];
+  int32_t j[2];
+  uint64_t key[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int32_t e = lane + q * G;
+    j[q] = e < len ? A.ci[b + e] : i;
+    key[q] = 0;
+    if (j[q] != i) key[q] = edge_key(i, j[q], A.val[b + e], wi, w[j[q]], di, dg[j[q]]);
+  }
+  int32_t rank[2] = {0, 0}, deg = 0;
+  const int32_t l0 = min(len, G);
+  for (int32_t f = 0; f < l0; ++f) {
+    const int32_t jf = __shfl(j[0], f, G);
+    const uint64_t kf = __shfl((unsigned long long)key[0], f, G);
+    if (jf == i) continue;
+    ++deg;
+    // entries ascend in j: of two equal weights the earlier entry comes first
+    if (kf > key[0] || (kf == key[0] && f < lane)) ++rank[0];
+    if (kf >= key[1]) ++rank[1];
+  }
+  for (int32_t f = G; f < len; ++f) {
+    const int32_t jf = __shfl(j[1], f - G, G);
+    const uint64_t kf = __shfl((unsigned long long)key[1], f - G, G);
+    if (jf == i) continue;
+    ++deg;
+    if (kf > key[0]) ++rank[0];
+    if (kf > key[1] || (kf == key[1] && f - G < lane)) ++rank[1];
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    if (j[q] == i) continue;
+    pref[b + rank[q]] = j[q];
+    if (rank[q] == 0) st[i] = pack_state(0, j[q]);
+  }
+  if (lane == 0) {
+    if (deg < len) pref[b + deg] = -1;
+    if (deg == 0) st[i] = pack_state(0, kDead);
+  }
+}
+
+// Rows listed by k_pref, one block each, their keys in LDS. A row of more
+// than kRapLongCap entries cannot be assembled into a coarse row later: it is
+// refused here already (kErrArg) and gets an empty list.
+__global__ void __launch_bounds__(kBlock) k_pref_long(
+    RowsOf A, const double *__restrict__ w, const double *__restrict__ dg,
+    int32_t *__restrict__ pref, uint64_t *__restrict__ st, const int32_t *__restrict__ ovf,
+    const int32_t *__restrict__ novf, int32_t *err) {
+  __shared__ uint64_t key[kRapLongCap];
+  const int32_t count = *novf;
+  for (int32_t o = blockIdx.x; o < count; o += gridDim.x) {
+    const int32_t i = ovf[o];
+    const int32_t b = A.b[i], len = A.e[i] - b;
+    if (len > kRapLongCap) {
+      if (threadIdx.x == 0) {
+        atomicOr(err, kErrArg);
+        pref[b] = -1;
+        st[i] = pack_state(0, kDead);
+      }
       continue;
     }
-    const int32_t lo = min(i, j), hi = max(i, j);
-    const double a = val[k];
-    const double wl = w[lo], wh = w[hi];
-    const double num = ((2.0 * a) * wl) * wh;
-    const double den = (val[dpos[lo]] * wl) * wl + (val[dpos[hi]] * wh) * wh;
-    c[k] = 1.0 - num / den;
+    const double wi = w[i], di = dg[i];
+    __syncthreads();  // the previous row's keys are read no more
+    for (int32_t e = threadIdx.x; e < len; e += kBlock) {
+      const int32_t j = A.ci[b + e];
+      key[e] = j == i ? 0 : edge_key(i, j, A.val[b + e], wi, w[j], di, dg[j]);
+    }
+    const int64_t dk = find_col(A.ci, b, A.e[i], i);
+    const int32_t de = dk >= 0 ? (int32_t)(dk - b) : -1;  // the diagonal's place, not ranked
+    const int32_t deg = len - (de >= 0 ? 1 : 0);
+    __syncthreads();
+    for (int32_t e = threadIdx.x; e < len; e += kBlock) {
+      if (e == de) continue;
+      const uint64_t ke = key[e];
+      int32_t rank = 0;
+      for (int32_t f = 0; f < len; ++f) {
+        const uint64_t kf = key[f];
+        rank += (f != de && (kf > ke || (kf == ke && f < e))) ? 1 : 0;
+      }
+      const int32_t j = A.ci[b + e];
+      pref[b + rank] = j;
+      if (rank == 0) st[i] = pack_state(0, j);
+    }
+    if (threadIdx.x == 0) {
+      if (deg < len) pref[b + deg] = -1;
+      if (deg == 0) st[i] = pack_state(0, kDead);
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
-// 2. matching: locally-dominant rounds
+// 2. matching: locally dominant edges
 // ---------------------------------------------------------------------------
+//
+// A free vertex proposes to the first vertex of its list that is not taken; a
+// mutual proposal is a locally dominant edge and is matched; a free vertex
+// whose list is used up is a singleton. Under the strict key the result does
+// not depend on the order of these steps, and each holds on stale reads too:
+// a vertex is taken for good, so one seen as taken is; one seen as free that
+// is taken by now only delays its proposer; and a proposal from u seen by the
+// free vertex v stands, since u leaves v only for v being taken. So there are
+// no rounds to wait for: every wave works on its own vertices at its own pace.
+// A vertex's word is written by its own thread, to memory for the other blocks
+// and to LDS for its own; the one that finds a mutual proposal also writes the
+// other end's, with the same value that its thread will write. (Where that
+// thread's earlier store of the proposal lands later, the end looks free until
+// its thread has seen the match: a delay like any other.)
+//
+// What bounds it is the chain of dependent steps, not bytes: with every weight
+// the same (the Poisson grid) the order of the indices decides, and vertex by
+// vertex the matching runs across the grid, about 2.5 N steps on N^3. As one
+// kernel per round over all vertices a step cost a launch and a pass over the
+// states (29 us at 160^3, 444 rounds, 12.9 ms). Here a block owns a run of
+// consecutive vertices, their words in LDS and the next entries of their lists
+// in registers, so a step inside it touches no memory; between blocks it costs
+// a store and a poll (3.3 ms). A wave looks outside when nothing moved inside,
+// and waves that wait sleep 2048 clocks between their looks and yield the
+// issue slots to those that move: with 64 clocks it was 4.4 ms, and with every
+// waiting wave polling all the time the polls filled the fabric and a step
+// took 8 us (16.5 ms). Blocks of 256 and 1024 vertices were 5 % and 1 % slower;
+// two vertices per thread (twice as many in flight) made no difference.
+//
+// A wave leaves when its vertices are settled, or when it found nothing new
+// kMatchSpin times (it may wait for a block that has not started); the next
+// launch goes on from the words in memory. In every launch the best edge left
+// is matched or gets nearer to it: a launch without any change (kMoved) means
+// that the input was not symmetric.
+//
+// The high half of a word carries the round of the synchronous algorithm
+// (everybody proposes, then all mutual proposals are matched): a vertex
+// proposes to x from the round in which the last vertex ahead of x in its list
+// was taken, an edge is matched in the round after both ends propose. The
+// largest one is the number of rounds that amg_matching_rounds reports.
+constexpr int kMatchThreads = 512;  // a vertex per thread
+constexpr int kMatchAhead = 8;      // list entries held
+constexpr int kMatchSpin = 1024;
+enum : int32_t { kLeft = 0, kMoved = 1, kMatchFlags = 2 };
 
-__device__ __forceinline__ bool better(double c1, int32_t lo1, int32_t hi1, double c2,
-                                       int32_t lo2, int32_t hi2) {
-  if (c1 != c2) return c1 > c2;
-  if (lo1 != lo2) return lo1 < lo2;
-  return hi1 < hi2;
-}
-
-// The best neighbour of v (entries [b, e) of its row) under the strict key
-// among those not taken: mate[j] != kFree, or (with cur) a mutual proposal
-// in cur. The loads go in batches of eight entries (all indices and weights,
-// then all mate and cur entries, then the proposals' proposals), so that a
-// vertex's chain of dependent loads does not grow with its degree; the
-// comparisons run in entry order. -1: every neighbour is taken.
-__device__ __forceinline__ int32_t best_free(int32_t v, int32_t b, int32_t e,
-                                             const int32_t *__restrict__ ci,
-                                             const double *__restrict__ c,
-                                             const int32_t *mate, const int32_t *cur) {
-  int32_t best = -1, blo = 0, bhi = 0;
-  double bc = 0.0;
-  for (int32_t k0 = b; k0 < e; k0 += 8) {
-    int32_t j[8];
-    double cc[8];
+__global__ void __launch_bounds__(kMatchThreads, 8) k_match(int32_t n,
+                                                            const int32_t *__restrict__ rb,
+                                                            const int32_t *__restrict__ re,
+                                                            const int32_t *__restrict__ pref,
+                                                            uint64_t *st, const int32_t *prev,
+                                                            int32_t *flags) {
+  constexpr int H = kMatchAhead;
+  __shared__ uint64_t own[kMatchThreads];
+  if (prev && prev[kLeft] == 0) return;
+  const int tid = threadIdx.x;
+  const int32_t v0 = blockIdx.x * kMatchThreads, v = v0 + tid;
+  uint64_t w = v < n ? st[v] : pack_state(0, kDead);
+  own[tid] = w;
+  int32_t r = round_of(w);  // round of the proposal
+  bool live = state_of(w) >= 0;
+  int32_t c[H];             // c[0]: the proposal; then the entries after it, -1: the list's end
+  int32_t k = 0, e = 0;     // place in the list of the first entry not held, its bound
+  auto fetch = [&]() {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool in = k0 + u < e;
-      j[u] = in ? ci[k0 + u] : v;
-      cc[u] = in ? c[k0 + u] : 0.0;
-    }
-    int32_t m[8], cj[8];
+    for (int i = 0; i < H; ++i) c[i] = k + i < e ? pref[k + i] : -1;
+    k += H;
+  };
+  auto advance = [&]() {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      m[u] = mate[j[u]];
-      cj[u] = cur ? cur[j[u]] : -1;
-    }
-    int32_t back[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) back[u] = cj[u] >= 0 ? cur[cj[u]] : -1;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (k0 + u >= e || j[u] == v) continue;
-      if (m[u] != kFree || (cj[u] >= 0 && back[u] == j[u])) continue;
-      const int32_t lo = min(v, j[u]), hi = max(v, j[u]);
-      if (best < 0 || better(cc[u], lo, hi, bc, blo, bhi)) {
-        best = j[u];
-        bc = cc[u];
-        blo = lo;
-        bhi = hi;
+    for (int i = 1; i < H; ++i) c[i - 1] = c[i];
+    c[H - 1] = -1;
+    if (c[0] < 0) fetch();
+  };
+  if (live) {
+    k = rb[v];
+    e = re[v];
+    fetch();
+    // entries ahead of the proposal were found taken by an earlier launch
+    while (c[0] != state_of(w)) advance();
+  }
+  __syncthreads();
+  auto inside = [&](int32_t x) { return (uint32_t)(x - v0) < (uint32_t)kMatchThreads; };
+  auto look = [&](int32_t x) -> uint64_t {
+    if (inside(x))
+      return __hip_atomic_load(&own[x - v0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __hip_atomic_load(&st[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  bool outside = true, moved = false;
+  int idle = 0, turn = 0;
+  while (__any(live)) {
+    bool step = false;
+    if (live && (outside || inside(c[0]))) {
+      w = look(c[0]);
+      int32_t s = state_of(w);
+      if (s < 0 || s == v) {
+        // taken: on to the first of the list that is not
+        while (s < 0 && s != kMatched - v) {
+          r = max(r, round_of(w));
+          advance();
+          if (c[0] < 0) break;
+          w = look(c[0]);
+          s = state_of(w);
+        }
+        int32_t next = c[0];
+        if (next < 0) {  // none left: a singleton
+          next = kDead;
+        } else if (s == v) {  // mutual: settle both, u waits for nothing else
+          r = max(r, round_of(w)) + 1;
+          const uint64_t wu = pack_state(r, kMatched - v);
+          if (inside(next))
+            __hip_atomic_store(&own[next - v0], wu, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_store(&st[next], wu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          next = kMatched - next;
+        } else if (s == kMatched - v) {  // the other end matched it already
+          r = round_of(w);
+          next = kMatched - next;
+        }
+        w = pack_state(r, next);
+        __hip_atomic_store(&own[tid], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&st[v], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        live = next >= 0;
+        step = true;
       }
     }
-  }
-  return best;
-}
-
-// For every free vertex: keep its proposal if the proposed vertex is still
-// free (the free set only shrinks, so it is still the best), else propose to
-// the best free neighbour under the strict key; a free vertex with no free
-// neighbour becomes a singleton. Flags the round if any vertex still proposes.
-__global__ void k_match_propose(int32_t n, const int32_t *rp, const int32_t *ci,
-                                const double *c, int32_t *mate, int32_t *cand,
-                                int32_t *active) {
-  const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  bool live = false;
-  if (v < n && mate[v] == kFree) {
-    const int32_t u = cand[v];
-    if (u >= 0 && mate[u] == kFree) {
-      live = true;
+    if (__any(step)) {
+      moved = true;
+      idle = 0;
+      __builtin_amdgcn_s_setprio(3);
+      outside = ++turn % 8 == 0;
+    } else if (!outside) {
+      outside = true;
     } else {
-      const int32_t best = best_free(v, rp[v], rp[v + 1], ci, c, mate, nullptr);
-      cand[v] = best;
-      if (best < 0) mate[v] = kDead; else live = true;
+      if (++idle >= kMatchSpin) break;
+      outside = idle < 8 || idle % 4 == 0;
+      if (idle >= 8) __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_s_sleep(32);
     }
   }
-  // one plain store per block that still has a proposing vertex (a per-wave
-  // atomic on one counter serialises tens of thousands of waves per round)
-  if (__syncthreads_or(live) && threadIdx.x == 0) *active = 1;
-}
-
-// Mutual proposals are locally dominant edges: match them.
-__global__ void k_match_accept(int32_t n, int32_t *mate, const int32_t *cand) {
-  const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n || mate[v] != kFree) return;
-  const int32_t u = cand[v];
-  if (u >= 0 && cand[u] == v) mate[v] = u;
-}
-
-// One round: accept the mutual proposals of `cur` and, for vertices that stay
-// free, write their next proposal into `nxt` (kept while its target stays
-// free, else the best free neighbour under the strict key; none: singleton).
-// x counts as taken in this round if it was matched or became a singleton
-// before it (mate), or is matched in it (mutual proposals in `cur`, which
-// nobody writes in this round). A stale read of mate[x] can only show a
-// vertex that becomes a singleton in this round as free; a proposal to it is
-// then repeated next round, while no free vertex is ever taken for matched.
-// `prev` is the previous round's flag (null for the first round of a batch):
-// once a round has no proposing vertex left, every free vertex has been
-// matched or made a singleton, and the rounds queued after it return at once.
-__global__ void k_match_round(int32_t n, const int32_t *rp, const int32_t *ci, const double *c,
-                              int32_t *mate, const int32_t *cur, int32_t *nxt,
-                              const int32_t *prev, int32_t *active) {
-  if (prev && *prev == 0) return;
-  const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  bool live = false;
-  if (v < n && mate[v] == kFree) {
-    // a free vertex's proposal and row bounds together, then the proposed
-    // vertex's state and proposal, then that proposal's target
-    const int32_t u = cur[v], b = rp[v], e = rp[v + 1];
-    const int32_t cu = u >= 0 ? cur[u] : -1;
-    const int32_t mu = u >= 0 ? mate[u] : kFree;
-    const int32_t ccu = cu >= 0 ? cur[cu] : -1;
-    if (u >= 0 && cu == v) {
-      mate[v] = u;
-      nxt[v] = u;
-    } else if (u >= 0 && mu == kFree && !(cu >= 0 && ccu == u)) {
-      nxt[v] = u;  // still free: still the best
-      live = true;
-    } else {
-      const int32_t best = best_free(v, b, e, ci, c, mate, cur);
-      nxt[v] = best;
-      if (best < 0) mate[v] = kDead; else live = true;
-    }
-  }
-  if (__syncthreads_or(live) && threadIdx.x == 0) *active = 1;
+  if (__any(live) && (tid & (kWave - 1)) == 0) flags[kLeft] = 1;
+  if (moved && (tid & (kWave - 1)) == 0) flags[kMoved] = 1;
 }
 
 // ---------------------------------------------------------------------------
-// 3. numbering, 4. eq. (prolongator), restriction of w
+// 3. numbering, 4. eq. (prolongator)
 // ---------------------------------------------------------------------------
 
-__global__ void k_leader(int32_t n, const int32_t *mate, int32_t *flag) {
-  const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int32_t m = mate[v];
-  flag[v] = (m < 0 || v < m) ? 1 : 0;
-}
-
-__global__ void k_assign(int32_t n, const int32_t *mate, const int32_t *id, int32_t *agg,
-                         int32_t *lead) {
-  const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int32_t m = mate[v];
-  if (m < 0 || v < m) {
-    agg[v] = id[v];
-    lead[id[v]] = v;
-  } else {
-    agg[v] = id[m];
+// mate of every vertex (-1: singleton) from its state; block scan of the
+// leaders (the smaller end of a pair, a singleton itself); the largest round
+// and the matrix's entries
+__global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint64_t *st,
+                                                          const int32_t *rb, const int32_t *re,
+                                                          int32_t *mate, int32_t *id,
+                                                          int32_t *bsum, int32_t *rounds,
+                                                          int32_t *entries) {
+  __shared__ int32_t most, sum;
+  if (threadIdx.x == 0) most = sum = 0;
+  const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
+  int32_t lead[kScanPer];
+  int32_t s = 0, r = 0, c = 0;
+  for (int k = 0; k < kScanPer; ++k) {
+    lead[k] = 0;
+    if (base + k >= n) continue;
+    const int32_t v = (int32_t)(base + k);
+    const uint64_t w = st[v];
+    const int32_t x = state_of(w), m = x <= kMatched ? kMatched - x : -1;
+    if (x < 0) r = max(r, round_of(w));
+    mate[v] = m;
+    c += re[v] - rb[v];
+    lead[k] = m < 0 || v < m ? 1 : 0;
+    s += lead[k];
+  }
+  int32_t total;
+  int32_t off = block_exclusive_scan(s, &total);
+  for (int k = 0; k < kScanPer; ++k) {
+    if (base + k < n) id[base + k] = off;
+    off += lead[k];
+  }
+  if (r > 0) atomicMax(&most, r);
+  atomicAdd(&sum, c);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    bsum[blockIdx.x] = total;
+    if (most > 0) atomicMax(rounds, most);
+    atomicAdd(entries, sum);
   }
 }
 
+// aggregates by their smallest member, and the pairwise prolongator:
 // pair {i < j}: p_v = w_v / sqrt(w_i w_i + w_j w_j); singleton: w_s / |w_s|
-__global__ void k_pair_prolongator(int32_t n, const int32_t *mate, const double *w, double *p) {
+__global__ void k_assign(int32_t n, const int32_t *mate, const int32_t *id, const int32_t *bsum,
+                         const double *w, int32_t *agg, int32_t *lead, double *p) {
   const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
   const int32_t m = mate[v];
+  const int32_t l = m >= 0 && m < v ? m : v;
+  const int32_t I = id[l] + bsum[l / (kScanBlock * kScanPer)];
+  agg[v] = I;
+  if (l == v) lead[I] = v;
   if (m < 0) {
     p[v] = w[v] / fabs(w[v]);
   } else {
-    const int32_t i = min(v, m), j = max(v, m);
-    const double s = w[i] * w[i] + w[j] * w[j];
-    p[v] = w[v] / sqrt(s);
+    const double wi = w[min(v, m)], wj = w[max(v, m)];
+    p[v] = w[v] / sqrt(wi * wi + wj * wj);
   }
 }
 
-// w_{k+1}(I) = sum over members i of I, ascending, of p_i w_i
-__global__ void k_restrict_pair(int32_t nc, const int32_t *lead, const int32_t *mate,
-                                const double *p, const double *w, double *wc) {
-  const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t i0 = lead[I], i1 = mate[i0];
-  double s = p[i0] * w[i0];
-  if (i1 >= 0) s = s + p[i1] * w[i1];
-  wc[I] = s;
-}
-
 // ---------------------------------------------------------------------------
-// 5. pairwise Galerkin product A_c = P^T A P
+// 5. pairwise Galerkin product A_c = P^T A P, w_c = P^T w
 // ---------------------------------------------------------------------------
 // Entry (I, J) sums (p_lo a_lo,hi) p_hi over the stored fine entries (i, j),
 // i in I, j in J, mapped to (lo, hi) = (min, max) and taken in ascending
 // (lo, hi) order, starting from the first term. Every structural entry is
-// kept. Each coarse row is produced in a temporary slot, then compacted.
+// kept. Row I's terms are those of its smaller member's row, then the other's,
+// each ascending in j: sorted by (J, lo) with equal keys in that order, they
+// are in ascending (lo, hi) order within each J. Row I is left in the first
+// slots of the room its terms need; only a level's own matrix is packed.
 
-__global__ void k_rap_inlen(int32_t nc, const int32_t *lead, const int32_t *mate,
-                            const int32_t *rp, int32_t *inlen) {
-  const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t i0 = lead[I], i1 = mate[i0];
-  int32_t len = rp[i0 + 1] - rp[i0];
-  if (i1 >= 0) len += rp[i1 + 1] - rp[i1];
-  inlen[I] = len;
+// block scan of the terms of the coarse rows
+__global__ void __launch_bounds__(kScanBlock) k_terms_scan(int32_t nc, const int32_t *lead,
+                                                           const int32_t *mate, const int32_t *rb,
+                                                           const int32_t *re, int32_t *off,
+                                                           int32_t *bsum) {
+  const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
+  int32_t len[kScanPer];
+  int32_t s = 0;
+  for (int k = 0; k < kScanPer; ++k) {
+    len[k] = 0;
+    if (base + k >= nc) continue;
+    const int32_t i0 = lead[base + k], i1 = mate[i0];
+    len[k] = re[i0] - rb[i0] + (i1 >= 0 ? re[i1] - rb[i1] : 0);
+    s += len[k];
+  }
+  int32_t total;
+  int32_t o = block_exclusive_scan(s, &total);
+  for (int k = 0; k < kScanPer; ++k) {
+    if (base + k < nc) off[base + k] = o;
+    o += len[k];
+  }
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-__device__ __forceinline__ bool key_less(int32_t J1, int32_t lo1, int32_t hi1, int32_t J2,
-                                         int32_t lo2, int32_t hi2) {
-  if (J1 != J2) return J1 < J2;
-  if (lo1 != lo2) return lo1 < lo2;
-  return hi1 < hi2;
+// LDS written by lanes of this wave is read by its other lanes
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ void k_rap_rows(int32_t nc, const int32_t *lead, const int32_t *mate,
-                           const int32_t *rp, const int32_t *ci, const double *val,
-                           const int32_t *agg, const double *p, const int32_t *toff,
-                           int32_t *tJ, double *tV, int32_t *cnt, int32_t *ovf,
-                           int32_t *novf) {
-  const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t mem[2] = {lead[I], mate[lead[I]]};
-  const int32_t len = toff[I + 1] - toff[I];
-  if (len > kRapCap) {
-    cnt[I] = 0;
-    ovf[atomicAdd(novf, 1)] = I;
+// One sweep's coarse matrix in the making
+struct Coarsened {
+  const int32_t *lead, *mate, *agg;  // coarse -> smaller member, pairs, fine -> coarse
+  const double *p, *w;               // prolongator and smooth vector of the fine level
+  const int32_t *off, *bsum;         // where row I's room starts: off[I] + its block's bsum
+  int32_t *b, *e, *ci;               // the coarse rows
+  double *val, *wc, *dg;             // their values, restricted w, diagonal
+};
+
+__device__ __forceinline__ void term_of(const RowsOf &A, const Coarsened &C, int32_t f, int32_t k,
+                                        uint64_t *key, double *t) {
+  const int32_t j = A.ci[k];
+  const int32_t lo = min(f, j), hi = max(f, j);
+  *key = ((uint64_t)(uint32_t)C.agg[j] << 32) | (uint32_t)lo;
+  *t = (C.p[lo] * A.val[k]) * C.p[hi];
+}
+
+// G lanes per coarse row, two terms per lane (rows of at most 2 G terms; longer
+// ones are listed for k_rap_long): the terms are ranked against the row's keys
+// in LDS, put in order there, and the first lane of every run of one column
+// adds it up (four terms at most). What bounds it is the gathers of agg and p
+// per term; loads of the fine rows and stores of the coarse ones are coalesced.
+template <int G>
+__global__ void __launch_bounds__(kBlock) k_rap(int32_t nc, RowsOf A, Coarsened C, int32_t *ovf,
+                                                int32_t *novf) {
+  constexpr int kCap = 2 * G;
+  __shared__ uint64_t skey[kBlock / G][kCap];
+  __shared__ double sval[kBlock / G][kCap];
+  __shared__ int32_t scol[kBlock / G][kCap];
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t I = (int32_t)(t / G);
+  const int lane = (int)(t % G), grp = threadIdx.x / G;
+  if (t / G >= nc) return;  // whole groups
+  const int32_t i0 = C.lead[I], i1 = C.mate[i0];
+  const int32_t b0 = A.b[i0], l0 = A.e[i0] - b0;
+  const int32_t b1 = i1 >= 0 ? A.b[i1] : 0, l1 = i1 >= 0 ? A.e[i1] - b1 : 0;
+  const int32_t len = l0 + l1;
+  const int32_t base = C.off[I] + C.bsum[I / (kScanBlock * kScanPer)];
+  if (lane == 0) {
+    C.b[I] = base;
+    double s = C.p[i0] * C.w[i0];
+    if (i1 >= 0) s = s + C.p[i1] * C.w[i1];
+    C.wc[I] = s;
+  }
+  if (len > kCap) {
+    if (lane == 0) {
+      C.e[I] = base;
+      C.dg[I] = 0.0;
+      ovf[atomicAdd(novf, 1)] = I;
+    }
     return;
   }
-  int32_t J[kRapCap], LO[kRapCap], HI[kRapCap];
-  double T[kRapCap];
-  int32_t m = 0;
+  uint64_t key[2];
+  double v[2];
+#pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int32_t f = mem[q];
-    if (f < 0) continue;
-    for (int32_t k = rp[f]; k < rp[f + 1]; ++k) {
-      const int32_t j = ci[k];
-      const int32_t lo = min(f, j), hi = max(f, j);
-      const double t = (p[lo] * val[k]) * p[hi];
-      // insertion into the sorted prefix
-      int32_t pos = m;
-      const int32_t Jj = agg[j];
-      while (pos > 0 && key_less(Jj, lo, hi, J[pos - 1], LO[pos - 1], HI[pos - 1])) {
-        J[pos] = J[pos - 1];
-        LO[pos] = LO[pos - 1];
-        HI[pos] = HI[pos - 1];
-        T[pos] = T[pos - 1];
-        --pos;
+    const int32_t e = lane + q * G;
+    key[q] = 0;
+    v[q] = 0.0;
+    if (e < len) {
+      if (e < l0) term_of(A, C, i0, b0 + e, &key[q], &v[q]);
+      else term_of(A, C, i1, b1 + (e - l0), &key[q], &v[q]);
+      skey[grp][e] = key[q];
+    }
+  }
+  wave_sync();
+  int32_t rank[2] = {0, 0};
+  for (int32_t f = 0; f < len; ++f) {
+    const uint64_t kf = skey[grp][f];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (kf < key[q] || (kf == key[q] && f < lane + q * G)) ++rank[q];
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (lane + q * G < len) {
+      scol[grp][rank[q]] = (int32_t)(key[q] >> 32);
+      sval[grp][rank[q]] = v[q];
+    }
+  wave_sync();
+  const int shift = (int)(threadIdx.x & (kWave - 1)) / G * G;
+  const uint64_t mask = G == kWave ? ~0ull : (1ull << (G % kWave)) - 1;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+  int32_t before = 0;
+  bool dg = false;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int32_t e = lane + q * G;
+    const int32_t J = e < len ? scol[grp][e] : -1;
+    const bool head = e < len && (e == 0 || scol[grp][e - 1] != J);
+    const uint64_t heads = (__ballot(head) >> shift) & mask;
+    if (head) {
+      double s = sval[grp][e];
+      for (int32_t f = e + 1; f < len && scol[grp][f] == J; ++f) s = s + sval[grp][f];
+      const int32_t o = base + before + __popcll(heads & below);
+      C.ci[o] = J;
+      C.val[o] = s;
+      if (J == I) {
+        C.dg[I] = s;
+        dg = true;
       }
-      J[pos] = Jj;
-      LO[pos] = lo;
-      HI[pos] = hi;
-      T[pos] = t;
-      ++m;
     }
+    before += __popcll(heads);
   }
-  const int32_t base = toff[I];
-  int32_t out = 0;
-  double s = 0.0;
-  for (int32_t e = 0; e < m; ++e) {
-    if (e == 0 || J[e] != J[e - 1]) {
-      if (e > 0) tV[base + out - 1] = s;
-      tJ[base + out] = J[e];
-      s = T[e];
-      ++out;
-    } else {
-      s = s + T[e];
-    }
+  const uint64_t has = (__ballot(dg) >> shift) & mask;
+  if (lane == 0) {
+    C.e[I] = base + before;
+    if (!has) C.dg[I] = 0.0;
   }
-  if (out > 0) tV[base + out - 1] = s;
-  cnt[I] = out;
 }
 
-// Rows whose two fine rows hold more than kRapCap entries: one block per row,
-// entries ranked in LDS by the same key, then summed in order.
-__global__ void __launch_bounds__(256) k_rap_long(
-    const int32_t *lead, const int32_t *mate, const int32_t *rp, const int32_t *ci,
-    const double *val, const int32_t *agg, const double *p, const int32_t *toff, int32_t *tJ,
-    double *tV, int32_t *cnt, const int32_t *ovf, const int32_t *novf, int32_t *err) {
-  __shared__ int32_t sJ[kRapLongCap], sLO[kRapLongCap], sHI[kRapLongCap];
-  __shared__ double sT[kRapLongCap];
-  __shared__ int16_t order[kRapLongCap];
+// Listed rows, one block each. More than kRapLongCap terms: kErrArg.
+__global__ void __launch_bounds__(kBlock) k_rap_long(RowsOf A, Coarsened C, const int32_t *ovf,
+                                                     const int32_t *novf, int32_t *err) {
+  __shared__ uint64_t skey[kRapLongCap];
+  __shared__ double sval[kRapLongCap];
+  __shared__ int32_t scol[kRapLongCap];
+  __shared__ int32_t wsum[kBlock / kWave];
+  constexpr int kPer = kRapLongCap / kBlock;
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   const int32_t count = *novf;
   for (int32_t o = blockIdx.x; o < count; o += gridDim.x) {
     const int32_t I = ovf[o];
-    const int32_t i0 = lead[I], i1 = mate[i0];
-    const int32_t l0 = rp[i0 + 1] - rp[i0];
-    const int32_t len = toff[I + 1] - toff[I];
-    if (len > kRapLongCap) {
-      if (threadIdx.x == 0) {
-        atomicOr(err, kErrArg);
-        cnt[I] = 0;
-      }
+    const int32_t i0 = C.lead[I], i1 = C.mate[i0];
+    const int32_t b0 = A.b[i0], l0 = A.e[i0] - b0;
+    const int32_t b1 = i1 >= 0 ? A.b[i1] : 0, l1 = i1 >= 0 ? A.e[i1] - b1 : 0;
+    const int32_t len = l0 + l1, base = C.b[I];
+    if (len > kRapLongCap || len < 0) {
+      if (threadIdx.x == 0) atomicOr(err, kErrArg);
       continue;
     }
-    for (int32_t e = threadIdx.x; e < len; e += blockDim.x) {
-      const int32_t f = e < l0 ? i0 : i1;
-      const int32_t k = e < l0 ? rp[i0] + e : rp[i1] + (e - l0);
-      const int32_t j = ci[k];
-      const int32_t lo = min(f, j), hi = max(f, j);
-      sJ[e] = agg[j];
-      sLO[e] = lo;
-      sHI[e] = hi;
-      sT[e] = (p[lo] * val[k]) * p[hi];
+    __syncthreads();  // the previous row's terms are read no more
+    double v[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int32_t e = threadIdx.x + q * kBlock;
+      v[q] = 0.0;
+      if (e >= len) continue;
+      uint64_t key;
+      if (e < l0) term_of(A, C, i0, b0 + e, &key, &v[q]);
+      else term_of(A, C, i1, b1 + (e - l0), &key, &v[q]);
+      skey[e] = key;
     }
     __syncthreads();
-    for (int32_t e = threadIdx.x; e < len; e += blockDim.x) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int32_t e = threadIdx.x + q * kBlock;
+      if (e >= len) continue;
+      const uint64_t ke = skey[e];
       int32_t rank = 0;
       for (int32_t f = 0; f < len; ++f) {
-        const bool lt = key_less(sJ[f], sLO[f], sHI[f], sJ[e], sLO[e], sHI[e]);
-        const bool eq = sJ[f] == sJ[e] && sLO[f] == sLO[e] && sHI[f] == sHI[e];
-        rank += (lt || (eq && f < e)) ? 1 : 0;
+        const uint64_t kf = skey[f];
+        rank += (kf < ke || (kf == ke && f < e)) ? 1 : 0;
       }
-      order[rank] = (int16_t)e;
+      scol[rank] = (int32_t)(ke >> 32);
+      sval[rank] = v[q];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      const int32_t base = toff[I];
-      int32_t out = 0;
-      double s = 0.0;
-      int32_t prevJ = -1;
-      for (int32_t q = 0; q < len; ++q) {
-        const int32_t e = order[q];
-        if (q == 0 || sJ[e] != prevJ) {
-          if (q > 0) tV[base + out - 1] = s;
-          tJ[base + out] = sJ[e];
-          s = sT[e];
-          prevJ = sJ[e];
-          ++out;
-        } else {
-          s = s + sT[e];
-        }
+    int32_t out = base;
+    for (int32_t e0 = 0; e0 < len; e0 += kBlock) {
+      const int32_t e = e0 + threadIdx.x;
+      const int32_t J = e < len ? scol[e] : -1;
+      const bool head = e < len && (e == 0 || scol[e - 1] != J);
+      const uint64_t heads = __ballot(head);
+      if (lane == 0) wsum[wid] = __popcll(heads);
+      __syncthreads();
+      int32_t at = out, all = 0;
+      for (int k = 0; k < kBlock / kWave; ++k) {
+        if (k < wid) at += wsum[k];
+        all += wsum[k];
       }
-      if (out > 0) tV[base + out - 1] = s;
-      cnt[I] = out;
+      if (head) {
+        double s = sval[e];
+        for (int32_t f = e + 1; f < len && scol[f] == J; ++f) s = s + sval[f];
+        at += __popcll(heads & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))));
+        C.ci[at] = J;
+        C.val[at] = s;
+        if (J == I) C.dg[I] = s;
+      }
+      out += all;
+      __syncthreads();
     }
-    __syncthreads();
+    if (threadIdx.x == 0) C.e[I] = out;
   }
 }
 
-__global__ void k_rap_copy(int32_t nc, const int32_t *toff, const int32_t *tJ,
-                           const double *tV, const int32_t *rpc, int32_t *cic,
-                           double *valc) {
-  const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t src = toff[I], dst = rpc[I], len = rpc[I + 1] - rpc[I];
-  for (int32_t e = 0; e < len; ++e) {
-    cic[dst + e] = tJ[src + e];
-    valc[dst + e] = tV[src + e];
+// lengths of a matrix's rows
+__global__ void k_row_len(int32_t n, const int32_t *rb, const int32_t *re, int32_t *len) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) len[i] = re[i] - rb[i];
+}
+
+// rows packed into a CSR, eight lanes per row
+__global__ void k_pack(int32_t n, RowsOf A, const int32_t *__restrict__ rp,
+                       int32_t *__restrict__ ci, double *__restrict__ val) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t i = (int32_t)(t / 8);
+  if (t / 8 >= n) return;
+  const int32_t b = A.b[i], len = A.e[i] - b, d = rp[i];
+  for (int32_t k = (int32_t)(t % 8); k < len; k += 8) {
+    ci[d + k] = A.ci[b + k];
+    val[d + k] = A.val[b + k];
   }
 }
 
@@ -582,18 +847,22 @@ __global__ void k_rap_copy(int32_t nc, const int32_t *toff, const int32_t *tJ,
 // ---------------------------------------------------------------------------
 
 // P_l(i) = ((p_1(i) p_2(agg_1(i))) p_3(...)), agg_l = ... o agg_2 o agg_1
-__global__ void k_compose(int32_t n, const int32_t *agg_k, const double *p_k, int32_t *agg_c,
-                          double *p_c, int32_t first) {
+constexpr int kMaxSweeps = 8;  // amg_params.sweeps
+struct SweepMaps {
+  const int32_t *agg[kMaxSweeps];
+  const double *p[kMaxSweeps];
+};
+__global__ void k_compose(int32_t n, int32_t sweeps, SweepMaps M, int32_t *agg, double *p) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  if (first) {
-    agg_c[i] = agg_k[i];
-    p_c[i] = p_k[i];
-  } else {
-    const int32_t a = agg_c[i];
-    p_c[i] = p_c[i] * p_k[a];
-    agg_c[i] = agg_k[a];
+  int32_t a = M.agg[0][i];
+  double v = M.p[0][i];
+  for (int32_t k = 1; k < sweeps; ++k) {
+    v = v * M.p[k][a];
+    a = M.agg[k][a];
   }
+  agg[i] = a;
+  p[i] = v;
 }
 
 __global__ void k_member_size(int32_t nc, const int32_t *lead, const int32_t *mate,
@@ -912,17 +1181,18 @@ amg_status map_err(int32_t flags) {
   return AMG_OK;
 }
 
-// A matrix of the current sweep: either a level's (borrowed) or a temporary.
+// A matrix of the current sweep: a level's (borrowed) or a temporary.
 struct Mat {
   int32_t n = 0;
-  int64_t nnz = 0;
-  int32_t *rp = nullptr, *ci = nullptr;
-  double *val = nullptr;
-  double *w = nullptr;
+  int64_t most = 0;   // at least its number of entries
+  double mean = 0.0;  // about the mean row's entries
+  RowsOf rows{};
+  const double *w = nullptr;
+  const double *dg = nullptr;  // its diagonal
 };
 
-// One pairwise sweep on A (Section 3.2). On return with nc < n, the outputs
-// hold the coarse matrix and vectors; nc == n means nothing was matched.
+// One pairwise sweep on A (Section 3.2). nc == n means nothing was matched;
+// else the outputs hold the coarse matrix and the maps.
 struct SweepOut {
   Mat Ac;
   int32_t nc = 0;
@@ -931,143 +1201,162 @@ struct SweepOut {
   int32_t *lead = nullptr;  // coarse -> smallest member (nc)
   int32_t *mate = nullptr;  // n
   int32_t rounds = 0;
+  const int32_t *err = nullptr;  // control block: kErr* of the product
 };
 
-amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
-                          double *t_match, double *t_number, double *t_rap) {
-  hipStream_t s = h->stream;
-  const int32_t n = A.n;
-  double t0 = now_ms();
-  int32_t *dpos, *mate, *cand, *cand2, *counters;
-  double *c;
-  AMG_TRY(tmp.get(&dpos, n));
-  AMG_TRY(tmp.get(&c, A.nnz));
-  AMG_TRY(tmp.get(&mate, n));
-  AMG_TRY(tmp.get(&cand, n));
-  AMG_TRY(tmp.get(&cand2, n));
-  constexpr int kMaxBatch = 128;
-  AMG_TRY(tmp.get(&counters, kMaxBatch));
-  k_diag_pos<<<grid(n), kBlock, 0, s>>>(n, A.rp, A.ci, dpos);
-  k_weights<<<grid(n), kBlock, 0, s>>>(n, A.rp, A.ci, A.val, dpos, A.w, c);
-  k_fill<int32_t><<<grid(n), kBlock, 0, s>>>(mate, kFree, n);
-  k_fill<int32_t><<<grid(n), kBlock, 0, s>>>(cand, -1, n);
-  // matching rounds in batches; the host reads the per-round counters after
-  // each batch (rounds past the last live one do nothing)
-  // first proposals, then one fused accept-and-propose kernel per round with
-  // the proposals double-buffered; the last round's accept is applied after
-  // rounds queued after the last live one return at once, so batches can be
-  // long: 8, 16, ... up to kMaxBatch rounds between host checks
-  int32_t rounds = 0, batch = 8;
-  int32_t hc[kMaxBatch];
-  int32_t *cur = cand, *nxt = cand2;
-  k_fill<int32_t><<<1, kMaxBatch, 0, s>>>(counters, 0, kMaxBatch);
-  k_match_propose<<<grid(n), kBlock, 0, s>>>(n, A.rp, A.ci, c, mate, cur, counters);
-  for (;;) {
-    k_fill<int32_t><<<1, kMaxBatch, 0, s>>>(counters, 0, kMaxBatch);
-    for (int32_t r = 0; r < batch; ++r) {
-      k_match_round<<<grid(n), kBlock, 0, s>>>(n, A.rp, A.ci, c, mate, cur, nxt,
-                                               r > 0 ? counters + r - 1 : nullptr, counters + r);
-      std::swap(cur, nxt);
-    }
-    AMG_HIP(hipMemcpyAsync(hc, counters, sizeof(int32_t) * batch, hipMemcpyDeviceToHost, s));
-    AMG_HIP(hipStreamSynchronize(s));
-    int32_t r = 0;
-    while (r < batch && hc[r] > 0) ++r;
-    rounds += r;
-    if (r < batch) break;
-    if (rounds > n + 2) return AMG_ERR_HIP;  // cannot happen: one edge per round at least
-    batch = batch * 2 > kMaxBatch ? kMaxBatch : batch * 2;
-  }
-  // the proposals of the last live round may still hold mutual pairs
-  k_match_accept<<<grid(n), kBlock, 0, s>>>(n, mate, cur);
-  o.rounds = rounds;
-  o.mate = mate;
-  tmp.drop(cand2);
-  tmp.drop(cand);
-  tmp.drop(c);
-  double t1 = now_ms();
-  *t_match += t1 - t0;
+// words of a sweep's control block (zeroed at its start, read back with nc)
+enum : int32_t {
+  kCtlErr = 0,       // kErr*
+  kCtlRounds = 1,    // largest matching round
+  kCtlPrefLong = 2,  // rows listed for k_pref_long
+  kCtlRapLong = 3,   // rows listed for k_rap_long
+  kCtlEntries = 4,   // entries of the sweep's matrix
+  kCtlFlags = 5      // kMatchFlags per queued launch of k_match
+};
+constexpr int kMatchQueue = 4;  // launches of k_match between host checks, at most
+static_assert(kCtlFlags + kMatchQueue * kMatchFlags <= kCtl, "control block");
 
-  // numbering
-  int32_t *flag, *id;
-  AMG_TRY(tmp.get(&flag, n));
-  AMG_TRY(tmp.get(&id, n + 1));
-  k_leader<<<grid(n), kBlock, 0, s>>>(n, mate, flag);
-  AMG_TRY(tmp.scan(flag, id, n));
-  int32_t nc = 0;
-  AMG_TRY(read_i32(id + n, &nc, s));
-  o.nc = nc;
-  if (nc == n) {
-    *t_number += now_ms() - t1;
-    return AMG_OK;
-  }
-  AMG_TRY(tmp.get(&o.agg, n));
-  AMG_TRY(tmp.get(&o.lead, nc));
-  AMG_TRY(tmp.get(&o.p, n));
-  k_assign<<<grid(n), kBlock, 0, s>>>(n, mate, id, o.agg, o.lead);
-  k_pair_prolongator<<<grid(n), kBlock, 0, s>>>(n, mate, A.w, o.p);
-  tmp.drop(flag);
-  tmp.drop(id);
-  double t2 = now_ms();
-  *t_number += t2 - t1;
+template <int G>
+void launch_pref(const Mat &A, int32_t *pref, uint64_t *st, int32_t *ovf, int32_t *ctl,
+                 hipStream_t s) {
+  k_pref<G><<<grid((int64_t)A.n * G), kBlock, 0, s>>>(A.n, A.rows, A.w, A.dg, pref, st, ovf,
+                                                      ctl + kCtlPrefLong);
+}
 
-  // Galerkin product and restricted w
-  int32_t *inlen, *toff, *tJ, *cnt, *ovf, *novf, *err;
-  double *tV;
-  AMG_TRY(tmp.get(&inlen, nc));
-  AMG_TRY(tmp.get(&toff, nc + 1));
-  AMG_TRY(tmp.get(&cnt, nc));
-  AMG_TRY(tmp.get(&ovf, nc));
-  AMG_TRY(tmp.get(&novf, 2));
-  err = novf + 1;
-  k_fill<int32_t><<<1, 2, 0, s>>>(novf, 0, 2);
-  k_rap_inlen<<<grid(nc), kBlock, 0, s>>>(nc, o.lead, mate, A.rp, inlen);
-  AMG_TRY(tmp.scan(inlen, toff, nc));
-  AMG_TRY(tmp.get(&tJ, A.nnz));
-  AMG_TRY(tmp.get(&tV, A.nnz));
-  k_rap_rows<<<grid(nc), kBlock, 0, s>>>(nc, o.lead, mate, A.rp, A.ci, A.val, o.agg, o.p, toff,
-                                         tJ, tV, cnt, ovf, novf);
-  k_rap_long<<<256, 256, 0, s>>>(o.lead, mate, A.rp, A.ci, A.val, o.agg, o.p, toff, tJ, tV, cnt,
-                                 ovf, novf, err);
-  int32_t herr = 0;
-  AMG_TRY(read_i32(err, &herr, s));
-  if (herr) return AMG_ERR_ARG;  // a coarse row gathers more than kRapLongCap entries
-  Mat &C = o.Ac;
-  C.n = nc;
-  AMG_TRY(tmp.get(&C.rp, nc + 1));
-  AMG_TRY(tmp.scan(cnt, C.rp, nc));
-  int32_t nnzc = 0;
-  AMG_TRY(read_i32(C.rp + nc, &nnzc, s));
-  C.nnz = nnzc;
-  AMG_TRY(tmp.get(&C.ci, nnzc));
-  AMG_TRY(tmp.get(&C.val, nnzc));
-  AMG_TRY(tmp.get(&C.w, nc));
-  k_rap_copy<<<grid(nc), kBlock, 0, s>>>(nc, toff, tJ, tV, C.rp, C.ci, C.val);
-  k_restrict_pair<<<grid(nc), kBlock, 0, s>>>(nc, o.lead, mate, o.p, A.w, C.w);
+template <int G>
+void launch_rap(int32_t nc, const RowsOf &A, const Coarsened &C, int32_t *ovf, int32_t *ctl,
+                hipStream_t s) {
+  k_rap<G><<<grid((int64_t)nc * G), kBlock, 0, s>>>(nc, A, C, ovf, ctl + kCtlRapLong);
+}
+
+// the host's copy of the control block and of the total scanned last
+amg_status read_ctl(const int32_t *pinned, int32_t *host, hipStream_t s) {
   AMG_HIP(hipStreamSynchronize(s));
-  tmp.drop(inlen);
-  tmp.drop(toff);
-  tmp.drop(tJ);
-  tmp.drop(tV);
-  tmp.drop(cnt);
-  tmp.drop(ovf);
-  tmp.drop(dpos);
-  *t_rap += now_ms() - t2;
+  for (int k = 0; k <= kCtl; ++k) host[k] = reinterpret_cast<const volatile int32_t *>(pinned)[k];
   return AMG_OK;
 }
 
-// copy a temporary matrix into hierarchy-owned level storage
-amg_status adopt_level(amg_hierarchy *h, const Mat &M, Level &L) {
+amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
+                          double *t_match, double *t_rap) {
   hipStream_t s = h->stream;
+  const int32_t n = A.n;
+  int32_t *const pinned = reinterpret_cast<int32_t *>(h->scal_host);
+  const double t0 = now_ms();
+  int32_t *pref, *ctl, *id, *bsum, *ovf;
+  uint64_t *st;
+  AMG_TRY(tmp.get(&pref, A.most));
+  AMG_TRY(tmp.get(&st, n));
+  AMG_TRY(tmp.get(&ctl, kCtl));
+  AMG_TRY(tmp.get(&id, n));
+  AMG_TRY(tmp.get(&bsum, (size_t)scan_blocks(n) + 1));
+  AMG_TRY(tmp.get(&ovf, n));
+  AMG_TRY(tmp.get(&o.mate, n));
+  const int32_t nmatch = ceil_div(n, kMatchThreads);
+  k_fill<int32_t><<<1, kCtl, 0, s>>>(ctl, 0, kCtl);
+  // lanes per row: the mean row (of a sweep's matrix: of the one before it)
+  // fills half of a group's places, so that most rows still fit
+  const double mean = A.mean;
+  if (mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, s);
+  else if (mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, s);
+  else if (mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, s);
+  else launch_pref<64>(A, pref, st, ovf, ctl, s);
+  k_pref_long<<<n < 2048 ? n : 2048, kBlock, 0, s>>>(A.rows, A.w, A.dg, pref, st, ovf,
+                                                     ctl + kCtlPrefLong, ctl + kCtlErr);
+  // matching, and the numbering of what it gives; where it takes more than
+  // the launches queued, both again from there on
+  int32_t hc[kCtl + 1];
+  for (int queue = 2;; queue = kMatchQueue) {
+    for (int r = 0; r < queue; ++r) {
+      int32_t *f = ctl + kCtlFlags + r * kMatchFlags;
+      k_match<<<nmatch, kMatchThreads, 0, s>>>(n, A.rows.b, A.rows.e, pref, st,
+                                               r > 0 ? f - kMatchFlags : nullptr, f);
+    }
+    k_lead_scan<<<scan_blocks(n), kScanBlock, 0, s>>>(n, st, A.rows.b, A.rows.e, o.mate, id, bsum,
+                                                      ctl + kCtlRounds, ctl + kCtlEntries);
+    k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), ctl, pinned);
+    AMG_HIP(hipGetLastError());
+    AMG_TRY(read_ctl(pinned, hc, s));
+    if (hc[kCtlErr]) return AMG_ERR_ARG;  // a row too long for the Galerkin product
+    const int32_t *last = hc + kCtlFlags + (queue - 1) * kMatchFlags;
+    if (!last[kLeft]) break;  // (the last launch does nothing once one before it left nothing)
+    if (!last[kMoved]) return AMG_ERR_HIP;  // cannot happen on a symmetric matrix
+    k_fill<int32_t><<<1, kCtl - kCtlEntries, 0, s>>>(ctl + kCtlEntries, 0, kCtl - kCtlEntries);
+  }
+  o.rounds = hc[kCtlRounds] > 0 ? hc[kCtlRounds] - 1 : 0;
+  const int32_t nc = hc[kCtl];
+  o.nc = nc;
+  const double t1 = now_ms();
+  *t_match += t1 - t0;
+  if (nc == n) return AMG_OK;
+  AMG_TRY(tmp.get(&o.agg, n));
+  AMG_TRY(tmp.get(&o.lead, nc));
+  AMG_TRY(tmp.get(&o.p, n));
+  k_assign<<<grid(n), kBlock, 0, s>>>(n, o.mate, id, bsum, A.w, o.agg, o.lead, o.p);
+
+  // Galerkin product and restricted w
+  Coarsened C{};
+  int32_t *off, *bsum2;
+  AMG_TRY(tmp.get(&off, nc));
+  AMG_TRY(tmp.get(&bsum2, (size_t)scan_blocks(nc) + 1));
+  AMG_TRY(tmp.get(&C.b, nc));
+  AMG_TRY(tmp.get(&C.e, nc));
+  AMG_TRY(tmp.get(&C.ci, hc[kCtlEntries]));
+  AMG_TRY(tmp.get(&C.val, hc[kCtlEntries]));
+  AMG_TRY(tmp.get(&C.wc, nc));
+  AMG_TRY(tmp.get(&C.dg, nc));
+  C.lead = o.lead;
+  C.mate = o.mate;
+  C.agg = o.agg;
+  C.p = o.p;
+  C.w = A.w;
+  C.off = off;
+  C.bsum = bsum2;
+  k_terms_scan<<<scan_blocks(nc), kScanBlock, 0, s>>>(nc, o.lead, o.mate, A.rows.b, A.rows.e, off,
+                                                      bsum2);
+  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum2, scan_blocks(nc));
+  // lanes per coarse row: room for the mean row's terms and an eighth more (the
+  // 7-point stencil's 14 terms take the 16 places of eight lanes)
+  const double terms = 1.125 * hc[kCtlEntries] / nc;
+  if (terms <= 16.0) launch_rap<8>(nc, A.rows, C, ovf, ctl, s);
+  else if (terms <= 32.0) launch_rap<16>(nc, A.rows, C, ovf, ctl, s);
+  else if (terms <= 64.0) launch_rap<32>(nc, A.rows, C, ovf, ctl, s);
+  else launch_rap<64>(nc, A.rows, C, ovf, ctl, s);
+  k_rap_long<<<nc < 1024 ? nc : 1024, kBlock, 0, s>>>(A.rows, C, ovf, ctl + kCtlRapLong,
+                                                      ctl + kCtlErr);
+  AMG_HIP(hipGetLastError());
+  o.Ac.n = nc;
+  o.Ac.most = hc[kCtlEntries];
+  o.Ac.mean = (double)hc[kCtlEntries] / n;
+  o.Ac.rows = RowsOf{C.b, C.e, C.ci, C.val};
+  o.Ac.w = C.wc;
+  o.Ac.dg = C.dg;
+  o.err = ctl + kCtlErr;
+  *t_rap += now_ms() - t1;
+  return AMG_OK;
+}
+
+// the last sweep's matrix, packed into level storage
+amg_status adopt_level(amg_hierarchy *h, Tmp &tmp, const Mat &M, const int32_t *err, Level &L) {
+  hipStream_t s = h->stream;
+  int32_t *const pinned = reinterpret_cast<int32_t *>(h->scal_host);
+  int32_t *len, *bsum;
+  AMG_TRY(tmp.get(&len, M.n));
+  AMG_TRY(tmp.get(&bsum, (size_t)scan_blocks(M.n) + 1));
   L.n = M.n;
-  L.nnz = M.nnz;
   AMG_TRY(dalloc(h, &L.rp, (size_t)M.n + 1));
-  AMG_TRY(dalloc(h, &L.ci, (size_t)M.nnz));
-  AMG_TRY(dalloc(h, &L.val, (size_t)M.nnz));
+  k_row_len<<<grid(M.n), kBlock, 0, s>>>(M.n, M.rows.b, M.rows.e, len);
+  const int32_t nb = scan_blocks(M.n);
+  k_scan_local<<<nb, kScanBlock, 0, s>>>(len, L.rp, bsum, M.n);
+  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, nb, err, pinned);
+  k_scan_add<<<grid((int64_t)M.n + 1), kBlock, 0, s>>>(L.rp, bsum, M.n, nb);
+  int32_t hc[kCtl + 1];
+  AMG_TRY(read_ctl(pinned, hc, s));
+  if (hc[kCtlErr]) return AMG_ERR_ARG;  // a coarse row gathers more than kRapLongCap entries
+  L.nnz = hc[kCtl];
+  AMG_TRY(dalloc(h, &L.ci, (size_t)L.nnz));
+  AMG_TRY(dalloc(h, &L.val, (size_t)L.nnz));
   AMG_TRY(dalloc(h, &L.w, (size_t)M.n));
-  AMG_HIP(hipMemcpyAsync(L.rp, M.rp, sizeof(int32_t) * (M.n + 1), hipMemcpyDeviceToDevice, s));
-  AMG_HIP(hipMemcpyAsync(L.ci, M.ci, sizeof(int32_t) * M.nnz, hipMemcpyDeviceToDevice, s));
-  AMG_HIP(hipMemcpyAsync(L.val, M.val, sizeof(double) * M.nnz, hipMemcpyDeviceToDevice, s));
+  k_pack<<<grid((int64_t)M.n * 8), kBlock, 0, s>>>(M.n, M.rows, L.rp, L.ci, L.val);
   AMG_HIP(hipMemcpyAsync(L.w, M.w, sizeof(double) * M.n, hipMemcpyDeviceToDevice, s));
   return AMG_OK;
 }
@@ -1116,6 +1405,10 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   } attach{h};
   h->setup_arena = &arena;
   Tmp tmp(h);
+  // (pinned: the scalars of a solve later, small results of the setup's kernels now)
+  if (!h->scal_host)
+    AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), sizeof(PcgScal)));
+  static_assert(sizeof(PcgScal) >= sizeof(int32_t) * (kCtl + 1), "control block and total");
 
   // validation
   int32_t *err;
@@ -1170,64 +1463,46 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     }
   }
 
-  double t_match = 0, t_number = 0, t_rap = 0, t_compose = 0;
+  double t_match = 0, t_rap = 0, t_compose = 0;
   for (int32_t l = 0;; ++l) {
     const int32_t n = h->lv[l].n;
     if (n <= P.max_coarse || l == P.max_levels - 1) break;
-    Mat cur{h->lv[l].n, h->lv[l].nnz, h->lv[l].rp, h->lv[l].ci, h->lv[l].val, h->lv[l].w};
-    Tmp sweep_tmp(h);  // intermediate sweep matrices
-    int32_t *agg_c = nullptr, *mptr = nullptr, *mem = nullptr;
-    double *p_c = nullptr;
-    AMG_TRY(sweep_tmp.get(&agg_c, n));
-    AMG_TRY(sweep_tmp.get(&p_c, n));
-    AMG_TRY(sweep_tmp.get(&mptr, n + 1));
-    AMG_TRY(sweep_tmp.get(&mem, n));
+    const Level &A0 = h->lv[l];
+    double *dg;
+    AMG_TRY(tmp.get(&dg, n));
+    const RowsOf rows{A0.rp, A0.rp + 1, A0.ci, A0.val};
+    k_diag<<<grid(n), kBlock, 0, s>>>(n, rows, dg);
+    Mat cur{n, A0.nnz, (double)A0.nnz / n, rows, A0.w, dg};
+    int32_t *mptr, *mem;
+    AMG_TRY(tmp.get(&mptr, (size_t)n + 1));
+    AMG_TRY(tmp.get(&mem, n));
     k_iota<<<grid((int64_t)n + 1), kBlock, 0, s>>>(mptr, n);
     k_iota<<<grid(n), kBlock, 0, s>>>(mem, n - 1);
     int32_t done = 0, rounds = 0;
-    std::vector<Tmp *> owners;
-    Tmp *prev_owner = nullptr;
+    SweepMaps maps{};
+    const int32_t *err_ctl = nullptr;
     for (int32_t k = 0; k < P.sweeps; ++k) {
-      Tmp *own = new Tmp(h);
       SweepOut o;
-      amg_status st = pairwise_sweep(h, *own, cur, o, &t_match, &t_number, &t_rap);
-      if (st != AMG_OK) {
-        delete own;
-        delete prev_owner;
-        return st;
-      }
+      AMG_TRY(pairwise_sweep(h, tmp, cur, o, &t_match, &t_rap));
       rounds += o.rounds;
-      if (o.nc == cur.n) {  // nothing matched: end this level's sweeps
-        delete own;
-        break;
-      }
-      double tc = now_ms();
-      k_compose<<<grid(n), kBlock, 0, s>>>(n, o.agg, o.p, agg_c, p_c, k == 0 ? 1 : 0);
+      if (o.nc == cur.n) break;  // nothing matched: end this level's sweeps
+      maps.agg[k] = o.agg;
+      maps.p[k] = o.p;
       int32_t *msz, *mptr_n, *mem_n;
-      AMG_TRY(sweep_tmp.get(&msz, o.nc));
-      AMG_TRY(sweep_tmp.get(&mptr_n, o.nc + 1));
-      AMG_TRY(sweep_tmp.get(&mem_n, n));
+      AMG_TRY(tmp.get(&msz, o.nc));
+      AMG_TRY(tmp.get(&mptr_n, (size_t)o.nc + 1));
+      AMG_TRY(tmp.get(&mem_n, n));
       k_member_size<<<grid(o.nc), kBlock, 0, s>>>(o.nc, o.lead, o.mate, mptr, msz);
-      AMG_TRY(sweep_tmp.scan(msz, mptr_n, o.nc));
+      AMG_TRY(tmp.scan(msz, mptr_n, o.nc));
       k_member_merge<<<grid(o.nc), kBlock, 0, s>>>(o.nc, o.lead, o.mate, mptr, mem, mptr_n,
                                                    mem_n);
-      AMG_HIP(hipStreamSynchronize(s));
-      sweep_tmp.drop(mptr);
-      sweep_tmp.drop(mem);
-      sweep_tmp.drop(msz);
       mptr = mptr_n;
       mem = mem_n;
-      // the previous sweep's matrix is no longer needed
-      delete prev_owner;
-      prev_owner = own;
+      err_ctl = o.err;
       cur = o.Ac;
       ++done;
-      t_compose += now_ms() - tc;
     }
-    if (done == 0) {  // level l does not coarsen: it is the coarsest
-      delete prev_owner;
-      break;
-    }
+    if (done == 0) break;  // level l does not coarsen: it is the coarsest
     double tc = now_ms();
     Level &F = h->lv[l];
     F.sweeps = done;
@@ -1236,41 +1511,31 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     AMG_TRY(dalloc(h, &F.p64, (size_t)n));
     AMG_TRY(dalloc(h, &F.mptr, (size_t)cur.n + 1));
     AMG_TRY(dalloc(h, &F.mem, (size_t)n));
-    AMG_HIP(hipMemcpyAsync(F.agg, agg_c, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-    AMG_HIP(hipMemcpyAsync(F.p64, p_c, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
+    k_compose<<<grid(n), kBlock, 0, s>>>(n, done, maps, F.agg, F.p64);
     AMG_HIP(hipMemcpyAsync(F.mptr, mptr, sizeof(int32_t) * (cur.n + 1), hipMemcpyDeviceToDevice,
                            s));
     AMG_HIP(hipMemcpyAsync(F.mem, mem, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
+    Level Cn;
     if (P.smooth_p) {
       // the tentative product chose the aggregates and restricted w; the
       // next level is the Galerkin product with the smoothed prolongator
+      int32_t herr = 0;
+      AMG_TRY(read_i32(err_ctl, &herr, s));
+      if (herr) return AMG_ERR_ARG;
       const double tr = now_ms();
-      int32_t *crp, *cci;
-      double *cval;
-      int64_t cnnz = 0;
-      const int32_t nc = cur.n;
-      AMG_TRY(smooth_level(h, F, nc, agg_c, p_c, &crp, &cci, &cval, &cnnz));
-      h->lv.emplace_back();
-      Level &Cn = h->lv[l + 1];
-      Cn.n = nc;
-      Cn.nnz = cnnz;
-      Cn.rp = crp;
-      Cn.ci = cci;
-      Cn.val = cval;
-      AMG_TRY(dalloc(h, &Cn.w, (size_t)nc));
-      AMG_HIP(hipMemcpyAsync(Cn.w, cur.w, sizeof(double) * nc, hipMemcpyDeviceToDevice, s));
+      Cn.n = cur.n;
+      AMG_TRY(smooth_level(h, F, cur.n, F.agg, F.p64, &Cn.rp, &Cn.ci, &Cn.val, &Cn.nnz));
+      AMG_TRY(dalloc(h, &Cn.w, (size_t)cur.n));
+      AMG_HIP(hipMemcpyAsync(Cn.w, cur.w, sizeof(double) * cur.n, hipMemcpyDeviceToDevice, s));
       tc += now_ms() - tr;  // counted as Galerkin time, not composition
       t_rap += now_ms() - tr;
     } else {
-      h->lv.emplace_back();
-      AMG_TRY(adopt_level(h, cur, h->lv[l + 1]));
+      AMG_TRY(adopt_level(h, tmp, cur, err_ctl, Cn));
     }
-    AMG_HIP(hipStreamSynchronize(s));
-    delete prev_owner;
+    h->lv.push_back(Cn);
     t_compose += now_ms() - tc;
   }
   T[1] = t_match;
-  T[2] = t_number;
   T[3] = t_rap;
   T[4] = t_compose;
 

@@ -2555,7 +2555,6 @@ amg_status build_solve_formats(amg_hierarchy *h) {
   AMG_TRY(dalloc(h, &h->zero_flag, 4));
   AMG_HIP(hipMemsetAsync(h->zero_flag, 0, sizeof(int32_t) * 4, s));
   AMG_HIP(hipMemsetAsync(h->scal, 0, sizeof(PcgScal), s));
-  if (!h->scal_host) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), sizeof(PcgScal)));
   return AMG_OK;
 }
 
