@@ -159,7 +159,7 @@ typedef struct {
                             the V-cycle restricts with Pbar^T and prolongates with Pbar.
                             V-cycle only. The setup's sort buffers come from a workspace
                             per device that is kept, and reused, until the process ends
-                            (about twice the largest setup's temporaries: ~30 GB for
+                            (about twice the largest setup's temporaries: ~25 GB for
                             4.1 M unknowns); smoothed setups on one device take turns.
                             0 */
 } amg_params;

@@ -1524,7 +1524,12 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       if (herr) return AMG_ERR_ARG;
       const double tr = now_ms();
       Cn.n = cur.n;
-      AMG_TRY(smooth_level(h, F, cur.n, F.agg, F.p64, &Cn.rp, &Cn.ci, &Cn.val, &Cn.nnz));
+      const amg_status st =
+          smooth_level(h, F, cur.n, F.agg, F.p64, &Cn.rp, &Cn.ci, &Cn.val, &Cn.nnz);
+      // a row over every limit: too wide a coarsest level if it was to be the last
+      if (st == AMG_ERR_ARG && l + 1 == P.max_levels - 1 && cur.n > AMG_MAX_DENSE)
+        return AMG_ERR_STALL;
+      AMG_TRY(st);
       AMG_TRY(dalloc(h, &Cn.w, (size_t)cur.n));
       AMG_HIP(hipMemcpyAsync(Cn.w, cur.w, sizeof(double) * cur.n, hipMemcpyDeviceToDevice, s));
       tc += now_ms() - tr;  // counted as Galerkin time, not composition

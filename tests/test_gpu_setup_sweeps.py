@@ -101,3 +101,24 @@ def test_row_too_long_is_refused():
     A = inputs.random_spd_graph(3000, 4.0, seed=1, hub_degree=2500)
     st, h = setup_status(A)
     assert st == amg.Status.ERR_ARG and h is None
+
+
+@pytest.mark.parametrize("n,degree,hub,sweeps", [
+    (900, 3.0, 0, 3), (3000, 6.0, 250, 3), (800, 60.0, 0, 3), (2000, 12.0, 0, 2),
+    (12000, 70.0, 0, 8)])  # the last: columns of Pbar longer than a block sorts in LDS
+def test_smoothed_products(n, degree, hub, sweeps):
+    from paper_2006_16147_amd import inputs
+
+    A = inputs.random_spd_graph(n, degree, seed=n, hub_degree=hub)
+    h = setup(A, smooth_p=1, max_coarse=60, sweeps=sweeps)
+    ho = oracle.Hierarchy(A, smooth=True, max_coarse=60, sweeps=sweeps)
+    assert ho.ok
+    assert_same_hierarchy(h, ho)
+    for l in range(ho.num_levels - 1):
+        (rp, ci, val), om = h.prolongator(l)
+        rpo, cio, valo = ho.pbar(l)
+        assert om == ho.omega(l)
+        np.testing.assert_array_equal(rp, rpo)
+        np.testing.assert_array_equal(ci, cio)
+        np.testing.assert_array_equal(val.view(np.uint64), valo.view(np.uint64))
+    h.close()
