@@ -72,13 +72,57 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
   return off + x - v;
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_local(const int32_t *in, int32_t *out,
-                                                           int32_t *bsum, int32_t n) {
+// Control block of a pairwise sweep (device), and what the host reads of it:
+// the kernel that knows a total writes it, with the block's words, to pinned
+// host memory, which saves a copy of its own.
+constexpr int kCtl = 16;
+enum : int32_t {
+  kCtlErr = 0,       // kErr*
+  kCtlRounds = 1,    // largest matching round
+  kCtlPrefLong = 2,  // rows listed for k_pref_long
+  kCtlRapLong = 3,   // rows listed for k_rap_long
+  kCtlEntries = 4,   // entries of the sweep's matrix
+  kCtlLongest = 5,   // its longest row
+  kCtlFlags = 6      // kMatchFlags per queued launch of k_match
+};
+constexpr int kMatchFlags = 2;  // kLeft, kMoved
+constexpr int kMatchQueue = 4;  // launches of k_match between host checks, at most
+static_assert(kCtlFlags + kMatchQueue * kMatchFlags <= kCtl, "control block");
+struct Report {
+  const int32_t *from = nullptr;  // kCtl words
+  int32_t *to = nullptr;          // kCtl + 1 words, the total last; null: no report
+};
+
+__device__ __forceinline__ void report(const Report &R, int32_t total) {
+  if (!R.to) return;
+  for (int k = 0; k < kCtl; ++k)
+    R.to[k] = __hip_atomic_load(&R.from[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  R.to[kCtl] = total;
+}
+
+// the end of a block's part of a scan (one thread): its sum; a scan of one
+// block is complete with it (end: where the total goes, may be null)
+__device__ __forceinline__ void scan_block_end(int32_t total, int32_t *bsum, int32_t *end,
+                                               const Report &R) {
+  if (gridDim.x > 1) {
+    bsum[blockIdx.x] = total;
+    return;
+  }
+  bsum[0] = 0;
+  bsum[1] = total;
+  if (end) *end = total;
+  report(R, total);
+}
+
+// scan of in[i], or of the lengths e[i] - in[i] of rows [in[i], e[i])
+__global__ void __launch_bounds__(kScanBlock) k_scan_local(const int32_t *in, const int32_t *e,
+                                                           int32_t *out, int32_t *bsum, int32_t n,
+                                                           Report R) {
   const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
   int32_t v[kScanPer];
   int32_t s = 0;
   for (int k = 0; k < kScanPer; ++k) {
-    v[k] = base + k < n ? in[base + k] : 0;
+    v[k] = base + k < n ? (e ? e[base + k] - in[base + k] : in[base + k]) : 0;
     s += v[k];
   }
   int32_t total;
@@ -87,16 +131,11 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_local(const int32_t *in, in
     if (base + k < n) out[base + k] = off;
     off += v[k];
   }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
+  if (threadIdx.x == 0) scan_block_end(total, bsum, out + n, R);
 }
 
-// (with `from`: the total and kCtl words from there also go to `to`, pinned
-// host memory that the caller reads after waiting for the stream, which saves
-// a copy of its own)
-constexpr int kCtl = 16;
-__global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t nb,
-                                                          const int32_t *from = nullptr,
-                                                          int32_t *to = nullptr) {
+// block sums of a scan of more than one block
+__global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t nb, Report R) {
   int32_t carry = 0;
   for (int32_t c0 = 0; c0 < nb; c0 += kScanBlock * kScanPer) {
     const int32_t base = c0 + threadIdx.x * kScanPer;
@@ -115,10 +154,9 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_sums(int32_t *bsum, int32_t
     carry += total;
     __syncthreads();
   }
-  if (threadIdx.x == 0) bsum[nb] = carry;
-  if (to) {
-    if (threadIdx.x < kCtl) to[threadIdx.x] = from[threadIdx.x];
-    if (threadIdx.x == 0) to[kCtl] = carry;
+  if (threadIdx.x == 0) {
+    bsum[nb] = carry;
+    report(R, carry);
   }
 }
 
@@ -138,11 +176,6 @@ __global__ void k_fill(T *a, T v, int64_t n) {
   if (i < n) a[i] = v;
 }
 
-__global__ void k_iota(int32_t *a, int32_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= n) a[i] = (int32_t)i;
-}
-
 // ---------------------------------------------------------------------------
 // input validation: structure, positive diagonal, bitwise symmetry
 // ---------------------------------------------------------------------------
@@ -158,41 +191,48 @@ __device__ __forceinline__ int64_t find_col(const int32_t *ci, int64_t b, int64_
   return -1;
 }
 
+// eight lanes per row, each its own entries: an entry's search in the other
+// row is a chain of loads (a thread per row: 0.50 ms at 160^3)
 __global__ void k_validate(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci,
                            const double *val, int32_t *err) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (i == 0 && rp[0] != 0) atomicOr(err, kErrArg);
-  if (i == n - 1 && (int64_t)rp[n] != nnz) atomicOr(err, kErrArg);
-  const int64_t b = rp[i], e = rp[i + 1];
-  if (b < 0 || e < b || e > nnz) {
-    atomicOr(err, kErrArg);
-    return;
-  }
-  bool diag = false;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t i = (int32_t)(t / 8), lane = (int32_t)(t % 8);
+  if (t / 8 >= n) return;
   int32_t flags = 0;
-  for (int64_t k = b; k < e; ++k) {
-    const int32_t j = ci[k];
-    const double a = val[k];
-    if (j < 0 || j >= n || (k > b && j <= ci[k - 1]) || !isfinite(a)) {
-      flags |= kErrArg;
-      break;
+  if (i == 0 && rp[0] != 0) flags |= kErrArg;
+  if (i == n - 1 && (int64_t)rp[n] != nnz) flags |= kErrArg;
+  const int64_t b = rp[i], e = rp[i + 1];
+  int32_t diag = 0;
+  if (b < 0 || e < b || e > nnz) {
+    flags |= kErrArg;
+  } else {
+    for (int64_t k = b + lane; k < e; k += 8) {
+      const int32_t j = ci[k];
+      const double a = val[k];
+      if (j < 0 || j >= n || (k > b && j <= ci[k - 1]) || !isfinite(a)) {
+        flags |= kErrArg;
+        break;
+      }
+      if (j == i) {
+        diag = 1;
+        if (!(a > 0.0)) flags |= kErrSpd;
+        continue;
+      }
+      const int64_t bj = rp[j], ej = rp[j + 1];
+      if (bj < 0 || ej < bj || ej > nnz) {
+        flags |= kErrArg;
+        break;
+      }
+      const int64_t at = find_col(ci, bj, ej, i);
+      if (at < 0 || __double_as_longlong(val[at]) != __double_as_longlong(a)) flags |= kErrSym;
     }
-    if (j == i) {
-      diag = true;
-      if (!(a > 0.0)) flags |= kErrSpd;
-      continue;
-    }
-    const int64_t bj = rp[j], ej = rp[j + 1];
-    if (bj < 0 || ej < bj || ej > nnz) {
-      flags |= kErrArg;
-      break;
-    }
-    const int64_t t = find_col(ci, bj, ej, i);
-    if (t < 0 || __double_as_longlong(val[t]) != __double_as_longlong(a)) flags |= kErrSym;
+  }
+  for (int o = 4; o > 0; o >>= 1) {
+    diag |= __shfl_xor(diag, o, 8);
+    flags |= __shfl_xor(flags, o, 8);
   }
   if (!diag) flags |= kErrSpd;
-  if (flags) atomicOr(err, flags);
+  if (flags && lane == 0) atomicOr(err, flags);
 }
 
 __global__ void k_check_w(int32_t n, const double *w, int32_t *err) {
@@ -431,7 +471,7 @@ __global__ void __launch_bounds__(kBlock) k_pref_long(
 constexpr int kMatchThreads = 512;  // a vertex per thread
 constexpr int kMatchAhead = 8;      // list entries held
 constexpr int kMatchSpin = 1024;
-enum : int32_t { kLeft = 0, kMoved = 1, kMatchFlags = 2 };
+enum : int32_t { kLeft = 0, kMoved = 1 };
 
 __global__ void __launch_bounds__(kMatchThreads, 8) k_match(int32_t n,
                                                             const int32_t *__restrict__ rb,
@@ -536,18 +576,17 @@ __global__ void __launch_bounds__(kMatchThreads, 8) k_match(int32_t n,
 // ---------------------------------------------------------------------------
 
 // mate of every vertex (-1: singleton) from its state; block scan of the
-// leaders (the smaller end of a pair, a singleton itself); the largest round
-// and the matrix's entries
+// leaders (the smaller end of a pair, a singleton itself); the largest round,
+// the matrix's entries and its longest row
 __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint64_t *st,
                                                           const int32_t *rb, const int32_t *re,
                                                           int32_t *mate, int32_t *id,
-                                                          int32_t *bsum, int32_t *rounds,
-                                                          int32_t *entries) {
-  __shared__ int32_t most, sum;
-  if (threadIdx.x == 0) most = sum = 0;
+                                                          int32_t *bsum, int32_t *ctl, Report R) {
+  __shared__ int32_t most, sum, wide;
+  if (threadIdx.x == 0) most = sum = wide = 0;
   const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
   int32_t lead[kScanPer];
-  int32_t s = 0, r = 0, c = 0;
+  int32_t s = 0, r = 0, c = 0, l = 0;
   for (int k = 0; k < kScanPer; ++k) {
     lead[k] = 0;
     if (base + k >= n) continue;
@@ -556,7 +595,9 @@ __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint6
     const int32_t x = state_of(w), m = x <= kMatched ? kMatched - x : -1;
     if (x < 0) r = max(r, round_of(w));
     mate[v] = m;
-    c += re[v] - rb[v];
+    const int32_t len = re[v] - rb[v];
+    c += len;
+    l = max(l, len);
     lead[k] = m < 0 || v < m ? 1 : 0;
     s += lead[k];
   }
@@ -566,13 +607,23 @@ __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint6
     if (base + k < n) id[base + k] = off;
     off += lead[k];
   }
-  if (r > 0) atomicMax(&most, r);
-  atomicAdd(&sum, c);
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    r = max(r, __shfl_xor(r, o, kWave));
+    l = max(l, __shfl_xor(l, o, kWave));
+    c += __shfl_xor(c, o, kWave);
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    atomicMax(&most, r);
+    atomicMax(&wide, l);
+    atomicAdd(&sum, c);
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    bsum[blockIdx.x] = total;
-    if (most > 0) atomicMax(rounds, most);
-    atomicAdd(entries, sum);
+    if (most > 0) atomicMax(ctl + kCtlRounds, most);
+    atomicMax(ctl + kCtlLongest, wide);
+    atomicAdd(ctl + kCtlEntries, sum);
+    __threadfence();
+    scan_block_end(total, bsum, nullptr, R);
   }
 }
 
@@ -627,7 +678,7 @@ __global__ void __launch_bounds__(kScanBlock) k_terms_scan(int32_t nc, const int
     if (base + k < nc) off[base + k] = o;
     o += len[k];
   }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
+  if (threadIdx.x == 0) scan_block_end(total, bsum, nullptr, Report{});
 }
 
 // LDS written by lanes of this wave is read by its other lanes
@@ -644,6 +695,8 @@ struct Coarsened {
   const int32_t *off, *bsum;         // where row I's room starts: off[I] + its block's bsum
   int32_t *b, *e, *ci;               // the coarse rows
   double *val, *wc, *dg;             // their values, restricted w, diagonal
+  const int32_t *size;               // finest members of the fine rows (null: one each)
+  int32_t *csize;                    // and of the coarse ones
 };
 
 __device__ __forceinline__ void term_of(const RowsOf &A, const Coarsened &C, int32_t f, int32_t k,
@@ -680,6 +733,7 @@ __global__ void __launch_bounds__(kBlock) k_rap(int32_t nc, RowsOf A, Coarsened 
     double s = C.p[i0] * C.w[i0];
     if (i1 >= 0) s = s + C.p[i1] * C.w[i1];
     C.wc[I] = s;
+    C.csize[I] = C.size ? C.size[i0] + (i1 >= 0 ? C.size[i1] : 0) : (i1 >= 0 ? 2 : 1);
   }
   if (len > kCap) {
     if (lane == 0) {
@@ -823,20 +877,16 @@ __global__ void __launch_bounds__(kBlock) k_rap_long(RowsOf A, Coarsened C, cons
   }
 }
 
-// lengths of a matrix's rows
-__global__ void k_row_len(int32_t n, const int32_t *rb, const int32_t *re, int32_t *len) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) len[i] = re[i] - rb[i];
-}
-
-// rows packed into a CSR, eight lanes per row
-__global__ void k_pack(int32_t n, RowsOf A, const int32_t *__restrict__ rp,
-                       int32_t *__restrict__ ci, double *__restrict__ val) {
+// rows packed into a CSR, eight lanes per row; and w
+__global__ void k_pack(int32_t n, RowsOf A, const double *__restrict__ w,
+                       const int32_t *__restrict__ rp, int32_t *__restrict__ ci,
+                       double *__restrict__ val, double *__restrict__ wo) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t i = (int32_t)(t / 8);
+  const int32_t i = (int32_t)(t / 8), lane = (int32_t)(t % 8);
   if (t / 8 >= n) return;
+  if (lane == 0) wo[i] = w[i];
   const int32_t b = A.b[i], len = A.e[i] - b, d = rp[i];
-  for (int32_t k = (int32_t)(t % 8); k < len; k += 8) {
+  for (int32_t k = lane; k < len; k += 8) {
     ci[d + k] = A.ci[b + k];
     val[d + k] = A.val[b + k];
   }
@@ -849,8 +899,9 @@ __global__ void k_pack(int32_t n, RowsOf A, const int32_t *__restrict__ rp,
 // P_l(i) = ((p_1(i) p_2(agg_1(i))) p_3(...)), agg_l = ... o agg_2 o agg_1
 constexpr int kMaxSweeps = 8;  // amg_params.sweeps
 struct SweepMaps {
-  const int32_t *agg[kMaxSweeps];
+  const int32_t *agg[kMaxSweeps];  // fine -> coarse
   const double *p[kMaxSweeps];
+  const int32_t *lead[kMaxSweeps], *mate[kMaxSweeps];  // coarse -> members
 };
 __global__ void k_compose(int32_t n, int32_t sweeps, SweepMaps M, int32_t *agg, double *p) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -865,28 +916,25 @@ __global__ void k_compose(int32_t n, int32_t sweeps, SweepMaps M, int32_t *agg, 
   p[i] = v;
 }
 
-__global__ void k_member_size(int32_t nc, const int32_t *lead, const int32_t *mate,
-                              const int32_t *mptr, int32_t *size) {
+// The finest members of aggregate I, ascending, at mem[mptr[I]]: the leaves of
+// its tree of pairs (at most 2^sweeps), put in order as they come. The first
+// of a pair being its smallest member, most come in order.
+__global__ void k_members(int32_t nc, int32_t sweeps, SweepMaps M, const int32_t *mptr,
+                          int32_t *mem) {
   const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
   if (I >= nc) return;
-  const int32_t a = lead[I], b = mate[a];
-  int32_t s = mptr[a + 1] - mptr[a];
-  if (b >= 0) s += mptr[b + 1] - mptr[b];
-  size[I] = s;
-}
-
-__global__ void k_member_merge(int32_t nc, const int32_t *lead, const int32_t *mate,
-                               const int32_t *mptr, const int32_t *mem, const int32_t *mptr_n,
-                               int32_t *mem_n) {
-  const int32_t I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  const int32_t a = lead[I], b = mate[a];
-  int32_t pa = mptr[a], ea = mptr[a + 1];
-  int32_t pb = b >= 0 ? mptr[b] : 0, eb = b >= 0 ? mptr[b + 1] : 0;
-  int32_t o = mptr_n[I];
-  while (pa < ea || pb < eb) {
-    if (pb >= eb || (pa < ea && mem[pa] < mem[pb])) mem_n[o++] = mem[pa++];
-    else mem_n[o++] = mem[pb++];
+  const int32_t o = mptr[I];
+  int32_t m = 0;
+  for (int32_t t = 0; t < 1 << sweeps; ++t) {
+    int32_t v = I;
+    for (int32_t k = sweeps - 1; k >= 0 && v >= 0; --k) {
+      v = M.lead[k][v];
+      if ((t >> k) & 1) v = M.mate[k][v];
+    }
+    if (v < 0) continue;
+    int32_t q = m++;
+    for (; q > 0 && mem[o + q - 1] > v; --q) mem[o + q] = mem[o + q - 1];
+    mem[o + q] = v;
   }
 }
 
@@ -894,20 +942,35 @@ __global__ void k_member_merge(int32_t nc, const int32_t *lead, const int32_t *m
 // l1-Jacobi diagonal, eq. (l1weights) with blocks of one row
 // ---------------------------------------------------------------------------
 
-__global__ void k_l1_diag(int32_t n, const int32_t *rp, const int32_t *ci, const double *val,
-                          double *m, double *minv) {
+// (a thread per row, the sum's order being fixed; eight loads at a time)
+__global__ void k_l1_diag(int32_t n, const int32_t *__restrict__ rp,
+                          const int32_t *__restrict__ ci, const double *__restrict__ val,
+                          double *__restrict__ m, double *__restrict__ minv) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double aii = 0.0, s = 0.0;
   bool first = true;
-  for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-    if (ci[k] == i) {
-      aii = val[k];
-    } else if (first) {
-      s = fabs(val[k]);
-      first = false;
-    } else {
-      s = s + fabs(val[k]);
+  const int32_t b = rp[i], e = rp[i + 1];
+  for (int32_t k0 = b; k0 < e; k0 += 8) {
+    double a[8];
+    int32_t c[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int32_t k = k0 + u < e ? k0 + u : e - 1;
+      a[u] = val[k];
+      c[u] = ci[k];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (k0 + u >= e) continue;
+      if (c[u] == i) {
+        aii = a[u];
+      } else if (first) {
+        s = fabs(a[u]);
+        first = false;
+      } else {
+        s = s + fabs(a[u]);
+      }
     }
   }
   const double mi = aii + s;
@@ -959,14 +1022,19 @@ __global__ void __launch_bounds__(1024) k_cholesky(int32_t n, double *D, int32_t
   }
 }
 
-// k_cholesky on the packed lower triangle held in LDS (n (n + 1) / 2 doubles,
-// up to 64 KB: n <= 127): the same steps on the same numbers, with every
-// access of the n steps in LDS instead of L2.
-constexpr int kCholLdsMax = 127;
-static_assert(kCholLdsMax * (kCholLdsMax + 1) / 2 * sizeof(double) <= 65536, "LDS triangle");
+// k_cholesky on the packed lower triangle held in LDS (n (n + 1) / 2 doubles
+// and the factor's diagonal, up to 159.4 KB: n <= 200, the default max_coarse):
+// the same steps on the same numbers, with every access of the n steps in LDS
+// instead of L2. The pivot's square root is taken by every thread that divides
+// by it, so a step has two barriers. What bounds it is the chain of n steps of
+// a square root, a division and two LDS trips (1.1 us each): 137 us at n = 125;
+// n = 141, through L2 before, 435 -> 168 us.
+constexpr int kCholLdsMax = 200;
+static_assert((kCholLdsMax * (kCholLdsMax + 1) / 2 + kCholLdsMax) * sizeof(double) <= 163840 - 64,
+              "LDS triangle");
 __global__ void __launch_bounds__(1024) k_cholesky_lds(int32_t n, double *D, int32_t *err) {
   extern __shared__ double tri[];  // row i of the lower triangle at i (i + 1) / 2
-  __shared__ int32_t bad;
+  double *const piv = tri + n * (n + 1) / 2;
   auto at = [&](int32_t i, int32_t j) -> double & { return tri[i * (i + 1) / 2 + j]; };
   for (int32_t e = threadIdx.x; e < n * (n + 1) / 2; e += blockDim.x) {
     int32_t i = (int32_t)((sqrt(8.0 * e + 1.0) - 1.0) / 2.0);
@@ -974,17 +1042,15 @@ __global__ void __launch_bounds__(1024) k_cholesky_lds(int32_t n, double *D, int
     while ((i + 1) * (i + 2) / 2 <= e) ++i;
     tri[e] = D[(int64_t)i * n + (e - i * (i + 1) / 2)];
   }
-  if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   for (int32_t k = 0; k < n; ++k) {
-    if (threadIdx.x == 0) {
-      const double d = at(k, k);
-      if (!(d > 0.0)) bad = 1;
-      else at(k, k) = sqrt(d);
+    const double d2 = at(k, k);
+    if (!(d2 > 0.0)) {  // the same for every thread
+      if (threadIdx.x == 0) atomicOr(err, kErrSpd);
+      return;
     }
-    __syncthreads();
-    if (bad) break;
-    const double d = at(k, k);
+    const double d = sqrt(d2);
+    if (threadIdx.x == 0) piv[k] = d;
     for (int32_t i = k + 1 + threadIdx.x; i < n; i += blockDim.x) at(i, k) /= d;
     __syncthreads();
     for (int32_t i = k + 1 + (int32_t)threadIdx.x / 32; i < n; i += (int32_t)blockDim.x / 32)
@@ -992,13 +1058,9 @@ __global__ void __launch_bounds__(1024) k_cholesky_lds(int32_t n, double *D, int
         at(i, j) -= at(i, k) * at(j, k);
     __syncthreads();
   }
-  if (bad) {
-    if (threadIdx.x == 0) atomicOr(err, kErrSpd);
-    return;
-  }
   for (int32_t e = threadIdx.x; e < n * n; e += blockDim.x) {
     const int32_t i = e / n, j = e % n;
-    D[e] = j > i ? 0.0 : at(i, j);
+    D[e] = j > i ? 0.0 : (j == i ? piv[i] : at(i, j));
   }
 }
 
@@ -1069,12 +1131,14 @@ inline int32_t grid(int64_t n) { return ceil_div(n > 0 ? n : 1, kBlock); }
 // block count of the exclusive scan of n values (its block sums take nb + 1)
 int32_t scan_blocks(int32_t n) { return ceil_div(n > 0 ? n : 1, kScanBlock * kScanPer); }
 
-// exclusive scan with the caller's block-sum scratch (scan_blocks(n) + 1 ints)
-void scan_exclusive_i32_with(const int32_t *in, int32_t *out, int32_t n, int32_t *bsum,
-                             hipStream_t s) {
+// exclusive scan with the caller's block-sum scratch (scan_blocks(n) + 1
+// ints): of in[i], or with `e` of e[i] - in[i]; one kernel for one block
+void scan_exclusive_i32_with(const int32_t *in, const int32_t *e, int32_t *out, int32_t n,
+                             int32_t *bsum, hipStream_t s, const Report &R = Report{}) {
   const int32_t nb = scan_blocks(n);
-  k_scan_local<<<nb, kScanBlock, 0, s>>>(in, out, bsum, n);
-  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, nb);
+  k_scan_local<<<nb, kScanBlock, 0, s>>>(in, e, out, bsum, n, R);
+  if (nb == 1) return;
+  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, nb, R);
   k_scan_add<<<grid((int64_t)n + 1), kBlock, 0, s>>>(out, bsum, n, nb);
 }
 
@@ -1152,25 +1216,21 @@ struct Tmp {
     *p = reinterpret_cast<T *>(q);
     return AMG_OK;
   }
-  void drop(void *p) {
-    for (auto &q : ptrs)
-      if (q == p) {
-        stream_free(device, s, q);
-        q = nullptr;
-      }
-  }
   // exclusive scan of n values, its block sums in this object's memory
   amg_status scan(const int32_t *in, int32_t *out, int32_t n) {
     int32_t *bsum = nullptr;
     AMG_TRY(get(&bsum, (size_t)scan_blocks(n) + 1));
-    scan_exclusive_i32_with(in, out, n, bsum, s);
+    scan_exclusive_i32_with(in, nullptr, out, n, bsum, s);
     return AMG_OK;
   }
 };
 
-amg_status read_i32(const int32_t *dev, int32_t *host, hipStream_t s) {
-  AMG_HIP(hipMemcpyAsync(host, dev, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  AMG_HIP(hipStreamSynchronize(s));
+// (by way of the pinned block)
+amg_status read_i32(const amg_hierarchy *h, const int32_t *dev, int32_t *host) {
+  int32_t *const pinned = reinterpret_cast<int32_t *>(h->scal_host);
+  AMG_HIP(hipMemcpyAsync(pinned, dev, sizeof(int32_t), hipMemcpyDeviceToHost, h->stream));
+  AMG_HIP(hipStreamSynchronize(h->stream));
+  *host = *pinned;
   return AMG_OK;
 }
 
@@ -1186,9 +1246,11 @@ struct Mat {
   int32_t n = 0;
   int64_t most = 0;   // at least its number of entries
   double mean = 0.0;  // about the mean row's entries
+  int32_t longest = 0;  // its longest row at most (0: not known)
   RowsOf rows{};
   const double *w = nullptr;
   const double *dg = nullptr;  // its diagonal
+  const int32_t *size = nullptr;  // members of each row on the level (null: one each)
 };
 
 // One pairwise sweep on A (Section 3.2). nc == n means nothing was matched;
@@ -1204,29 +1266,23 @@ struct SweepOut {
   const int32_t *err = nullptr;  // control block: kErr* of the product
 };
 
-// words of a sweep's control block (zeroed at its start, read back with nc)
-enum : int32_t {
-  kCtlErr = 0,       // kErr*
-  kCtlRounds = 1,    // largest matching round
-  kCtlPrefLong = 2,  // rows listed for k_pref_long
-  kCtlRapLong = 3,   // rows listed for k_rap_long
-  kCtlEntries = 4,   // entries of the sweep's matrix
-  kCtlFlags = 5      // kMatchFlags per queued launch of k_match
-};
-constexpr int kMatchQueue = 4;  // launches of k_match between host checks, at most
-static_assert(kCtlFlags + kMatchQueue * kMatchFlags <= kCtl, "control block");
-
 template <int G>
 void launch_pref(const Mat &A, int32_t *pref, uint64_t *st, int32_t *ovf, int32_t *ctl,
                  hipStream_t s) {
   k_pref<G><<<grid((int64_t)A.n * G), kBlock, 0, s>>>(A.n, A.rows, A.w, A.dg, pref, st, ovf,
                                                       ctl + kCtlPrefLong);
+  if (A.longest == 0 || A.longest > 2 * G)
+    k_pref_long<<<A.n < 2048 ? A.n : 2048, kBlock, 0, s>>>(A.rows, A.w, A.dg, pref, st, ovf,
+                                                           ctl + kCtlPrefLong, ctl + kCtlErr);
 }
 
 template <int G>
-void launch_rap(int32_t nc, const RowsOf &A, const Coarsened &C, int32_t *ovf, int32_t *ctl,
-                hipStream_t s) {
+void launch_rap(int32_t nc, const RowsOf &A, const Coarsened &C, int32_t longest, int32_t *ovf,
+                int32_t *ctl, hipStream_t s) {
   k_rap<G><<<grid((int64_t)nc * G), kBlock, 0, s>>>(nc, A, C, ovf, ctl + kCtlRapLong);
+  if (longest > 2 * G)
+    k_rap_long<<<nc < 1024 ? nc : 1024, kBlock, 0, s>>>(A, C, ovf, ctl + kCtlRapLong,
+                                                        ctl + kCtlErr);
 }
 
 // the host's copy of the control block and of the total scanned last
@@ -1236,46 +1292,41 @@ amg_status read_ctl(const int32_t *pinned, int32_t *host, hipStream_t s) {
   return AMG_OK;
 }
 
-amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
+// (ctl: a zeroed control block)
+amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl, SweepOut &o,
                           double *t_match, double *t_rap) {
   hipStream_t s = h->stream;
   const int32_t n = A.n;
-  int32_t *const pinned = reinterpret_cast<int32_t *>(h->scal_host);
+  const Report R{ctl, reinterpret_cast<int32_t *>(h->scal_host)};
   const double t0 = now_ms();
-  int32_t *pref, *ctl, *id, *bsum, *ovf;
+  int32_t *pref, *id, *bsum, *ovf;
   uint64_t *st;
   AMG_TRY(tmp.get(&pref, A.most));
   AMG_TRY(tmp.get(&st, n));
-  AMG_TRY(tmp.get(&ctl, kCtl));
   AMG_TRY(tmp.get(&id, n));
   AMG_TRY(tmp.get(&bsum, (size_t)scan_blocks(n) + 1));
   AMG_TRY(tmp.get(&ovf, n));
   AMG_TRY(tmp.get(&o.mate, n));
-  const int32_t nmatch = ceil_div(n, kMatchThreads);
-  k_fill<int32_t><<<1, kCtl, 0, s>>>(ctl, 0, kCtl);
   // lanes per row: the mean row (of a sweep's matrix: of the one before it)
   // fills half of a group's places, so that most rows still fit
-  const double mean = A.mean;
-  if (mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, s);
-  else if (mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, s);
-  else if (mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, s);
+  if (A.mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, s);
+  else if (A.mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, s);
+  else if (A.mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, s);
   else launch_pref<64>(A, pref, st, ovf, ctl, s);
-  k_pref_long<<<n < 2048 ? n : 2048, kBlock, 0, s>>>(A.rows, A.w, A.dg, pref, st, ovf,
-                                                     ctl + kCtlPrefLong, ctl + kCtlErr);
   // matching, and the numbering of what it gives; where it takes more than
   // the launches queued, both again from there on
   int32_t hc[kCtl + 1];
-  for (int queue = 2;; queue = kMatchQueue) {
+  for (int queue = 1;; queue = kMatchQueue) {
     for (int r = 0; r < queue; ++r) {
       int32_t *f = ctl + kCtlFlags + r * kMatchFlags;
-      k_match<<<nmatch, kMatchThreads, 0, s>>>(n, A.rows.b, A.rows.e, pref, st,
-                                               r > 0 ? f - kMatchFlags : nullptr, f);
+      k_match<<<ceil_div(n, kMatchThreads), kMatchThreads, 0, s>>>(
+          n, A.rows.b, A.rows.e, pref, st, r > 0 ? f - kMatchFlags : nullptr, f);
     }
     k_lead_scan<<<scan_blocks(n), kScanBlock, 0, s>>>(n, st, A.rows.b, A.rows.e, o.mate, id, bsum,
-                                                      ctl + kCtlRounds, ctl + kCtlEntries);
-    k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), ctl, pinned);
+                                                      ctl, R);
+    if (scan_blocks(n) > 1) k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), R);
     AMG_HIP(hipGetLastError());
-    AMG_TRY(read_ctl(pinned, hc, s));
+    AMG_TRY(read_ctl(R.to, hc, s));
     if (hc[kCtlErr]) return AMG_ERR_ARG;  // a row too long for the Galerkin product
     const int32_t *last = hc + kCtlFlags + (queue - 1) * kMatchFlags;
     if (!last[kLeft]) break;  // (the last launch does nothing once one before it left nothing)
@@ -1283,7 +1334,7 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
     k_fill<int32_t><<<1, kCtl - kCtlEntries, 0, s>>>(ctl + kCtlEntries, 0, kCtl - kCtlEntries);
   }
   o.rounds = hc[kCtlRounds] > 0 ? hc[kCtlRounds] - 1 : 0;
-  const int32_t nc = hc[kCtl];
+  const int32_t nc = hc[kCtl], nnz = hc[kCtlEntries];
   o.nc = nc;
   const double t1 = now_ms();
   *t_match += t1 - t0;
@@ -1300,10 +1351,11 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
   AMG_TRY(tmp.get(&bsum2, (size_t)scan_blocks(nc) + 1));
   AMG_TRY(tmp.get(&C.b, nc));
   AMG_TRY(tmp.get(&C.e, nc));
-  AMG_TRY(tmp.get(&C.ci, hc[kCtlEntries]));
-  AMG_TRY(tmp.get(&C.val, hc[kCtlEntries]));
+  AMG_TRY(tmp.get(&C.ci, nnz));
+  AMG_TRY(tmp.get(&C.val, nnz));
   AMG_TRY(tmp.get(&C.wc, nc));
   AMG_TRY(tmp.get(&C.dg, nc));
+  AMG_TRY(tmp.get(&C.csize, nc));
   C.lead = o.lead;
   C.mate = o.mate;
   C.agg = o.agg;
@@ -1311,53 +1363,50 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, SweepOut &o,
   C.w = A.w;
   C.off = off;
   C.bsum = bsum2;
+  C.size = A.size;
   k_terms_scan<<<scan_blocks(nc), kScanBlock, 0, s>>>(nc, o.lead, o.mate, A.rows.b, A.rows.e, off,
                                                       bsum2);
-  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum2, scan_blocks(nc));
+  if (scan_blocks(nc) > 1)
+    k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum2, scan_blocks(nc), Report{});
   // lanes per coarse row: room for the mean row's terms and an eighth more (the
   // 7-point stencil's 14 terms take the 16 places of eight lanes)
-  const double terms = 1.125 * hc[kCtlEntries] / nc;
-  if (terms <= 16.0) launch_rap<8>(nc, A.rows, C, ovf, ctl, s);
-  else if (terms <= 32.0) launch_rap<16>(nc, A.rows, C, ovf, ctl, s);
-  else if (terms <= 64.0) launch_rap<32>(nc, A.rows, C, ovf, ctl, s);
-  else launch_rap<64>(nc, A.rows, C, ovf, ctl, s);
-  k_rap_long<<<nc < 1024 ? nc : 1024, kBlock, 0, s>>>(A.rows, C, ovf, ctl + kCtlRapLong,
-                                                      ctl + kCtlErr);
+  const double terms = 1.125 * nnz / nc;
+  const int32_t longest = hc[kCtlLongest] > kRapLongCap ? 2 * kRapLongCap : 2 * hc[kCtlLongest];
+  if (terms <= 16.0) launch_rap<8>(nc, A.rows, C, longest, ovf, ctl, s);
+  else if (terms <= 32.0) launch_rap<16>(nc, A.rows, C, longest, ovf, ctl, s);
+  else if (terms <= 64.0) launch_rap<32>(nc, A.rows, C, longest, ovf, ctl, s);
+  else launch_rap<64>(nc, A.rows, C, longest, ovf, ctl, s);
   AMG_HIP(hipGetLastError());
   o.Ac.n = nc;
-  o.Ac.most = hc[kCtlEntries];
-  o.Ac.mean = (double)hc[kCtlEntries] / n;
+  o.Ac.most = nnz;
+  o.Ac.mean = (double)nnz / n;
+  o.Ac.longest = longest;
   o.Ac.rows = RowsOf{C.b, C.e, C.ci, C.val};
   o.Ac.w = C.wc;
   o.Ac.dg = C.dg;
+  o.Ac.size = C.csize;
   o.err = ctl + kCtlErr;
   *t_rap += now_ms() - t1;
   return AMG_OK;
 }
 
 // the last sweep's matrix, packed into level storage
-amg_status adopt_level(amg_hierarchy *h, Tmp &tmp, const Mat &M, const int32_t *err, Level &L) {
+amg_status adopt_level(amg_hierarchy *h, Tmp &tmp, const Mat &M, const int32_t *ctl, Level &L) {
   hipStream_t s = h->stream;
-  int32_t *const pinned = reinterpret_cast<int32_t *>(h->scal_host);
-  int32_t *len, *bsum;
-  AMG_TRY(tmp.get(&len, M.n));
+  const Report R{ctl, reinterpret_cast<int32_t *>(h->scal_host)};
+  int32_t *bsum;
   AMG_TRY(tmp.get(&bsum, (size_t)scan_blocks(M.n) + 1));
   L.n = M.n;
   AMG_TRY(dalloc(h, &L.rp, (size_t)M.n + 1));
-  k_row_len<<<grid(M.n), kBlock, 0, s>>>(M.n, M.rows.b, M.rows.e, len);
-  const int32_t nb = scan_blocks(M.n);
-  k_scan_local<<<nb, kScanBlock, 0, s>>>(len, L.rp, bsum, M.n);
-  k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, nb, err, pinned);
-  k_scan_add<<<grid((int64_t)M.n + 1), kBlock, 0, s>>>(L.rp, bsum, M.n, nb);
+  scan_exclusive_i32_with(M.rows.b, M.rows.e, L.rp, M.n, bsum, s, R);
   int32_t hc[kCtl + 1];
-  AMG_TRY(read_ctl(pinned, hc, s));
+  AMG_TRY(read_ctl(R.to, hc, s));
   if (hc[kCtlErr]) return AMG_ERR_ARG;  // a coarse row gathers more than kRapLongCap entries
   L.nnz = hc[kCtl];
   AMG_TRY(dalloc(h, &L.ci, (size_t)L.nnz));
   AMG_TRY(dalloc(h, &L.val, (size_t)L.nnz));
   AMG_TRY(dalloc(h, &L.w, (size_t)M.n));
-  k_pack<<<grid((int64_t)M.n * 8), kBlock, 0, s>>>(M.n, M.rows, L.rp, L.ci, L.val);
-  AMG_HIP(hipMemcpyAsync(L.w, M.w, sizeof(double) * M.n, hipMemcpyDeviceToDevice, s));
+  k_pack<<<grid((int64_t)M.n * 8), kBlock, 0, s>>>(M.n, M.rows, M.w, L.rp, L.ci, L.val, L.w);
   return AMG_OK;
 }
 
@@ -1376,7 +1425,7 @@ amg_status setup_scan(amg_hierarchy *h, const int32_t *in, int32_t *out, int32_t
   int32_t *bsum = nullptr;
   AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&bsum),
                           sizeof(int32_t) * ((size_t)scan_blocks(n) + 1)));
-  scan_exclusive_i32_with(in, out, n, bsum, h->stream);
+  scan_exclusive_i32_with(in, nullptr, out, n, bsum, h->stream);
   setup_tmp_free(h, bsum);
   return AMG_OK;
 }
@@ -1385,7 +1434,7 @@ amg_status scan_exclusive_i32(const int32_t *in, int32_t *out, int32_t n, hipStr
   const int32_t nb = scan_blocks(n);
   int32_t *bsum = nullptr;
   AMG_HIP(hipMallocAsync(reinterpret_cast<void **>(&bsum), sizeof(int32_t) * (nb + 1), s));
-  scan_exclusive_i32_with(in, out, n, bsum, s);
+  scan_exclusive_i32_with(in, nullptr, out, n, bsum, s);
   AMG_HIP(hipFreeAsync(bsum, s));
   return AMG_OK;
 }
@@ -1415,10 +1464,10 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   AMG_TRY(tmp.get(&err, 1));
   k_fill<int32_t><<<1, 1, 0, s>>>(err, 0, 1);
   if (!(P.flags & AMG_FLAG_SKIP_CHECKS))
-    k_validate<<<grid(n0), kBlock, 0, s>>>(n0, A->nnz, A->row_ptr, A->col, A->val, err);
+    k_validate<<<grid((int64_t)n0 * 8), kBlock, 0, s>>>(n0, A->nnz, A->row_ptr, A->col, A->val, err);
   if (P.w) k_check_w<<<grid(n0), kBlock, 0, s>>>(n0, P.w, err);
   int32_t herr = 0;
-  AMG_TRY(read_i32(err, &herr, s));
+  AMG_TRY(read_i32(h, err, &herr));
   AMG_TRY(map_err(herr));
   T[0] = now_ms() - t_start;
 
@@ -1458,46 +1507,57 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
         AMG_HIP(hipMemcpyAsync(L0.w, src, sizeof(double) * n0, hipMemcpyDeviceToDevice, s));
       k_fill<int32_t><<<1, 1, 0, s>>>(err, 0, 1);
       k_check_w<<<grid(n0), kBlock, 0, s>>>(n0, L0.w, err);
-      AMG_TRY(read_i32(err, &herr, s));
+      AMG_TRY(read_i32(h, err, &herr));
       AMG_TRY(map_err(herr));
     }
   }
 
   double t_match = 0, t_rap = 0, t_compose = 0;
+  // control blocks of the sweeps to come, zeroed a level's worth or more at a time
+  constexpr int kCtlBlocks = 32;
+  static_assert(kCtlBlocks >= kMaxSweeps, "a level's sweeps");
+  int32_t *ctls = nullptr;
+  int ctl_left = 0;
+  const double *dg = nullptr;  // the level's diagonal, where the sweep before left it
+  int32_t longest = 0;
   for (int32_t l = 0;; ++l) {
     const int32_t n = h->lv[l].n;
     if (n <= P.max_coarse || l == P.max_levels - 1) break;
     const Level &A0 = h->lv[l];
-    double *dg;
-    AMG_TRY(tmp.get(&dg, n));
+    if (ctl_left < P.sweeps) {
+      AMG_TRY(tmp.get(&ctls, kCtlBlocks * kCtl));
+      k_fill<int32_t><<<grid(kCtlBlocks * kCtl), kBlock, 0, s>>>(ctls, 0, kCtlBlocks * kCtl);
+      ctl_left = kCtlBlocks;
+    }
     const RowsOf rows{A0.rp, A0.rp + 1, A0.ci, A0.val};
-    k_diag<<<grid(n), kBlock, 0, s>>>(n, rows, dg);
-    Mat cur{n, A0.nnz, (double)A0.nnz / n, rows, A0.w, dg};
-    int32_t *mptr, *mem;
-    AMG_TRY(tmp.get(&mptr, (size_t)n + 1));
-    AMG_TRY(tmp.get(&mem, n));
-    k_iota<<<grid((int64_t)n + 1), kBlock, 0, s>>>(mptr, n);
-    k_iota<<<grid(n), kBlock, 0, s>>>(mem, n - 1);
+    if (!dg) {
+      double *d;
+      AMG_TRY(tmp.get(&d, n));
+      k_diag<<<grid(n), kBlock, 0, s>>>(n, rows, d);
+      dg = d;
+    }
+    Mat cur;
+    cur.n = n;
+    cur.most = A0.nnz;
+    cur.mean = (double)A0.nnz / n;
+    cur.longest = longest;
+    cur.rows = rows;
+    cur.w = A0.w;
+    cur.dg = dg;
     int32_t done = 0, rounds = 0;
     SweepMaps maps{};
     const int32_t *err_ctl = nullptr;
     for (int32_t k = 0; k < P.sweeps; ++k) {
       SweepOut o;
-      AMG_TRY(pairwise_sweep(h, tmp, cur, o, &t_match, &t_rap));
+      AMG_TRY(pairwise_sweep(h, tmp, cur, ctls, o, &t_match, &t_rap));
+      ctls += kCtl;
+      --ctl_left;
       rounds += o.rounds;
       if (o.nc == cur.n) break;  // nothing matched: end this level's sweeps
       maps.agg[k] = o.agg;
       maps.p[k] = o.p;
-      int32_t *msz, *mptr_n, *mem_n;
-      AMG_TRY(tmp.get(&msz, o.nc));
-      AMG_TRY(tmp.get(&mptr_n, (size_t)o.nc + 1));
-      AMG_TRY(tmp.get(&mem_n, n));
-      k_member_size<<<grid(o.nc), kBlock, 0, s>>>(o.nc, o.lead, o.mate, mptr, msz);
-      AMG_TRY(tmp.scan(msz, mptr_n, o.nc));
-      k_member_merge<<<grid(o.nc), kBlock, 0, s>>>(o.nc, o.lead, o.mate, mptr, mem, mptr_n,
-                                                   mem_n);
-      mptr = mptr_n;
-      mem = mem_n;
+      maps.lead[k] = o.lead;
+      maps.mate[k] = o.mate;
       err_ctl = o.err;
       cur = o.Ac;
       ++done;
@@ -1512,15 +1572,14 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     AMG_TRY(dalloc(h, &F.mptr, (size_t)cur.n + 1));
     AMG_TRY(dalloc(h, &F.mem, (size_t)n));
     k_compose<<<grid(n), kBlock, 0, s>>>(n, done, maps, F.agg, F.p64);
-    AMG_HIP(hipMemcpyAsync(F.mptr, mptr, sizeof(int32_t) * (cur.n + 1), hipMemcpyDeviceToDevice,
-                           s));
-    AMG_HIP(hipMemcpyAsync(F.mem, mem, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
+    AMG_TRY(tmp.scan(cur.size, F.mptr, cur.n));
+    k_members<<<grid(cur.n), kBlock, 0, s>>>(cur.n, done, maps, F.mptr, F.mem);
     Level Cn;
     if (P.smooth_p) {
       // the tentative product chose the aggregates and restricted w; the
       // next level is the Galerkin product with the smoothed prolongator
       int32_t herr = 0;
-      AMG_TRY(read_i32(err_ctl, &herr, s));
+      AMG_TRY(read_i32(h, err_ctl, &herr));
       if (herr) return AMG_ERR_ARG;
       const double tr = now_ms();
       Cn.n = cur.n;
@@ -1534,8 +1593,12 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       AMG_HIP(hipMemcpyAsync(Cn.w, cur.w, sizeof(double) * cur.n, hipMemcpyDeviceToDevice, s));
       tc += now_ms() - tr;  // counted as Galerkin time, not composition
       t_rap += now_ms() - tr;
+      dg = nullptr;
+      longest = 0;
     } else {
       AMG_TRY(adopt_level(h, tmp, cur, err_ctl, Cn));
+      dg = cur.dg;
+      longest = cur.longest;
     }
     h->lv.push_back(Cn);
     t_compose += now_ms() - tc;
@@ -1565,11 +1628,16 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     AMG_HIP(hipMemsetAsync(D, 0, sizeof(double) * (size_t)nL * nL, s));
     k_dense_scatter<<<grid(nL), kBlock, 0, s>>>(nL, L.rp, L.ci, L.val, D);
     k_fill<int32_t><<<1, 1, 0, s>>>(err, 0, 1);
+    const size_t chol_lds = sizeof(double) * ((size_t)nL * (nL + 1) / 2 + nL);
+    if (nL <= kCholLdsMax && chol_lds > 65536)
+      AMG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_cholesky_lds),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)chol_lds));
     if (nL <= kCholLdsMax)
-      k_cholesky_lds<<<1, 1024, sizeof(double) * (size_t)nL * (nL + 1) / 2, s>>>(nL, D, err);
+      k_cholesky_lds<<<1, 1024, chol_lds, s>>>(nL, D, err);
     else
       k_cholesky<<<1, 1024, 0, s>>>(nL, D, err);
-    AMG_TRY(read_i32(err, &herr, s));
+    AMG_HIP(hipGetLastError());
+    AMG_TRY(read_i32(h, err, &herr));
     if (herr) return AMG_ERR_NOT_SPD;
     h->C.n = nL;
     AMG_TRY(dalloc(h, &h->C.Linv, (size_t)nL * nL));

@@ -673,7 +673,8 @@ __global__ void __launch_bounds__(kBlock) k_sort_rows(Work W, const int32_t *__r
     for (int32_t e = lane; e < len; e += G) {
       const int32_t c = key[grp][e];
       int32_t rank = 0;
-      for (int32_t f = 0; f < len; ++f) rank += key[grp][f] < c ? 1 : 0;
+      for (int32_t f = 0; f < len; ++f)
+        rank += key[grp][f] < c || (key[grp][f] == c && f < e) ? 1 : 0;
       dci[d + rank] = c;
       dval[d + rank] = val[b + e];
     }

@@ -271,73 +271,105 @@ __global__ void k_iota_i32(int32_t *a, int32_t n) {
   if (i < n) a[i] = i;
 }
 
-__global__ void k_gather_f64(int32_t n, const int32_t *perm, const double *src, double *dst) {
-  const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) dst[k] = src[perm[k]];
+// Entries of each 64-row slice (width = longest row, times 64), a wave per
+// slice; stat[0]: their 64-bit total (the int32 offsets of the format must not
+// overflow), stat[1]: the widest slice.
+__global__ void __launch_bounds__(1024) k_sell_width(int32_t n, int32_t ns,
+                                                     const int32_t *__restrict__ rp,
+                                                     const int32_t *__restrict__ perm,
+                                                     int32_t *__restrict__ w64,
+                                                     unsigned long long *stat) {
+  __shared__ unsigned long long total, widest;
+  if (threadIdx.x == 0) total = widest = 0;
+  __syncthreads();
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t s = (int32_t)(k / kSlice);
+  int32_t w = 0;
+  if (k < n) {
+    const int32_t i = perm[k];
+    w = rp[i + 1] - rp[i];
+  }
+  for (int o = kWave / 2; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o, kWave));
+  if (s < ns && threadIdx.x % kWave == 0) {
+    const int64_t e = (int64_t)w * kSlice;
+    w64[s] = e > INT32_MAX ? INT32_MAX : (int32_t)e;
+    atomicAdd(&total, (unsigned long long)e);
+    atomicMax(&widest, (unsigned long long)w);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    atomicAdd(&stat[0], total);
+    atomicMax(&stat[1], widest);
+  }
 }
 
-// Entries of each 64-row slice (width = longest row, times 64), and their
-// 64-bit total: the int32 offsets of the format must not overflow.
-__global__ void k_sell_width(int32_t n, int32_t ns, const int32_t *rp, const int32_t *perm,
-                             int32_t *w64, unsigned long long *total) {
-  const int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= ns) return;
-  const int32_t r0 = s * kSlice, r1 = min(n, r0 + kSlice);
-  int32_t w = 0;
-  for (int32_t k = r0; k < r1; ++k) {
-    const int32_t i = perm[k];
-    w = max(w, rp[i + 1] - rp[i]);
-  }
-  const int64_t e = (int64_t)w * kSlice;
-  w64[s] = e > INT32_MAX ? INT32_MAX : (int32_t)e;
-  atomicAdd(total, (unsigned long long)e);
-}
+// What k_sell_fill writes: the SELL arrays (null: not wanted), and by position
+// the diagonal scaling and the prolongator's FP32 copy.
+struct SellOut {
+  int32_t *col;
+  double *v64;
+  float *v32;
+  double *s64;
+  float *s32;
+  double *minv64;
+  float *minv32;
+  const double *pp64;
+  float *pp32;
+};
 
 // Row k of the permuted matrix is original row perm[k] with columns renumbered
 // by iperm and sorted (rows up to kSortCap entries); padding entries point at
-// the row itself with value 0.
+// the row itself with value 0. A block per slice, four lanes per row (and
+// gridDim.y blocks over the entries of long rows): an entry's place is its rank
+// among the row's columns, held in LDS with consecutive rows in consecutive
+// banks. (A thread per row with an insertion sort of indices in scratch, every
+// comparison two dependent loads, took 0.79 ms at 160^3, and 0.9 ms for 1019
+// rows of 428 entries.)
 constexpr int kSortCap = 64;
-__global__ void k_sell_fill(int32_t n, int32_t ns, const int32_t *rp, const int32_t *ci,
-                            const double *val, const int32_t *perm, const int32_t *iperm,
-                            const double *minv, const int32_t *sptr, int32_t *col, double *v64,
-                            float *v32, double *s64, float *s32) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= (int64_t)ns * kSlice) return;
-  const int32_t s = (int32_t)(k / kSlice), lane = (int32_t)(k % kSlice);
+__global__ void __launch_bounds__(kBlock) k_sell_fill(
+    int32_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+    const double *__restrict__ val, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ iperm, const double *__restrict__ minv,
+    const int32_t *__restrict__ sptr, SellOut O) {
+  __shared__ int32_t key[kSortCap][kSlice];
+  constexpr int kParts = kBlock / kSlice;
+  const int32_t s = blockIdx.x, row = threadIdx.x % kSlice, part = threadIdx.x / kSlice;
+  const int64_t k = (int64_t)s * kSlice + row;
   const int32_t base = sptr[s], w = (sptr[s + 1] - base) / kSlice;
   const int32_t i = k < n ? perm[k] : 0;
   const int32_t b = k < n ? rp[i] : 0, len = k < n ? rp[i + 1] - b : 0;
-  int32_t order[kSortCap];
   const bool sorted = len <= kSortCap;
-  if (sorted) {
-    for (int32_t e = 0; e < len; ++e) {
-      const int32_t c = iperm[ci[b + e]];
-      int32_t pos = e;
-      while (pos > 0 && iperm[ci[b + order[pos - 1]]] > c) {
-        order[pos] = order[pos - 1];
-        --pos;
-      }
-      order[pos] = e;
-    }
-  }
-  for (int32_t e = 0; e < w; ++e) {
-    const int64_t idx = base + (int64_t)e * kSlice + lane;
+  if (sorted)
+    for (int32_t e = part; e < len; e += kParts) key[e][row] = iperm[ci[b + e]];
+  __syncthreads();
+  for (int32_t e = part + kParts * (int32_t)blockIdx.y; e < w; e += kParts * (int32_t)gridDim.y) {
+    int32_t at = e, J = k < n ? (int32_t)k : 0;
+    double a = 0.0, m = 0.0;
     if (e < len) {
-      const int32_t src = b + (sorted ? order[e] : e);
-      const int32_t c = ci[src];
-      const double a = val[src];
-      col[idx] = iperm[c];
-      if (v64) v64[idx] = a;
-      if (v32) v32[idx] = (float)a;
-      if (s64) s64[idx] = a * minv[c];
-      if (s32) s32[idx] = (float)(a * minv[c]);
-    } else {
-      col[idx] = k < n ? (int32_t)k : 0;
-      if (v64) v64[idx] = 0.0;
-      if (v32) v32[idx] = 0.f;
-      if (s64) s64[idx] = 0.0;
-      if (s32) s32[idx] = 0.f;
+      const int32_t c = ci[b + e];
+      a = val[b + e];
+      if (O.s64 || O.s32) m = minv[c];
+      if (sorted) {
+        J = key[e][row];
+        at = 0;
+        for (int32_t f = 0; f < len; ++f)
+          at += key[f][row] < J || (key[f][row] == J && f < e) ? 1 : 0;
+      } else {
+        J = iperm[c];
+      }
     }
+    const int64_t idx = base + (int64_t)at * kSlice + row;
+    O.col[idx] = J;
+    if (O.v64) O.v64[idx] = a;
+    if (O.v32) O.v32[idx] = (float)a;
+    if (O.s64) O.s64[idx] = a * m;
+    if (O.s32) O.s32[idx] = (float)(a * m);
+  }
+  if (blockIdx.y == 0 && part == 0 && k < n && O.minv64) {
+    const double m = minv[i];
+    O.minv64[k] = m;
+    if (O.minv32) O.minv32[k] = (float)m;
+    if (O.pp32) O.pp32[k] = (float)O.pp64[k];
   }
 }
 
@@ -345,11 +377,6 @@ __global__ void k_sell_fill(int32_t n, int32_t ns, const int32_t *rp, const int3
 __global__ void k_not_fp32_exact(int64_t n, const double *a, int32_t *flag) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n && !((double)(float)a[i] == a[i])) *flag = 1;
-}
-
-__global__ void k_demote(int64_t n, const double *a, float *b) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = (float)a[i];
 }
 
 __global__ void k_permute_in(int32_t n, const int32_t *__restrict__ perm,
@@ -2199,7 +2226,6 @@ amg_status alloc_level_vectors(amg_hierarchy *h, Level &L, size_t vbytes) {
 // ---- LDS-staged gathers: tile lists (setup) ----
 
 constexpr int kHaloCap = 8192;        // padded entries of one tile sorted in LDS
-constexpr int kHaloThreads = 1024;
 constexpr int32_t kHaloMaxList = 4096;  // longest list a level may have (LDS of a block)
 
 __global__ void k_tile_starts(int32_t ntiles, int32_t step, int32_t nmax,
@@ -2213,21 +2239,25 @@ __global__ void k_tile_starts(int32_t ntiles, int32_t step, int32_t nmax,
 
 // Tile t = rows [tb[t], tb[t + 1]). Its list is the sorted distinct columns
 // of its SELL positions (W per row, W the widest slice among its rows; at
-// most kHaloCap positions, else count[t] = -1 and no list): the columns below
+// most CAP positions, else count[t] = -1 and no list): the columns below
 // the tile's own rows, then the own rows themselves (every row holds its
 // diagonal), then the columns above. Only the columns outside the own rows
 // are sorted (bitonic, in LDS) and made distinct; an own row's index in the
 // list follows from its offset. Pass 0 writes the list length to count[t];
 // pass 1 writes the list at hidx + hptr[t] and, at every position, the index
-// of its column in the list.
-__global__ void __launch_bounds__(kHaloThreads) k_halo(
+// of its column in the list. What bounds it is the barriers of the sort, so a
+// tile takes a block of no more threads than its columns need: 256 for the
+// down step's tiles of 256 rows (0.52 and 0.64 ms a pass with 1024 at 160^3).
+template <int NT, int CAP>
+__global__ void __launch_bounds__(NT) k_halo(
     int32_t pass, const int32_t *__restrict__ tb, const int32_t *__restrict__ sptr,
     const int32_t *__restrict__ col, int32_t *__restrict__ count,
     const int32_t *__restrict__ hptr, int32_t *__restrict__ hidx, uint16_t *__restrict__ lcol) {
-  __shared__ int32_t keys[kHaloCap];
-  __shared__ int32_t part[kHaloThreads];
+  __shared__ int32_t keys[CAP];
+  __shared__ int32_t part[NT];
   __shared__ int32_t wmax, nout;
-  const int32_t t = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  const int32_t t = blockIdx.x, tid = threadIdx.x;
+  constexpr int32_t nt = NT;
   const int32_t r0 = tb[t], r1 = tb[t + 1], rows = r1 - r0;
   if (tid == 0) {
     wmax = 0;
@@ -2243,7 +2273,7 @@ __global__ void __launch_bounds__(kHaloThreads) k_halo(
   __syncthreads();
   const int32_t W = wmax;
   const int64_t E = (int64_t)rows * W;
-  if (E > kHaloCap) {
+  if (E > CAP) {
     if (pass == 0 && tid == 0) count[t] = -1;
     return;
   }
@@ -2277,8 +2307,8 @@ __global__ void __launch_bounds__(kHaloThreads) k_halo(
       __syncthreads();
     }
   // distinct keys: thread tid takes positions [tid * per, tid * per + per)
-  const int32_t per = (P + nt - 1) / nt;  // at most kHaloCap / kHaloThreads = 8
-  int32_t kv[kHaloCap / kHaloThreads];
+  const int32_t per = (P + nt - 1) / nt;  // at most CAP / NT
+  int32_t kv[CAP / NT];
   uint32_t first = 0;
   int32_t mine = 0;
   for (int32_t q = 0; q < per; ++q) {
@@ -2340,44 +2370,65 @@ __global__ void __launch_bounds__(kHaloThreads) k_halo(
   }
 }
 
-// Tile lists of level L for `ntiles` tiles starting at tb (device, ntiles + 1
-// entries). Leaves H empty (the kernels then gather from memory) when a tile
-// has too many entries to sort in LDS or too long a list for a block's LDS.
-amg_status build_halo(amg_hierarchy *h, const Level &L, const int32_t *tb, int32_t ntiles,
-                      int32_t param, Halo *H) {
+// A tiling in the making: `ntiles` tiles starting at tb (device, ntiles + 1
+// entries) of at most `rows` rows, their list lengths in count.
+struct Tiling {
+  int32_t ntiles = 0, param = 0;
+  int64_t rows = 0;
+  int32_t *tb = nullptr, *count = nullptr;
+  std::vector<int32_t> hc;
+};
+
+void launch_halo(amg_hierarchy *h, const Level &L, const Tiling &T, int32_t pass,
+                 const Halo &H) {
   hipStream_t s = h->stream;
-  int32_t *count;
-  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&count), sizeof(int32_t) * (ntiles + 1)));
-  k_halo<<<ntiles, kHaloThreads, 0, s>>>(0, tb, L.S.sptr, L.S.col, count, nullptr, nullptr,
-                                        nullptr);
-  std::vector<int32_t> hc(ntiles);
-  AMG_HIP(hipMemcpyAsync(hc.data(), count, sizeof(int32_t) * ntiles, hipMemcpyDeviceToHost, s));
-  AMG_HIP(hipStreamSynchronize(s));
+  if (T.rows * L.S.max_width <= 2048)
+    k_halo<256, 2048><<<T.ntiles, 256, 0, s>>>(pass, T.tb, L.S.sptr, L.S.col, T.count, H.hptr,
+                                               H.hidx, H.lcol);
+  else
+    k_halo<1024, kHaloCap><<<T.ntiles, 1024, 0, s>>>(pass, T.tb, L.S.sptr, L.S.col, T.count,
+                                                     H.hptr, H.hidx, H.lcol);
+}
+
+// the tiles' starts and list lengths (the lengths on their way to the host)
+amg_status count_halo(amg_hierarchy *h, const Level &L, int32_t step, int32_t nmax,
+                      const int32_t *seg, Tiling *T) {
+  hipStream_t s = h->stream;
+  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&T->tb),
+                          sizeof(int32_t) * ((size_t)T->ntiles + 1)));
+  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&T->count),
+                          sizeof(int32_t) * ((size_t)T->ntiles + 1)));
+  k_tile_starts<<<ceil_div(T->ntiles + 1, kBlock), kBlock, 0, s>>>(T->ntiles, step, nmax, seg,
+                                                                   T->tb);
+  launch_halo(h, L, *T, 0, Halo{});
+  T->hc.resize(T->ntiles);
+  AMG_HIP(hipMemcpyAsync(T->hc.data(), T->count, sizeof(int32_t) * T->ntiles,
+                         hipMemcpyDeviceToHost, s));
+  return AMG_OK;
+}
+
+// Tile lists of level L. Leaves H empty (the kernels then gather from memory)
+// when a tile has too many entries to sort in LDS or too long a list for a
+// block's LDS.
+amg_status build_halo(amg_hierarchy *h, const Level &L, const Tiling &T, Halo *H) {
   int64_t total = 0;
   int32_t umax = 0;
   bool fits = true;
-  for (int32_t c : hc) {
+  for (int32_t c : T.hc) {
     fits = fits && c >= 0;
     umax = std::max(umax, c);
     total += c > 0 ? c : 0;
   }
-  if (!fits || umax > kHaloMaxList || total > INT32_MAX) {
-    setup_tmp_free(h, count);
-    return AMG_OK;
-  }
+  if (!fits || umax > kHaloMaxList || total > INT32_MAX) return AMG_OK;
   Halo G;
-  G.ntiles = ntiles;
-  G.param = param;
+  G.ntiles = T.ntiles;
+  G.param = T.param;
   G.umax = umax;
-  amg_status st = dalloc(h, &G.hptr, (size_t)ntiles + 1);
-  if (st == AMG_OK) st = setup_scan(h, count, G.hptr, ntiles);
-  if (st == AMG_OK) st = dalloc(h, &G.hidx, (size_t)(total > 0 ? total : 1));
-  if (st == AMG_OK) st = dalloc(h, &G.lcol, (size_t)L.S.nnz_padded);
-  if (st == AMG_OK)
-    k_halo<<<ntiles, kHaloThreads, 0, s>>>(1, tb, L.S.sptr, L.S.col, nullptr, G.hptr, G.hidx,
-                                          G.lcol);
-  setup_tmp_free(h, count);
-  AMG_TRY(st);
+  AMG_TRY(dalloc(h, &G.hptr, (size_t)T.ntiles + 1));
+  AMG_TRY(setup_scan(h, T.count, G.hptr, T.ntiles));
+  AMG_TRY(dalloc(h, &G.hidx, (size_t)(total > 0 ? total : 1)));
+  AMG_TRY(dalloc(h, &G.lcol, (size_t)L.S.nnz_padded));
+  launch_halo(h, L, T, 1, G);
   AMG_HIP(hipGetLastError());
   *H = G;
   return AMG_OK;
@@ -2386,28 +2437,26 @@ amg_status build_halo(amg_hierarchy *h, const Level &L, const int32_t *tb, int32
 // Level 0's tiles: the row chunks of the streaming kernels and the blocks of
 // the down step (coarse rows by coarse_per_block, fine rows by segment).
 amg_status build_level0_halos(amg_hierarchy *h) {
-  hipStream_t s = h->stream;
   Level &F = h->lv[0];
   // none on levels of kManyRows rows or more: there the kernels take one row
   // per thread (256-row tiles), and staging lost to the gathers from memory
   // (256^3 anisotropic blocks: 144.2 -> 138.6 ms per FP64 solve without tiles)
   if (F.n >= kManyRows) return AMG_OK;
   const Level &C = h->lv[1];
-  int32_t *tb;
   const Geom g = geom(F.n);
   const int32_t G = staged_down_G(h);
-  const int32_t nseg = ceil_div(C.n, G);
-  const int32_t most = std::max(g.grid, nseg);
-  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&tb), sizeof(int32_t) * (most + 1)));
-  k_tile_starts<<<ceil_div(g.grid + 1, kBlock), kBlock, 0, s>>>(g.grid, g.chunk, F.n, nullptr,
-                                                                tb);
-  amg_status st = build_halo(h, F, tb, g.grid, g.chunk, &F.hrow);
-  if (st == AMG_OK) {
-    k_tile_starts<<<ceil_div(nseg + 1, kBlock), kBlock, 0, s>>>(nseg, G, C.n, F.seg, tb);
-    st = build_halo(h, F, tb, nseg, G, &F.hseg);
-  }
-  setup_tmp_free(h, tb);
-  return st;
+  Tiling rows, segs;
+  rows.ntiles = g.grid;
+  rows.param = g.chunk;
+  rows.rows = g.chunk;
+  segs.ntiles = ceil_div(C.n, G);
+  segs.param = G;
+  segs.rows = (int64_t)G * h->max_seg;
+  AMG_TRY(count_halo(h, F, g.chunk, F.n, nullptr, &rows));
+  AMG_TRY(count_halo(h, F, G, C.n, F.seg, &segs));
+  AMG_HIP(hipStreamSynchronize(h->stream));
+  AMG_TRY(build_halo(h, F, rows, &F.hrow));
+  return build_halo(h, F, segs, &F.hseg);
 }
 
 // average row length from which a level of a smoothed hierarchy is smoothed
@@ -2445,81 +2494,76 @@ amg_status build_solve_formats(amg_hierarchy *h) {
                                               F.iperm, F.aggp, F.pp64);
     h->max_seg = std::max(h->max_seg, 1 << F.sweeps);
   }
+  // The widths of every level's slices, and whether every value of A on level
+  // 0 is an FP32 number: one wait for all of them. The coarsest level of
+  // several uses A_L^-1 only.
+  const auto has_sell = [&](int32_t l) { return l == 0 || l + 1 < nlev; };
+  std::vector<unsigned long long> stat(2 * nlev + 1, 0);
+  {
+    unsigned long long *dstat;
+    const size_t bytes = sizeof(unsigned long long) * stat.size();
+    AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&dstat), bytes));
+    AMG_HIP(hipMemsetAsync(dstat, 0, bytes, s));
+    const Level &L0 = h->lv[0];
+    k_not_fp32_exact<<<grid1(L0.nnz), kBlock, 0, s>>>(
+        L0.nnz, L0.val, reinterpret_cast<int32_t *>(dstat + 2 * nlev));
+    for (int32_t l = 0; l < nlev; ++l) {
+      if (!has_sell(l)) continue;
+      Level &L = h->lv[l];
+      L.S.n = L.n;
+      L.S.nslices = ceil_div(L.n, kSlice);
+      int32_t *w64;
+      AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&w64),
+                              sizeof(int32_t) * L.S.nslices + 16));
+      AMG_TRY(dalloc(h, &L.S.sptr, (size_t)L.S.nslices + 1));
+      k_sell_width<<<ceil_div(L.S.nslices, 1024 / kSlice), 1024, 0, s>>>(
+          L.n, L.S.nslices, L.rp, L.perm, w64, dstat + 2 * l);
+      AMG_TRY(setup_scan(h, w64, L.S.sptr, L.S.nslices));
+    }
+    AMG_HIP(hipMemcpyAsync(stat.data(), dstat, bytes, hipMemcpyDeviceToHost, s));
+    AMG_HIP(hipStreamSynchronize(s));
+  }
+  for (int32_t l = 0; l < nlev; ++l)
+    if (stat[2 * l] > (unsigned long long)INT32_MAX)
+      return AMG_ERR_ARG;  // padded rows exceed the format's 32-bit offsets
   for (int32_t l = 0; l < nlev; ++l) {
     Level &L = h->lv[l];
     const bool coarsest = (l == nlev - 1);
     // level 0 needs FP64 values for the outer CG; V-cycle levels need the
-    // hierarchy precision (plain and scaled); the coarsest uses A_L^-1 only
+    // hierarchy precision (plain and scaled)
     const bool need64 = (l == 0) || (!coarsest && !fp32);
     bool need32 = !coarsest && fp32;
     if (l == 0) {
       // every value of A an FP32 number: the FP64 products of level 0 read
       // the exact FP32 copy (identical arithmetic, half the value bytes)
       // unless AMG_FLAG_NO_VALUE_COMPRESSION switches it off
-      int32_t *flag;
-      AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&flag), sizeof(int32_t)));
-      AMG_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t), s));
-      k_not_fp32_exact<<<grid1(L.nnz), kBlock, 0, s>>>(L.nnz, L.val, flag);
-      int32_t hflag = 1;
-      AMG_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      AMG_HIP(hipStreamSynchronize(s));
-      setup_tmp_free(h, flag);
-      L.S.fp32_values = hflag == 0;
+      L.S.fp32_values = stat[2 * nlev] == 0;
       L.S.exact32 = L.S.fp32_values && !(h->params.flags & AMG_FLAG_NO_VALUE_COMPRESSION);
       need32 = need32 || L.S.exact32;
     }
-    if (need64 || need32) {
+    if (has_sell(l)) {
       Sell &S = L.S;
-      S.n = L.n;
-      S.nslices = ceil_div(L.n, kSlice);
-      int32_t *w64;
-      AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&w64), sizeof(int32_t) * S.nslices + 16));
-      unsigned long long *total;
-      AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&total), sizeof(unsigned long long)));
-      AMG_HIP(hipMemsetAsync(total, 0, sizeof(unsigned long long), s));
-      AMG_TRY(dalloc(h, &S.sptr, (size_t)S.nslices + 1));
-      k_sell_width<<<grid1(S.nslices), kBlock, 0, s>>>(L.n, S.nslices, L.rp, L.perm, w64, total);
-      unsigned long long htotal = 0;
-      AMG_HIP(hipMemcpyAsync(&htotal, total, sizeof(htotal), hipMemcpyDeviceToHost, s));
-      AMG_HIP(hipStreamSynchronize(s));
-      setup_tmp_free(h, total);
-      if (htotal > (unsigned long long)INT32_MAX) {
-        setup_tmp_free(h, w64);
-        return AMG_ERR_ARG;  // padded rows exceed the format's 32-bit offsets
+      const size_t padded = (size_t)stat[2 * l];
+      S.nnz_padded = (int64_t)padded;
+      S.max_width = (int32_t)stat[2 * l + 1];
+      AMG_TRY(dalloc(h, &S.col, padded));
+      if (need64) AMG_TRY(dalloc(h, &S.v64, padded));
+      if (need32) AMG_TRY(dalloc(h, &S.v32, padded));
+      if (!coarsest && !fp32) AMG_TRY(dalloc(h, &S.s64, padded));
+      if (!coarsest && fp32) AMG_TRY(dalloc(h, &S.s32, padded));
+      if (!coarsest) {
+        AMG_TRY(dalloc(h, &L.sminv64, (size_t)L.n));
+        if (fp32) {
+          AMG_TRY(dalloc(h, &L.sminv32, (size_t)L.n));
+          AMG_TRY(dalloc(h, &L.pp32, (size_t)L.n));
+        }
       }
-      AMG_TRY(setup_scan(h, w64, S.sptr, S.nslices));
-      setup_tmp_free(h, w64);
-      int32_t padded = 0;
-      AMG_HIP(hipMemcpyAsync(&padded, S.sptr + S.nslices, sizeof(int32_t),
-                             hipMemcpyDeviceToHost, s));
-      AMG_HIP(hipStreamSynchronize(s));
-      S.nnz_padded = padded;
-      if (L.n <= 1024) {  // small levels: the widest slice, for register-held rows
-        std::vector<int32_t> sp(S.nslices + 1);
-        AMG_HIP(hipMemcpyAsync(sp.data(), S.sptr, sizeof(int32_t) * (S.nslices + 1),
-                               hipMemcpyDeviceToHost, s));
-        AMG_HIP(hipStreamSynchronize(s));
-        for (int32_t q = 0; q < S.nslices; ++q)
-          S.max_width = std::max(S.max_width, (sp[q + 1] - sp[q]) / kSlice);
-      }
-      AMG_TRY(dalloc(h, &S.col, (size_t)padded));
-      if (need64) AMG_TRY(dalloc(h, &S.v64, (size_t)padded));
-      if (need32) AMG_TRY(dalloc(h, &S.v32, (size_t)padded));
-      if (!coarsest && !fp32) AMG_TRY(dalloc(h, &S.s64, (size_t)padded));
-      if (!coarsest && fp32) AMG_TRY(dalloc(h, &S.s32, (size_t)padded));
-      k_sell_fill<<<ceil_div((int64_t)S.nslices * kSlice, kBlock), kBlock, 0, s>>>(
-          L.n, S.nslices, L.rp, L.ci, L.val, L.perm, L.iperm, L.minv64, S.sptr, S.col, S.v64,
-          S.v32, S.s64, S.s32);
-    }
-    if (!coarsest) {
-      AMG_TRY(dalloc(h, &L.sminv64, (size_t)L.n));
-      k_gather_f64<<<grid1(L.n), kBlock, 0, s>>>(L.n, L.perm, L.minv64, L.sminv64);
-      if (fp32) {
-        AMG_TRY(dalloc(h, &L.sminv32, (size_t)L.n));
-        AMG_TRY(dalloc(h, &L.pp32, (size_t)L.n));
-        k_demote<<<grid1(L.n), kBlock, 0, s>>>(L.n, L.sminv64, L.sminv32);
-        k_demote<<<grid1(L.n), kBlock, 0, s>>>(L.n, L.pp64, L.pp32);
-      }
+      // long rows: their entries over several blocks
+      const int64_t mean = L.nnz / L.n;
+      const int32_t split = mean < 32 ? 1 : (mean < 512 ? (int32_t)(mean / 32) + 1 : 16);
+      k_sell_fill<<<dim3(S.nslices, split), kBlock, 0, s>>>(
+          L.n, L.rp, L.ci, L.val, L.perm, L.iperm, L.minv64, S.sptr,
+          SellOut{S.col, S.v64, S.v32, S.s64, S.s32, L.sminv64, L.sminv32, L.pp64, L.pp32});
     }
     AMG_TRY(alloc_level_vectors(h, L, vbytes));
     // K-cycle flexible-CG vectors on the levels strictly between the finest
