@@ -1585,7 +1585,7 @@ void free_batch(Batch *b, int device, hipStream_t s) {
   if (!b) return;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
-  for (void *p : b->allocs) stream_free(device, s, p);
+  stream_free(device, s, b->allocs);
   if (b->col_host) (void)hipHostFree(b->col_host);
   if (b->iter_host) (void)hipHostFree(b->iter_host);
   if (b->done_host) (void)hipHostFree(b->done_host);

@@ -262,14 +262,17 @@ struct amg_hierarchy {
 
 namespace amg {
 
-// allocation owned by the hierarchy (freed in amg_free)
 // Device memory of the library comes from one stream-ordered pool per device
 // (allocation and release are ordered on the given stream and never wait for
-// the whole device, unlike hipFree); freed memory up to kPoolKeepBytes stays
-// reserved in the pool for reuse. Without pool support: hipMalloc / hipFree.
+// the whole device, unlike hipFree). Freed blocks are kept, up to
+// kPoolKeepBytes per device, and given out again to any hierarchy; over that
+// the oldest go back to the device, all of them when an allocation fails.
+// Without pool support: hipMalloc / hipFree.
 constexpr uint64_t kPoolKeepBytes = 8ull << 30;
 amg_status stream_alloc(int device, hipStream_t s, void **p, size_t bytes);
-void stream_free(int device, hipStream_t s, void *p);
+// waits for the stream, the blocks' only user, first
+void stream_free(int device, hipStream_t s, const std::vector<void *> &blocks);
+// allocation owned by the hierarchy (freed in amg_free)
 amg_status dev_alloc(amg_hierarchy *h, void **p, size_t bytes);
 template <typename T>
 inline amg_status dalloc(amg_hierarchy *h, T **p, size_t count) {

@@ -1163,9 +1163,7 @@ struct Arena {
   }
   Arena(const Arena &) = delete;
   Arena &operator=(const Arena &) = delete;
-  ~Arena() {
-    for (void *p : blocks) stream_free(device, s, p);
-  }
+  ~Arena() { stream_free(device, s, blocks); }
   amg_status get(void **p, size_t bytes) {
     bytes = (bytes + 255) / 256 * 256;
     if (bytes > chunk / 4) {  // a large request gets a block of its own
@@ -1201,9 +1199,7 @@ struct Tmp {
       : device(h->device), s(h->stream), arena(static_cast<Arena *>(h->setup_arena)) {}
   Tmp(const Tmp &) = delete;
   Tmp &operator=(const Tmp &) = delete;
-  ~Tmp() {
-    for (void *p : ptrs) stream_free(device, s, p);
-  }
+  ~Tmp() { stream_free(device, s, ptrs); }
   template <typename T>
   amg_status get(T **p, size_t count) {
     void *q = nullptr;
@@ -1418,7 +1414,7 @@ amg_status setup_tmp_alloc(amg_hierarchy *h, void **p, size_t bytes) {
 }
 
 void setup_tmp_free(amg_hierarchy *h, void *p) {
-  if (!h->setup_arena) stream_free(h->device, h->stream, p);
+  if (!h->setup_arena) stream_free(h->device, h->stream, {p});
 }
 
 amg_status setup_scan(amg_hierarchy *h, const int32_t *in, int32_t *out, int32_t n) {
