@@ -603,7 +603,7 @@ size_t amg_estimate_footprint(int64_t n, int64_t nnz, const amg_params *params) 
   b += 4.0 * 1.02 * nnz;                        // exact FP32 copy of A_0 (when it applies)
   b += 2 * (2.0 * 1.02 * nnz + 4.0 * 2.5 * n);  // level 0's two sets of LDS tile lists
   b += 4 * V * sn;                              // V-cycle vectors
-  b += 6 * 8.0 * n;                             // CG vectors (x, r, z, p, q, b)
+  b += 7 * 8.0 * n;                             // CG vectors (x, r, z, p twice, q, b)
   b += (double)kPartPlanes * kMaxParts * 8.0;   // block partials
   if (P.cycle == AMG_CYCLE_K) b += 5 * V * (sn - n);  // K-cycle FCG vectors
   // the setup's temporaries (weights, matching state, Galerkin staging, sweep

@@ -65,6 +65,10 @@ struct PcgScal {
   int32_t maxit;
   int32_t done;   // 0 running, 1 converged, 2 maxit, 3 breakdown, 4 zero rhs
   int32_t phase;  // 0: next (r, z) initialises rho; 1: it also forms beta
+  // iterations whose kernels sum the scalars themselves (amg_hierarchy::fold):
+  // the iteration's (r, z) and count before they become rho and iter
+  double rho1;
+  int32_t iter1;
 };
 
 // Sliced ELLPACK, 64 rows per slice, column-major inside a slice so that
@@ -221,6 +225,12 @@ struct amg_hierarchy {
   // outer PCG state (FP64, level-0 size)
   // CG vectors, in the aggregate-major order of level 0
   double *x = nullptr, *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *b = nullptr;
+  // small systems: the scalars are summed by the kernels that use them, and
+  // p = z + beta p is formed by the product with A into the other p buffer
+  bool fold = false;
+  double *p2 = nullptr;
+  bool rr_in_down = false;  // the level-0 down step being launched sums (r, r)
+  bool rr_with_rz = false;  // the V-cycle being launched ends with both sums
   int32_t max_seg = 1;            // largest aggregate (segment) of any level
   double *partials = nullptr;     // kPartPlanes x kMaxParts block partial sums
   double *kscal = nullptr;  // K-cycle scalars, kKScal per level
@@ -234,7 +244,7 @@ struct amg_hierarchy {
   // graph of one CG iteration
   hipGraphExec_t iter_exec = nullptr;  // one CG iteration
   hipGraph_t iter_graph = nullptr;
-  hipGraphExec_t iter_exec4 = nullptr;  // kIterGroup CG iterations
+  hipGraphExec_t iter_exec4 = nullptr;  // a group of CG iterations
   hipGraph_t iter_graph4 = nullptr;
   bool graph_failed = false;
   // in-solve kernel timing (amg_time_kernel with AMG_TIME_IN_SOLVE): while

@@ -137,6 +137,11 @@ __device__ void block_partial(double (&v)[NV], double *partials) {
   }
 }
 
+// planes of the partials that a folded iteration's dot products use: each is
+// still read while the next is written
+constexpr int kRZPlane = 0, kPQPlane = 1, kRRPlane = 2;
+static_assert(kRRPlane < kPartPlanes, "planes");
+
 enum FinOp : int32_t {
   kFinInit = 0,  // (b, b), (r, r) of the initial residual
   kFinPQ = 1,    // CG: (p, q), alpha = rho / (p, q)
@@ -144,7 +149,8 @@ enum FinOp : int32_t {
   kFinRZ = 3,    // CG: (r, z), beta
   kFinTrue = 4,  // true residual
   kFinPQR = 5,   // flexible CG: (p, q), (p, r), alpha = (p, r) / (p, q)
-  kFinZQ = 6     // flexible CG: beta = -(z, q) / (p, q)
+  kFinZQ = 6,    // flexible CG: beta = -(z, q) / (p, q)
+  kFinRRZ = 7    // CG: (r, z) and (r, r): the stop test, then beta
 };
 
 __device__ __forceinline__ bool converged(double rr, double bb, double rtol) {
@@ -161,7 +167,7 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
   PcgScal sc;
   if (threadIdx.x == 0) sc = *scal;
   __shared__ double sh[2][1024 / kWave];
-  const int nv = op == kFinInit || op == kFinPQR ? 2 : 1;
+  const int nv = op == kFinInit || op == kFinPQR || op == kFinRRZ ? 2 : 1;
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   for (int q = 0; q < nv; ++q) {
     // this thread's partials in index order, sixteen loads at a time
@@ -211,6 +217,18 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
       if (converged(tot[0], sc.bb, sc.rtol)) scal->done = 1;
       else if (sc.iter + 1 >= sc.maxit) scal->done = 2;
       break;
+    case kFinRRZ:
+      scal->rr = tot[1];
+      scal->iter = sc.iter + 1;
+      if (converged(tot[1], sc.bb, sc.rtol)) {
+        scal->done = 1;
+        break;
+      }
+      if (sc.iter + 1 >= sc.maxit) {
+        scal->done = 2;
+        break;
+      }
+      [[fallthrough]];
     case kFinRZ:
       if (!(tot[0] > 0.0)) {
         scal->done = 3;
@@ -234,6 +252,55 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
       scal->rr_true = tot[0];
       break;
   }
+}
+
+// The sum of nparts partials by a block of kBlock threads, every one of which
+// gets it: k_finalize's sum in its order, thread t adding up what the threads
+// t, t + kBlock, ... of its 1024 would.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ src, int32_t nparts) {
+  constexpr int kRuns = 1024 / kBlock, kWaves = kBlock / kWave;
+  __shared__ double wsum[kRuns * kWaves];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+#pragma unroll
+  for (int k = 0; k < kRuns; ++k) {
+    double a = 0.0;
+    for (int32_t b0 = threadIdx.x + k * kBlock; b0 < nparts; b0 += 4 * 1024) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = b0 + u * 1024 < nparts ? src[b0 + u * 1024] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (b0 + u * 1024 < nparts) a += v[u];
+    }
+    if (k * kBlock < nparts)
+      for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kWave);
+    if (lane == 0) wsum[k * kWaves + wid] = a;
+  }
+  __syncthreads();
+  double t = wsum[0];
+  for (int k = 1; k < kRuns * kWaves; ++k) t += wsum[k];
+  return t;
+}
+
+// (r, r) and the stop test, by the level-0 down step of a folded iteration:
+// true if the solve goes on. Only block 0 writes, and nothing that a block
+// still starting reads but the flag, which then says what it would find.
+struct FinRR {
+  PcgScal *scal;
+  const double *partials;
+  int32_t nparts;
+};
+__device__ __forceinline__ bool stop_test(const FinRR &F) {
+  const int32_t iter = F.scal->iter1, maxit = F.scal->maxit;
+  const double bb = F.scal->bb, rtol = F.scal->rtol;
+  const double rr = sum_partials(F.partials, F.nparts);
+  const int32_t done = converged(rr, bb, rtol) ? 1 : (iter >= maxit ? 2 : 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    F.scal->rr = rr;
+    F.scal->iter = iter;
+    if (done) F.scal->done = done;
+  }
+  return done == 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -408,14 +475,15 @@ __global__ void k_permute_out(int32_t n, const int32_t *__restrict__ perm,
 // rows; thread t takes rows t, t + kBlock, ...).
 enum PreMode : int { kPreScaled = 0, kPreFromZ = 1, kPreStagedZ = 2 };
 
-template <typename TV, typename TR, int MODE, typename TA = TV, int R = 1>
+template <typename TV, typename TR, int MODE, typename TA = TV, int R = 1, bool FIN = false>
 __global__ void __launch_bounds__(kBlock) k_pre_restrict(
     int32_t nc, int32_t G, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
     const int32_t *__restrict__ col, const TA *__restrict__ val, const TV *__restrict__ minv,
     const TV *__restrict__ pp, const TR *__restrict__ r, TV *__restrict__ z,
-    TV *__restrict__ rc, const int32_t *__restrict__ done) {
+    TV *__restrict__ rc, const int32_t *__restrict__ done, FinRR fin = FinRR{}) {
   __shared__ TV sh[kBlock * R];
   if (*done) return;
+  if (FIN && !stop_test(fin)) return;
   const int32_t J0 = blockIdx.x * G;
   const int32_t J1 = min(nc, J0 + G);
   const int32_t f0 = seg[J0], f1 = seg[J1];
@@ -531,17 +599,18 @@ __device__ __forceinline__ TV sell_dot_lds(const uint16_t *__restrict__ lcol,
 // works down one contiguous range of tiles, so a tile's staged neighbours
 // were mostly just loaded into the same L2 by the tiles before it (160^3
 // FP64 down step 73.6 -> 64.4 us). The partial sums stay indexed by blockIdx.
-template <typename TV, typename TR, int MODE, typename TA = TV, int R = 1>
+template <typename TV, typename TR, int MODE, typename TA = TV, int R = 1, bool FIN = false>
 __global__ void __launch_bounds__(kBlock) k_pre_restrict_lds(
     int32_t nc, int32_t G, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
     const uint16_t *__restrict__ lcol, const int32_t *__restrict__ hptr,
     const int32_t *__restrict__ hidx, const TA *__restrict__ val, const TV *__restrict__ minv,
     const TV *__restrict__ pp, const TR *__restrict__ r, TV *__restrict__ z,
-    TV *__restrict__ rc, const int32_t *__restrict__ done) {
+    TV *__restrict__ rc, const int32_t *__restrict__ done, FinRR fin = FinRR{}) {
   extern __shared__ double lds_d[];
   TV *xs = reinterpret_cast<TV *>(lds_d);
   __shared__ TV sh[kBlock * R];
   if (*done) return;
+  if (FIN && !stop_test(fin)) return;
   const int32_t tb = xcd_block(blockIdx.x, gridDim.x);
   const int32_t J0 = tb * G;
   const int32_t J1 = min(nc, J0 + G);
@@ -1023,6 +1092,8 @@ __global__ void k_scal_init(PcgScal *s, double rtol, int32_t maxit) {
   s->maxit = maxit;
   s->done = 0;
   s->phase = 0;
+  s->rho1 = 0.0;
+  s->iter1 = 0;
 }
 
 // MODE 0: r = b - A x and partials of (b, b), (r, r)
@@ -1152,6 +1223,187 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
   } else if (i < n) {
     p[i] = copy ? z[i] : z[i] + beta * p[i];
   }
+}
+
+// ---- folded iterations ----
+//
+// On a small system a kernel costs its launch, about 4.6 us behind another one
+// of the graph, whatever it does: 9 kernels of an iteration at 20^3 took 42 us,
+// 15 at 96^3 110 us. The three one-block kernels that sum the partials are left
+// out: each block of the kernel that needs a sum forms it by itself, as long
+// as the partials are few (kFoldParts). And p = z + beta p joins the product
+// with A, which forms the entries it gathers from z and the old p and writes
+// the new p beside it, in the buffer of the other parity. What a kernel's
+// blocks read of the scalars its block 0 does not write, except the flag.
+
+//
+// Measured with every form at 8^3 to 192^3 (FP64, 1e-8; us a solve): all of it
+// 20^3 922 -> 739, 32^3 1263 -> 1040, 48^3 1885 -> 1715; up to 512 partials
+// (131 k rows): with 1024 (64^3) the blocks' sums cost what the kernels did, and
+// with 4000 10 % more. The direction in the product alone: 64^3 2552 -> 2480,
+// 96^3 4982 -> 4895, 128^3 8727 -> 8604, 160^3 15874 -> 15919 and 192^3 31449 ->
+// 31554 (it gathers two vectors and staging costs more than the kernel saved):
+// up to kDirRows. With it, (r, r) summed by the kernel that sums (r, z), one
+// kernel less for a V-cycle too many at the end: 64^3 -> 2459, 96^3 -> 4892,
+// 128^3 8621: up to kMergeRows.
+constexpr int32_t kFoldParts = 512;
+constexpr int32_t kDirRows = 1 << 21;
+constexpr int32_t kMergeRows = 1 << 20;
+
+// beta, the old and the new p; FOLD: beta from the partials of (r, z), summed
+// here. false: done, or a breakdown.
+struct Direction {
+  double beta;
+  bool first;
+  const double *po;
+  double *pn;
+};
+template <bool FOLD>
+__device__ __forceinline__ bool next_direction(PcgScal *scal, const double *partials,
+                                               int32_t nparts, double *p0, double *p1,
+                                               Direction *D) {
+  if (scal->done) return false;
+  const int32_t iter = scal->iter;
+  D->po = iter & 1 ? p1 : p0;
+  D->pn = iter & 1 ? p0 : p1;
+  D->first = iter == 0;
+  if (!FOLD) {
+    D->beta = scal->beta;
+    return true;
+  }
+  const double rho = scal->rho;
+  const double rz = sum_partials(partials + (int64_t)kRZPlane * kMaxParts, nparts);
+  if (!(rz > 0.0)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal->done = 3;
+    return false;
+  }
+  D->beta = D->first ? 0.0 : rz / rho;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    scal->rho1 = rz;
+    if (!D->first) scal->beta = D->beta;
+  }
+  return true;
+}
+
+// p = z + beta p, q = A p, partials of (p, q)
+template <typename TA, bool FOLD>
+__global__ void __launch_bounds__(kBlock) k_dir_spmv(
+    int32_t n, int32_t chunk, const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
+    const TA *__restrict__ val, const double *__restrict__ z, double *p0, double *p1,
+    double *__restrict__ q, double *__restrict__ partials, PcgScal *scal) {
+  Direction D;
+  if (!next_direction<FOLD>(scal, partials, gridDim.x, p0, p1, &D)) return;
+  auto dir = [&](int32_t c) -> double {
+    return D.first ? z[c] : z[c] + D.beta * D.po[c];
+  };
+  int32_t rb, re;
+  rows_of_block(n, chunk, &rb, &re);
+  double d[1] = {0.0};
+  for (int32_t row = rb + threadIdx.x; row < re; row += kBlock) {
+    int32_t base, w;
+    sell_row(sptr, row, &base, &w);
+    const double pi = dir(row);
+    const double acc = sell_dot_t<double, TA>(col, val, base, w, dir);
+    D.pn[row] = pi;
+    q[row] = acc;
+    d[0] += pi * acc;
+  }
+  block_partial<1>(d, partials + (int64_t)kPQPlane * kMaxParts);
+}
+
+// the same with the tile of block b = its row chunk (tiles hrow), XCD-aware order
+template <typename TA, bool FOLD>
+__global__ void __launch_bounds__(kBlock) k_dir_spmv_lds(
+    int32_t n, int32_t chunk, const int32_t *__restrict__ sptr, const uint16_t *__restrict__ lcol,
+    const int32_t *__restrict__ hptr, const int32_t *__restrict__ hidx,
+    const TA *__restrict__ val, const double *__restrict__ z, double *p0, double *p1,
+    double *__restrict__ q, double *__restrict__ partials, PcgScal *scal) {
+  extern __shared__ double lds_d[];
+  Direction D;
+  if (!next_direction<FOLD>(scal, partials, gridDim.x, p0, p1, &D)) return;
+  auto dir = [&](int32_t c) -> double {
+    return D.first ? z[c] : z[c] + D.beta * D.po[c];
+  };
+  int32_t rb, re;
+  const int32_t tb = xcd_block(blockIdx.x, gridDim.x);
+  rb = (int32_t)((int64_t)tb * chunk);
+  re = (int32_t)min((int64_t)n, (int64_t)rb + chunk);
+  const int32_t h0 = hptr[tb];
+  int32_t row = rb + (int32_t)threadIdx.x, nb = 0, nw = 0;
+  if (row < re) sell_row(sptr, row, &nb, &nw);
+  stage_tile(lds_d, hidx, h0, hptr[tb + 1] - h0, dir);
+  double d[1] = {0.0};
+  for (; row < re; row += kBlock) {
+    const int32_t base = nb, w = nw;
+    if (row + kBlock < re) sell_row(sptr, row + kBlock, &nb, &nw);
+    const double pi = dir(row);
+    const double acc = sell_dot_lds<double, TA>(lcol, val, base, w, lds_d);
+    D.pn[row] = pi;
+    q[row] = acc;
+    d[0] += pi * acc;
+  }
+  block_partial<1>(d, partials + (int64_t)kPQPlane * kMaxParts);
+}
+
+// alpha from the partials of (p, q); x += alpha p, r -= alpha q, partials of (r, r)
+__global__ void __launch_bounds__(kBlock) k_update_fold(int32_t n, int32_t chunk,
+                                                        double *__restrict__ x,
+                                                        double *__restrict__ r, const double *p0,
+                                                        const double *p1,
+                                                        const double *__restrict__ q,
+                                                        double *__restrict__ partials,
+                                                        PcgScal *scal) {
+  if (scal->done) return;
+  const double rho = scal->rho1;
+  const int32_t iter = scal->iter;
+  const double pq = sum_partials(partials + (int64_t)kPQPlane * kMaxParts, gridDim.x);
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  if (!(pq > 0.0)) {
+    if (lead) scal->done = 3;
+    return;
+  }
+  const double alpha = rho / pq;
+  if (lead) {
+    scal->pq = pq;
+    scal->alpha = alpha;
+    scal->rho = rho;
+    scal->iter1 = iter + 1;
+  }
+  const double *__restrict__ p = iter & 1 ? p0 : p1;
+  int32_t rb, re;
+  rows_of_block(n, chunk, &rb, &re);
+  double d[1] = {0.0};
+  for (int32_t i = rb + threadIdx.x; i < re; i += kBlock) {
+    x[i] += alpha * p[i];
+    const double ri = r[i] - alpha * q[i];
+    r[i] = ri;
+    d[0] += ri * ri;
+  }
+  block_partial<1>(d, partials + (int64_t)kRRPlane * kMaxParts);
+}
+
+// x += alpha p, r -= alpha q with alpha in the scalars, partials of (r, r) in
+// plane 1, beside the (r, z) to come
+__global__ void __launch_bounds__(kBlock) k_update_dir(int32_t n, int32_t chunk,
+                                                       double *__restrict__ x,
+                                                       double *__restrict__ r, const double *p0,
+                                                       const double *p1,
+                                                       const double *__restrict__ q,
+                                                       double *__restrict__ partials,
+                                                       const PcgScal *__restrict__ scal) {
+  if (scal->done) return;
+  const double alpha = scal->alpha;
+  const double *__restrict__ p = scal->iter & 1 ? p0 : p1;
+  int32_t rb, re;
+  rows_of_block(n, chunk, &rb, &re);
+  double d[1] = {0.0};
+  for (int32_t i = rb + threadIdx.x; i < re; i += kBlock) {
+    x[i] += alpha * p[i];
+    const double ri = r[i] - alpha * q[i];
+    r[i] = ri;
+    d[0] += ri * ri;
+  }
+  block_partial<1>(d, partials + kMaxParts);
 }
 
 // ---------------------------------------------------------------------------
@@ -1713,8 +1965,9 @@ void launch_k(const amg_hierarchy *h, K k, dim3 grid, dim3 block, uint32_t shmem
 // 16.7 M rows 2 rows were slower)
 inline int down_rows(int64_t n) { return n >= (1 << 21) && n < kManyRows ? 2 : 1; }
 
-void finalize(amg_hierarchy *h, int32_t op, int32_t nparts, const int32_t *done) {
-  k_finalize<<<1, 1024, 0, h->stream>>>(op, nparts, h->partials, h->scal, done);
+void finalize(amg_hierarchy *h, int32_t op, int32_t nparts, const int32_t *done, int plane = 0) {
+  k_finalize<<<1, 1024, 0, h->stream>>>(op, nparts, h->partials + (int64_t)plane * kMaxParts,
+                                        h->scal, done);
 }
 
 int32_t coarse_per_block(const amg_hierarchy *h) {
@@ -1729,25 +1982,39 @@ int32_t staged_down_G(const amg_hierarchy *h) { return coarse_per_block(h); }
 
 // Down step of level F into C: LDS-staged gathers where the level has tiles of
 // that geometry, else down_rows(n) fine rows per thread gathering from memory.
-template <typename TV, typename TR, int MODE, typename TA>
-void pre_restrict(const amg_hierarchy *h, const Level &F, const Level &C, const TA *val,
-                  const TV *mv, const TV *pp, const TR *r, TV *z, TV *rc, const int32_t *done) {
+template <typename TV, typename TR, int MODE, typename TA, bool FIN>
+void pre_restrict_fin(const amg_hierarchy *h, const Level &F, const Level &C, const TA *val,
+                      const TV *mv, const TV *pp, const TR *r, TV *z, TV *rc,
+                      const int32_t *done, const FinRR &fin) {
   hipStream_t s = h->stream;
   const int32_t Gt = staged_down_G(h);
   if (F.hseg.ok() && F.hseg.param == Gt && F.hseg.ntiles == ceil_div(C.n, Gt)) {
     const Halo &H = F.hseg;
-    launch_k(h, k_pre_restrict_lds<TV, TR, MODE, TA, 1>, dim3(ceil_div(C.n, Gt)), dim3(kBlock),
-             (uint32_t)(sizeof(TV) * H.umax), s, C.n, Gt, F.seg, F.S.sptr,
+    launch_k(h, k_pre_restrict_lds<TV, TR, MODE, TA, 1, FIN>, dim3(ceil_div(C.n, Gt)),
+             dim3(kBlock), (uint32_t)(sizeof(TV) * H.umax), s, C.n, Gt, F.seg, F.S.sptr,
              (const uint16_t *)H.lcol, (const int32_t *)H.hptr, (const int32_t *)H.hidx, val, mv,
-             pp, r, z, rc, done);
+             pp, r, z, rc, done, fin);
     return;
   }
   const int R = down_rows(F.n);
   const int32_t G = coarse_per_block(h) * R;
   const int32_t grid = ceil_div(C.n, G);
-  auto k = R == 2 ? k_pre_restrict<TV, TR, MODE, TA, 2> : k_pre_restrict<TV, TR, MODE, TA, 1>;
+  auto k = R == 2 ? k_pre_restrict<TV, TR, MODE, TA, 2, FIN>
+                  : k_pre_restrict<TV, TR, MODE, TA, 1, FIN>;
   launch_k(h, k, dim3(grid), dim3(kBlock), 0u, s, C.n, G, F.seg, F.S.sptr, F.S.col, val, mv, pp,
-           r, z, rc, done);
+           r, z, rc, done, fin);
+}
+
+template <typename TV, typename TR, int MODE, typename TA>
+void pre_restrict(const amg_hierarchy *h, const Level &F, const Level &C, const TA *val,
+                  const TV *mv, const TV *pp, const TR *r, TV *z, TV *rc, const int32_t *done) {
+  // (only level 0's right-hand side is double in both precisions)
+  if (MODE != kPreFromZ && h->rr_in_down && &F == &h->lv[0])
+    pre_restrict_fin<TV, TR, MODE, TA, MODE != kPreFromZ>(
+        h, F, C, val, mv, pp, r, z, rc, done,
+        FinRR{h->scal, h->partials + kRRPlane * kMaxParts, geom(F.n).grid});
+  else
+    pre_restrict_fin<TV, TR, MODE, TA, false>(h, F, C, val, mv, pp, r, z, rc, done, FinRR{});
 }
 
 // y = z + M^-1 (r - A z) on a level (DOT: with the block partials of the CG
@@ -1952,7 +2219,7 @@ void level0_post(amg_hierarchy *h, const double *r0, TV *z, double *z0, bool dot
       post_sweep<TV, double, double, true, TV>(h, F, vals<TV>(F), minv<TV>(F), r0, z, z0,
                                                h->partials, done, dv);
     h->probe_armed = false;
-    if (!dv) finalize(h, kFinRZ, g.grid, done);
+    if (!dv && !h->fold) finalize(h, h->rr_with_rz ? kFinRRZ : kFinRZ, g.grid, done);
   } else {
     if (a32)
       post_sweep<TV, double, double, false, float>(h, F, F.S.v32, minv<TV>(F), r0, z, z0,
@@ -2597,6 +2864,10 @@ amg_status build_solve_formats(amg_hierarchy *h) {
   AMG_TRY(dalloc(h, &h->partials, (size_t)kMaxParts * kPartPlanes));
   AMG_TRY(dalloc(h, &h->scal, 1));
   AMG_TRY(dalloc(h, &h->zero_flag, 4));
+  h->fold = h->params.cycle == AMG_CYCLE_V && !coarse_is_pcg(h) && nlev > 1 &&
+            geom(n0).grid <= kFoldParts;
+  if (h->params.cycle == AMG_CYCLE_V && !coarse_is_pcg(h) && nlev > 1 && n0 <= kDirRows)
+    AMG_TRY(dalloc(h, &h->p2, (size_t)n0));
   AMG_HIP(hipMemsetAsync(h->zero_flag, 0, sizeof(int32_t) * 4, s));
   AMG_HIP(hipMemsetAsync(h->scal, 0, sizeof(PcgScal), s));
   return AMG_OK;
@@ -2663,9 +2934,6 @@ void launch_xpay(amg_hierarchy *h, int32_t n, int32_t copy, const int32_t *done)
     k_xpay<1><<<grid1(n), kBlock, 0, h->stream>>>(n, h->z, h->p, h->scal, copy, done);
 }
 
-// One CG iteration: q = A p, alpha, x and r updates with the stop test,
-// z = B r with (r, z) and beta, p = z + beta p. Touches only hierarchy
-// buffers, so it is captured once and replayed.
 // One flexible-CG iteration (K-cycle, or the iterative coarsest solve):
 // q = A p with (p, q), (p, r), alpha = (p, r) / (p, q), the x and r updates
 // with the stop test, z = B r with (q, z), beta = -(z, q) / (p, q),
@@ -2693,16 +2961,70 @@ void fcg_iteration(amg_hierarchy *h) {
   launch_xpay(h, n, 0, done);
 }
 
+// the direction and the outer product
+template <bool FOLD, typename TA>
+void dir_spmv(amg_hierarchy *h, const TA *val) {
+  hipStream_t s = h->stream;
+  const Level &F = h->lv[0];
+  const Geom g = geom(F.n);
+  if (F.hrow.ok() && F.hrow.param == g.chunk && F.hrow.ntiles == g.grid) {
+    const Halo &H = F.hrow;
+    launch_k(h, k_dir_spmv_lds<TA, FOLD>, dim3(g.grid), dim3(kBlock),
+             (uint32_t)(sizeof(double) * H.umax), s, F.n, g.chunk, F.S.sptr,
+             (const uint16_t *)H.lcol, (const int32_t *)H.hptr, (const int32_t *)H.hidx, val,
+             (const double *)h->z, h->p, h->p2, h->q, h->partials, h->scal);
+    return;
+  }
+  launch_k(h, k_dir_spmv<TA, FOLD>, dim3(g.grid), dim3(kBlock), 0u, s, F.n, g.chunk, F.S.sptr,
+           F.S.col, val, (const double *)h->z, h->p, h->p2, h->q, h->partials, h->scal);
+}
+
+template <bool FOLD>
+void dir_spmv(amg_hierarchy *h) {
+  arm_probe(h, 4);
+  if (h->lv[0].S.exact32) dir_spmv<FOLD, float>(h, h->lv[0].S.v32);
+  else dir_spmv<FOLD, double>(h, h->lv[0].S.v64);
+  h->probe_armed = false;
+}
+
+// One CG iteration: (p = z + beta p,) q = A p, alpha, x and r updates with the
+// stop test, z = B r with (r, z) and beta(, p = z + beta p). Touches only
+// hierarchy buffers, so it is captured once and replayed.
 void cg_iteration(amg_hierarchy *h) {
   if (flexible(h)) {
     fcg_iteration(h);
     return;
   }
   hipStream_t s = h->stream;
+  if (h->fold) {
+    const int32_t *done = &h->scal->done;
+    const Geom g = geom(h->lv[0].n);
+    dir_spmv<true>(h);
+    k_update_fold<<<g.grid, kBlock, 0, s>>>(h->lv[0].n, g.chunk, h->x, h->r, h->p, h->p2, h->q,
+                                            h->partials, h->scal);
+    // the stop test in the first kernel of the V-cycle, where that is the
+    // one-sweep down step
+    h->rr_in_down = h->params.pre == 1 && !h->params.smooth_p;
+    if (!h->rr_in_down) finalize(h, kFinRR, g.grid, done, kRRPlane);
+    vcycle_perm(h, h->r, h->z, true, done);
+    h->rr_in_down = false;
+    return;
+  }
   Level &L0 = h->lv[0];
   const int32_t n = L0.n;
   const int32_t *done = &h->scal->done;
   const Geom g = geom(n);
+  if (h->p2) {
+    dir_spmv<false>(h);
+    finalize(h, kFinPQ, g.grid, done, kPQPlane);
+    k_update_dir<<<g.grid, kBlock, 0, s>>>(n, g.chunk, h->x, h->r, h->p, h->p2, h->q,
+                                           h->partials, h->scal);
+    h->rr_with_rz = n <= kMergeRows;
+    if (!h->rr_with_rz) finalize(h, kFinRR, g.grid, done, 1);
+    vcycle_perm(h, h->r, h->z, true, done);
+    h->rr_with_rz = false;
+    return;
+  }
   arm_probe(h, 4);
   spmv_dot0(h, h->p, h->q, done);
   h->probe_armed = false;
@@ -2739,16 +3061,17 @@ bool capture_iterations(amg_hierarchy *h, int32_t count, hipGraph_t *graph, hipG
   return true;
 }
 
-// Graphs of one and of kIterGroup CG iterations (once per hierarchy): a
+// Graphs of one and of iter_group() CG iterations (once per hierarchy): a
 // group replay saves the launch gap between consecutive graphs.
-constexpr int32_t kIterGroup = 4;
+// (folded iterations have about half the kernels: groups of eight)
+int32_t iter_group(const amg_hierarchy *h) { return h->fold ? 8 : 4; }
 amg_status ensure_iteration_graph(amg_hierarchy *h) {
   if (h->iter_exec || h->graph_failed || (h->params.flags & AMG_FLAG_NO_GRAPH)) return AMG_OK;
   if (!capture_iterations(h, 1, &h->iter_graph, &h->iter_exec)) {
     h->graph_failed = true;
     return AMG_OK;
   }
-  if (!capture_iterations(h, kIterGroup, &h->iter_graph4, &h->iter_exec4)) {
+  if (!capture_iterations(h, iter_group(h), &h->iter_graph4, &h->iter_exec4)) {
     h->iter_graph4 = nullptr;
     h->iter_exec4 = nullptr;
   }
@@ -2785,9 +3108,11 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
   k_zero_if_zero_rhs<<<grid1(n), kBlock, 0, s>>>(n, h->x, h->scal);
   if (flexible(h)) AMG_TRY(precond_perm(h, h->r, h->z, nullptr, done));
   else AMG_TRY(vcycle_perm(h, h->r, h->z, true, done));
-  launch_xpay(h, n, 1, done);
+  if (!h->p2) launch_xpay(h, n, 1, done);
   // iterations in chunks; the chunk length follows the observed convergence
-  int32_t queued = 0, chunk = 4;
+  // (folded ones queued after the last cost 10 us, a look at the scalars 50)
+  const int32_t group = iter_group(h);
+  int32_t queued = 0, chunk = h->fold ? 16 : 4;
   double rr_prev = -1.0;
   int32_t it_prev = 0;
   for (;;) {
@@ -2806,7 +3131,7 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
     const int32_t c = std::min(chunk, maxit - queued);
     int32_t k = 0;
     if (exec4)
-      for (; k + kIterGroup <= c; k += kIterGroup) AMG_HIP(hipGraphLaunch(exec4, s));
+      for (; k + group <= c; k += group) AMG_HIP(hipGraphLaunch(exec4, s));
     for (; k < c; ++k) {
       if (exec1) AMG_HIP(hipGraphLaunch(exec1, s));
       else cg_iteration(h);
@@ -2970,7 +3295,7 @@ amg_status time_in_solve(amg_hierarchy *h, int32_t kernel, int32_t reps, double 
                                                           h->partials);
   finalize(h, kFinInit, g.grid, nullptr);
   AMG_TRY(vcycle_perm(h, h->r, h->z, true, done));
-  launch_xpay(h, n, 1, done);
+  if (!h->p2) launch_xpay(h, n, 1, done);
   h->probe_ev.assign(2 * (size_t)reps, nullptr);
   amg_status st = AMG_OK;
   // timing-only events: no system-scope release at the timed dispatch's end
