@@ -24,6 +24,8 @@ namespace amg {
 namespace {
 
 constexpr int kBatchBlocks = 4096;  // x-blocks of a streaming batch kernel
+constexpr int kDownGroups = 2048;   // blocks from which kb_down_v takes four passes each
+constexpr int kAllCount = 2;          // Batch::all_done: the flag, and from here a 64-bit counter
 enum ColField { cRho = 0, cPq, cAlpha, cBeta, cRr, cBb, cRtol, cRrTrue, kColFields };
 enum BatchOp { bInit = 0, bPq, bRr, bRz0, bRz, bTrue };
 
@@ -290,6 +292,98 @@ __global__ void __launch_bounds__(kBlock) kb_pre_residual_v(
   }
 }
 
+// The down step of a level with one pre-sweep in one kernel: a block takes the
+// rows of kDownAggs aggregates in passes of kBlock / KT, the KT lanes of a team
+// form t = r - (A M^-1 r) of a row each and leave it in LDS, and then a lane per
+// aggregate and vector sums R_c = sum p t: the same sums in the same order as
+// kb_pre_residual_v and kb_restrict, without t or z = M^-1 r in memory
+// (kb_prolong_v forms z again from r), which is 12 of the 20 bytes per FP32
+// entry that the two moved. Level 0 of 128^3 at k = 32: 214 us for 282 + 71 in
+// FP32. What is left is waiting on gathered lines already on their way to L1
+// (its pending stalls are half of the kernel's cycles, memory is at 2.3 TB/s);
+// asking for a row's entries one pass ahead, or keeping the window's rows of R in LDS for the
+// gathers that fall into it, was no faster (214 and 324 us).
+// NP passes: with four, sums and waits are shared by more rows (102.4 against
+// 105.7 ms per solve with one, 128^3, k = 32); a level with fewer than kDownGroups
+// such blocks takes one pass per block and fills the chip instead (40^3,
+// k = 16: 3.40 against 3.80 ms).
+template <int KT, int NP>
+constexpr int kDownAggs = NP * kBlock / KT / 8 > 0 ? NP * kBlock / KT / 8 : 1;
+template <typename TV, int KT, bool SHF, int NP>
+__global__ void __launch_bounds__(kBlock) kb_down_v(
+    int32_t nc, int32_t kv, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
+    const int32_t *__restrict__ col, const TV *__restrict__ val, const TV *__restrict__ pp,
+    const TV *__restrict__ R, TV *__restrict__ Rc, const int32_t *__restrict__ stop) {
+  using V = typename Vec16<TV>::T;
+  constexpr int VW = Vec16<TV>::width;
+  constexpr int kRows = kBlock / KT;  // rows per pass
+  constexpr int M = kDownAggs<KT, NP>;
+  static_assert(M * KT <= kBlock, "one lane per aggregate and vector");
+  __shared__ V tl[NP * kBlock];
+  if (*stop) return;
+  const int32_t lane = (int32_t)threadIdx.x % KT, team = (int32_t)threadIdx.x / KT;
+  const int32_t jv = blockIdx.y * KT + lane;
+  const bool ok = jv < kv;
+  const V *Rv = reinterpret_cast<const V *>(R);
+  for (int64_t grp = first_group(); grp * M < nc; grp += gridDim.x) {
+    const int32_t a0 = (int32_t)(grp * M), a1 = nc - a0 < M ? nc : a0 + M;
+    const int32_t lo = seg[a0], hi = seg[a1];
+    const int32_t I = a0 + team;  // the aggregate that this lane sums
+    const bool mine = ok && team < M && I < a1;
+    const int32_t b = mine ? seg[I] : 0, e = mine ? seg[I + 1] : 0;
+    TV s[VW];
+#pragma unroll
+    for (int q = 0; q < VW; ++q) s[q] = 0;
+    for (int32_t c0 = lo; c0 < hi; c0 += NP * kRows) {
+      if (ok)
+        for (int32_t ps = 0; ps < NP; ++ps) {
+          const int32_t row = c0 + ps * kRows + team;
+          if (row >= hi) break;
+          int32_t base, w;
+          sell_row(sptr, row, &base, &w);
+          TV acc[VW];
+#pragma unroll
+          for (int q = 0; q < VW; ++q) acc[q] = 0;
+          for (int32_t k0 = 0; k0 < w; k0 += kRowBatch) {
+            int32_t c[kRowBatch];
+            TV v[kRowBatch];
+            V g[kRowBatch];
+            row_batch<KT, SHF>(col, val, base, k0, w, c, v);
+#pragma unroll
+            for (int u = 0; u < kRowBatch; ++u)
+              if (k0 + u < w) g[u] = Rv[(int64_t)c[u] * kv + jv];
+#pragma unroll
+            for (int u = 0; u < kRowBatch; ++u)
+              if (k0 + u < w) {
+                const TV *gu = reinterpret_cast<const TV *>(&g[u]);
+#pragma unroll
+                for (int q = 0; q < VW; ++q) acc[q] += v[u] * gu[q];
+              }
+          }
+          const V r = Rv[(int64_t)row * kv + jv];
+          const TV *ri = reinterpret_cast<const TV *>(&r);
+          V t;
+          TV *to = reinterpret_cast<TV *>(&t);
+#pragma unroll
+          for (int q = 0; q < VW; ++q) to[q] = ri[q] - acc[q];
+          tl[ps * kBlock + threadIdx.x] = t;
+        }
+      __syncthreads();
+      const int32_t m0 = b > c0 ? b : c0;
+      const int32_t m1 = e < c0 + NP * kRows ? e : c0 + NP * kRows;
+      for (int32_t m = m0; m < m1; ++m) {
+        const TV p = pp[m];
+        const V t = tl[(m - c0) * KT + lane];
+        const TV *tv = reinterpret_cast<const TV *>(&t);
+#pragma unroll
+        for (int q = 0; q < VW; ++q) s[q] += p * tv[q];
+      }
+      __syncthreads();  // the next rows overwrite tl
+    }
+    if (mine) st_vals(Rc + ((int64_t)I * kv + jv) * VW, s);
+  }
+}
+
 template <typename TV, typename TR, typename TO, int KT, bool DOT>
 __global__ void __launch_bounds__(kBlock) kb_post(
     int32_t n, int32_t k, const int32_t *__restrict__ sptr,
@@ -503,10 +597,12 @@ __global__ void kb_prolong(int32_t n, int32_t k, const int32_t *__restrict__ agg
   Z[i * k + j] += pp[i] * Zc[(int64_t)aggp[i] * k + j];
 }
 
-// the prolongation with VW consecutive columns per thread
-template <typename TV, int KT>
+// the prolongation with VW consecutive columns per thread; FROMR after
+// kb_down_v: z = M^-1 r is formed here, rounded as a stored z would be
+template <typename TV, int KT, bool FROMR>
 __global__ void kb_prolong_v(int32_t n, int32_t kv, const int32_t *__restrict__ aggp,
                              const TV *__restrict__ pp, const TV *__restrict__ Zc,
+                             const TV *__restrict__ minv, const TV *__restrict__ R,
                              TV *__restrict__ Z, const int32_t *__restrict__ stop) {
   using V = typename Vec16<TV>::T;
   constexpr int VW = Vec16<TV>::width;
@@ -517,11 +613,12 @@ __global__ void kb_prolong_v(int32_t n, int32_t kv, const int32_t *__restrict__ 
   const TV p = pp[i];
   const V c = reinterpret_cast<const V *>(Zc)[(int64_t)aggp[i] * kv + jv];
   V *zp = reinterpret_cast<V *>(Z) + i * kv + jv;
-  V z = *zp;
+  V z = FROMR ? reinterpret_cast<const V *>(R)[i * kv + jv] : *zp;
   const TV *cv = reinterpret_cast<const TV *>(&c);
   TV *zv = reinterpret_cast<TV *>(&z);
+  const TV mi = FROMR ? minv[i] : TV(1);
 #pragma unroll
-  for (int q = 0; q < VW; ++q) zv[q] += p * cv[q];
+  for (int q = 0; q < VW; ++q) zv[q] = fma(p, cv[q], FROMR ? zv[q] * mi : zv[q]);
   *zp = z;
 }
 
@@ -537,7 +634,10 @@ __global__ void kb_permute_rows(int32_t n, int32_t k, const int32_t *__restrict_
   else Dst[(int64_t)perm[q] * k + j] = Src[e];
 }
 
-// Z = A_L^-1 R on the coarsest level, one thread per (row, column)
+// Z = A_L^-1 R on the coarsest level, one thread per (row, column). A chain of
+// load latencies: kTerms terms are asked for before the first is used, without
+// a test of each while that many are left (against eight with tests,
+// a solve of 40^3 at k = 16 took 2.82 for 3.32 ms, of 64^3 at k = 32 11.6 for 12.1).
 template <typename TI, typename TO>
 __global__ void kb_coarse(int32_t nL, int32_t k, const double *__restrict__ Ainv,
                           const TI *__restrict__ R, TO *__restrict__ Z,
@@ -545,23 +645,23 @@ __global__ void kb_coarse(int32_t nL, int32_t k, const double *__restrict__ Ainv
   if (*stop) return;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (int64_t)nL * k) return;
+  constexpr int kTerms = 16;
   const int32_t i = (int32_t)(e / k), j = (int32_t)(e % k);
   const double *row = Ainv + (int64_t)i * nL;
   double s = 0.0;
-  for (int32_t m0 = 0; m0 < nL; m0 += 8) {  // loads of eight terms before their use
-    double av[8], rv[8];
+  int32_t m0 = 0;
+  for (; m0 + kTerms <= nL; m0 += kTerms) {
+    double av[kTerms];
+    TI rv[kTerms];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      av[u] = rv[u] = 0.0;
-      if (m0 + u < nL) {
-        av[u] = row[m0 + u];
-        rv[u] = (double)R[(int64_t)(m0 + u) * k + j];
-      }
+    for (int u = 0; u < kTerms; ++u) {
+      av[u] = row[m0 + u];
+      rv[u] = R[(int64_t)(m0 + u) * k + j];
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (m0 + u < nL) s += av[u] * rv[u];
+    for (int u = 0; u < kTerms; ++u) s += av[u] * (double)rv[u];
   }
+  for (; m0 < nL; ++m0) s += row[m0] * (double)R[(int64_t)m0 * k + j];
   Z[e] = (TO)s;
 }
 
@@ -884,38 +984,9 @@ __global__ void kb_init_cols(int32_t k, double rtol, int32_t maxit, double *colv
   done[j] = maxit < 0 ? 2 : 0;
 }
 
-// per-column fixed-order sum of the block partials and the CG update of op
-__global__ void __launch_bounds__(kBlock) kb_finalize(int32_t op, int32_t nparts, int32_t k,
-                                                      const double *__restrict__ partials,
-                                                      double *__restrict__ colv,
-                                                      int32_t *__restrict__ iter,
-                                                      int32_t *__restrict__ done,
-                                                      int32_t *__restrict__ xpend, int32_t maxit,
-                                                      const int32_t *__restrict__ stop) {
-  const int32_t j = blockIdx.x;
-  // the previous iteration's x update has been applied by now (also in
-  // iterations queued after every column stopped)
-  if (op == bPq && threadIdx.x == 0) xpend[j] = 0;
-  if (stop && *stop) return;
-  __shared__ double sh[2][kBlock / kWave];
-  const int nv = op == bInit ? 2 : 1;
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int64_t plane = (int64_t)kBatchBlocks * k;
-  for (int q = 0; q < nv; ++q) {
-    double a = 0.0;
-    for (int32_t b = threadIdx.x; b < nparts; b += kBlock) a += partials[q * plane + (int64_t)b * k + j];
-    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kWave);
-    if (lane == 0) sh[q][wid] = a;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  double tot[2] = {0.0, 0.0};
-  for (int q = 0; q < nv; ++q) {
-    double t = sh[q][0];
-    for (int w = 1; w < kBlock / kWave; ++w) t += sh[q][w];
-    tot[q] = t;
-  }
-  double *c = colv;
+// column j's scalars from the sums of op
+__device__ void column_step(int32_t op, int32_t j, int32_t k, const double (&tot)[2], double *c,
+                            int32_t *iter, int32_t *done, int32_t *xpend, int32_t maxit) {
   const double rtol = c[cRtol * k + j];
   if (op == bTrue) {
     c[cRrTrue * k + j] = tot[0];
@@ -962,11 +1033,59 @@ __global__ void __launch_bounds__(kBlock) kb_finalize(int32_t op, int32_t nparts
   }
 }
 
-__global__ void kb_all_done(int32_t k, const int32_t *done, int32_t *stop) {
+// per-column fixed-order sum of the block partials and the CG update of op;
+// for bInit and bRr (all not null) the block that counts itself last also
+// notes in *all whether every column has stopped, a launch of its own before
+// (4.6 us of an iteration). The partials of a thread are all asked for before
+// the first is used: one after the other they took 11 us at 4096 blocks and
+// k = 32.
+__global__ void __launch_bounds__(kBlock) kb_finalize(int32_t op, int32_t nparts, int32_t k,
+                                                      const double *__restrict__ partials,
+                                                      double *__restrict__ colv,
+                                                      int32_t *__restrict__ iter,
+                                                      int32_t *__restrict__ done,
+                                                      int32_t *__restrict__ xpend, int32_t maxit,
+                                                      int32_t *all, const int32_t *stop) {
+  const int32_t j = blockIdx.x;
+  // the previous iteration's x update has been applied by now (also in
+  // iterations queued after every column stopped)
+  if (op == bPq && threadIdx.x == 0) xpend[j] = 0;
+  if (stop && *stop) return;
+  __shared__ double sh[2][kBlock / kWave];
+  const int nv = op == bInit ? 2 : 1;
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  const int64_t plane = (int64_t)kBatchBlocks * k;
+  for (int q = 0; q < nv; ++q) {
+    constexpr int kPer = kBatchBlocks / kBlock;
+    double v[kPer], a = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int32_t b = (int32_t)threadIdx.x + i * kBlock;
+      v[i] = b < nparts ? partials[q * plane + (int64_t)b * k + j] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) a += v[i];
+    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kWave);
+    if (lane == 0) sh[q][wid] = a;
+  }
+  __syncthreads();
   if (threadIdx.x != 0) return;
-  int32_t all = 1;
-  for (int32_t j = 0; j < k; ++j) all &= done[j] != 0 ? 1 : 0;
-  *stop = all;
+  double tot[2] = {0.0, 0.0};
+  for (int q = 0; q < nv; ++q) {
+    double t = sh[q][0];
+    for (int w = 1; w < kBlock / kWave; ++w) t += sh[q][w];
+    tot[q] = t;
+  }
+  column_step(op, j, k, tot, colv, iter, done, xpend, maxit);
+  if (!all) return;
+  // columns that have come and, from bit 32, stopped
+  unsigned long long *count = reinterpret_cast<unsigned long long *>(all + kAllCount);
+  const unsigned long long c = atomicAdd(count, 1ull + (done[j] != 0 ? 1ull << 32 : 0ull)) + 1ull +
+                               (done[j] != 0 ? 1ull << 32 : 0ull);
+  if ((int32_t)(c & 0xffffffffull) == k) {
+    *all = (int32_t)(c >> 32) == k ? 1 : 0;
+    *count = 0;
+  }
 }
 
 // the vector kernels' tile for kv vectors per row: row_tile(kv) scaled by
@@ -1034,7 +1153,8 @@ const float *ppv<float>(const Level &L) { return L.pp32; }
 void bfinalize(amg_hierarchy *h, int32_t op, int32_t nparts, int32_t maxit, const int32_t *stop) {
   Batch &B = *h->batch;
   kb_finalize<<<B.k, kBlock, 0, h->stream>>>(op, nparts, B.k, B.partials, B.col, B.iter, B.done,
-                                            B.xpend, maxit, stop);
+                                            B.xpend, maxit,
+                                            op == bInit || op == bRr ? B.all_done : nullptr, stop);
 }
 
 // whether the block solve keeps the V-cycle's output in Batch::Zf: an FP32
@@ -1046,6 +1166,31 @@ bool z32(const amg_hierarchy *h) {
          aligned16(B.z[0]) && aligned16(B.y[0]) && aligned16(B.t[0]) && B.k % 2 == 0 &&
          aligned16(B.X) && aligned16(B.P) && aligned16(B.Q) &&
          (!B.Rf || reinterpret_cast<uintptr_t>(B.Rf) % 8 == 0);
+}
+
+// kb_down_v on level l with NP passes per block, or with one where that leaves
+// fewer than kDownGroups blocks
+template <typename TV, int NP>
+void down_vec(amg_hierarchy *h, int32_t l, const TV *R, TV *Rc, const int32_t *stop) {
+  Batch &B = *h->batch;
+  const Level &F = h->lv[l];
+  const int32_t nc = h->lv[l + 1].n, kv = B.k / Vec16<TV>::width;
+  with_vec_tile(B, kv, [&](auto kt) {
+    constexpr int KV = decltype(kt)::value;
+    const int64_t groups = ceil_div(nc, kDownAggs<KV, NP>);
+    if constexpr (NP > 1)
+      if (groups < kDownGroups) {
+        down_vec<TV, 1>(h, l, R, Rc, stop);
+        return;
+      }
+    const dim3 g((unsigned)std::min<int64_t>(groups, kBatchBlocks), (unsigned)ceil_div(kv, KV));
+    if (kv % KV == 0)  // every lane of a team active: shuffled index loads
+      kb_down_v<TV, KV, true, NP><<<g, kBlock, 0, h->stream>>>(
+          nc, kv, F.seg, F.S.sptr, F.S.col, svals<TV>(F), ppv<TV>(F), R, Rc, stop);
+    else
+      kb_down_v<TV, KV, false, NP><<<g, kBlock, 0, h->stream>>>(
+          nc, kv, F.seg, F.S.sptr, F.S.col, svals<TV>(F), ppv<TV>(F), R, Rc, stop);
+  });
 }
 
 // one block V-cycle: Z = B_0 R on all k columns; with rz_op >= 0 also the
@@ -1079,6 +1224,7 @@ void vcycle_b(amg_hierarchy *h, const double *R0, double *Z0, int32_t rz_op, int
                       ? reinterpret_cast<const TV *>(B.Rf)
                       : nullptr;
   std::vector<TV *> zc(L), yout(L + 1);
+  std::vector<const TV *> zr(L);  // the level's residual where kb_down_v left z unformed
   for (int32_t l = 0; l < L; ++l) {
     Level &F = h->lv[l];
     const BGeom g = bgeom(F.n, k, KT);
@@ -1090,7 +1236,18 @@ void vcycle_b(amg_hierarchy *h, const double *R0, double *Z0, int32_t rz_op, int
                                        ? reinterpret_cast<const TV *>(R0)
                                        : nullptr));
     constexpr int VW = Vec16<TV>::width;
-    if (Rl && k % VW == 0 && aligned16(Rl) && aligned16(z) && aligned16(t))
+    const Level &C = h->lv[l + 1];
+    const bool vec = Rl && k % VW == 0 && aligned16(Rl) && aligned16(z) && aligned16(t);
+    zr[l] = vec && pre == 1 && aligned16(B.r[l + 1]) &&
+                    aligned16(B.y[l + 1]) && aligned16(B.z[l + 1]) && aligned16(B.t[l + 1])
+                ? Rl
+                : nullptr;
+    if (zr[l]) {
+      down_vec<TV, 4>(h, l, Rl, (TV *)B.r[l + 1], stop);
+      zc[l] = z;
+      continue;
+    }
+    if (vec)
       with_vec_tile(B, k / VW, [&](auto kt) {
         constexpr int KV = decltype(kt)::value;
         const BGeom gv = bgeom(F.n, k / VW, KV);
@@ -1137,7 +1294,6 @@ void vcycle_b(amg_hierarchy *h, const double *R0, double *Z0, int32_t rz_op, int
             F.n, k, F.S.sptr, F.S.col, vals<TV>(F), (const TV *)B.r[l], z, t, stop);
     }
     zc[l] = z;
-    const Level &C = h->lv[l + 1];
     with_row_tile(k, [&](auto kt) {
       constexpr int KE = decltype(kt)::value;
       kb_restrict<TV, KE><<<egrid(C.n, k, KE), kBlock, 0, s>>>(C.n, k, F.seg, ppv<TV>(F), t,
@@ -1154,11 +1310,16 @@ void vcycle_b(amg_hierarchy *h, const double *R0, double *Z0, int32_t rz_op, int
   for (int32_t l = L - 1; l >= 0; --l) {
     Level &F = h->lv[l];
     constexpr int VW = Vec16<TV>::width;
-    if (k % VW == 0 && aligned16(yout[l + 1]) && aligned16(zc[l]))
+    if (zr[l] || (k % VW == 0 && aligned16(yout[l + 1]) && aligned16(zc[l])))
       with_vec_tile(B, k / VW, [&](auto kt) {
         constexpr int KE = decltype(kt)::value;
-        kb_prolong_v<TV, KE><<<egrid(F.n, k / VW, KE), kBlock, 0, s>>>(
-            F.n, k / VW, F.aggp, ppv<TV>(F), yout[l + 1], zc[l], stop);
+        const dim3 ge = egrid(F.n, k / VW, KE);
+        if (zr[l])
+          kb_prolong_v<TV, KE, true><<<ge, kBlock, 0, s>>>(
+              F.n, k / VW, F.aggp, ppv<TV>(F), yout[l + 1], minv<TV>(F), zr[l], zc[l], stop);
+        else
+          kb_prolong_v<TV, KE, false><<<ge, kBlock, 0, s>>>(
+              F.n, k / VW, F.aggp, ppv<TV>(F), yout[l + 1], nullptr, nullptr, zc[l], stop);
       });
     else
       with_row_tile(k, [&](auto kt) {
@@ -1178,9 +1339,23 @@ void vcycle_b(amg_hierarchy *h, const double *R0, double *Z0, int32_t rz_op, int
       const bool last = sw + 1 == post;
       if (l > 0) {
         TV *out = other(z);
-        kb_post<TV, TV, TV, KT, false><<<tgrid(g, k, KT), kBlock, 0, s>>>(
-            F.n, k, F.S.sptr, F.S.col, vals<TV>(F), minv<TV>(F), (const TV *)B.r[l], z,
-            out, nullptr, stop);
+        const TV *Rl = (const TV *)B.r[l];
+        if (k % VW == 0 && aligned16(Rl) && aligned16(z) && aligned16(out))
+          with_vec_tile(B, k / VW, [&](auto kt) {
+            constexpr int KV = decltype(kt)::value;
+            const BGeom gv = bgeom(F.n, k / VW, KV);
+            if ((k / VW) % KV == 0)
+              kb_post_v<TV, TV, TV, KV, false, true><<<gv.grid, kBlock, 0, s>>>(
+                  F.n, k / VW, F.S.sptr, F.S.col, vals<TV>(F), minv<TV>(F), Rl, z, out,
+                  nullptr, stop);
+            else
+              kb_post_v<TV, TV, TV, KV, false, false><<<gv.grid, kBlock, 0, s>>>(
+                  F.n, k / VW, F.S.sptr, F.S.col, vals<TV>(F), minv<TV>(F), Rl, z, out,
+                  nullptr, stop);
+          });
+        else
+          kb_post<TV, TV, TV, KT, false><<<tgrid(g, k, KT), kBlock, 0, s>>>(
+              F.n, k, F.S.sptr, F.S.col, vals<TV>(F), minv<TV>(F), Rl, z, out, nullptr, stop);
         z = out;
         if (last) yout[l] = out;
       } else if (!last) {
@@ -1332,7 +1507,6 @@ void iteration_b(amg_hierarchy *h, int32_t maxit) {
   }
   bfinalize(h, bPq, np, maxit, stop);
   bfinalize(h, bRr, cg_update(h, stop), maxit, stop);
-  kb_all_done<<<1, 64, 0, s>>>(k, B.done, B.all_done);
   vcycle_b<TV, KT>(h, B.R, B.Z, bRz, maxit, stop);
   if (z32(h))
     with_vec_tile(B, k / 2, [&](auto kt) {
@@ -1529,7 +1703,6 @@ amg_status autotune(amg_hierarchy *h) {
   int32_t np = 0;
   spmv_mode(h, B.X, B.Bp, B.R, 1, &np);
   bfinalize(h, bInit, np, INT32_MAX, nullptr);
-  kb_all_done<<<1, 64, 0, s>>>(k, B.done, B.all_done);
   dispatch_vcycle<TV>(h, B.R, B.Z, bRz0, INT32_MAX, B.all_done);
   small_kernel(h, 1);  // P = Z
   AMG_HIP(hipGetLastError());
@@ -1636,7 +1809,6 @@ amg_status pcg_batch(amg_hierarchy *h, int32_t k, const double *Bu, double *Xu, 
   spmv_mode(h, B.X, B.Bp, B.R, 1, &np);
   bfinalize(h, bInit, np, maxit, nullptr);
   small_kernel(h, 0);  // zero the columns of zero right-hand sides
-  kb_all_done<<<1, 64, 0, s>>>(k, B.done, B.all_done);
   if (fp32) dispatch_vcycle<float>(h, B.R, B.Z, bRz0, maxit, B.all_done);
   else dispatch_vcycle<double>(h, B.R, B.Z, bRz0, maxit, B.all_done);
   small_kernel(h, 1);  // P = Z
