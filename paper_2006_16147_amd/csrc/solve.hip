@@ -475,6 +475,53 @@ __global__ void k_permute_out(int32_t n, const int32_t *__restrict__ perm,
 // rows; thread t takes rows t, t + kBlock, ...).
 enum PreMode : int { kPreScaled = 0, kPreFromZ = 1, kPreStagedZ = 2 };
 
+// A K-cycle level's first flexible-CG step: its vectors and block partials of
+// rho1 = (c1, v1) and (c1, b).
+template <typename TV>
+struct KSub {
+  const TV *b, *v1;
+  const double *partials;
+  int32_t nparts;
+  double *ks;
+};
+
+// s1 = (c1, b) / rho1, summed by every block in the same order (so all blocks
+// hold the same s1); block 0 keeps both for the second step and the prolongation
+template <typename TV>
+__device__ __forceinline__ double first_step(const KSub<TV> &S) {
+  __shared__ double sh[2][kBlock / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  for (int q = 0; q < 2; ++q) {
+    const double *src = S.partials + (int64_t)q * kMaxParts;
+    double a = 0.0;
+    for (int32_t b0 = threadIdx.x; b0 < S.nparts; b0 += 16 * kBlock) {
+      double v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int32_t bb = b0 + u * kBlock;
+        v[u] = bb < S.nparts ? src[bb] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (b0 + u * kBlock < S.nparts) a += v[u];
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kWave);
+    if (lane == 0) sh[q][wid] = a;
+  }
+  __syncthreads();
+  double rho1 = sh[0][0], cb = sh[1][0];
+  for (int k = 1; k < kBlock / kWave; ++k) {
+    rho1 += sh[0][k];
+    cb += sh[1][k];
+  }
+  const double s1 = rho1 > 0.0 ? cb / rho1 : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    S.ks[kRho1] = rho1;
+    S.ks[kS1] = s1;
+  }
+  return s1;
+}
+
 template <typename TV, typename TR, int MODE, typename TA = TV, int R = 1, bool FIN = false>
 __global__ void __launch_bounds__(kBlock) k_pre_restrict(
     int32_t nc, int32_t G, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
@@ -513,6 +560,45 @@ __global__ void __launch_bounds__(kBlock) k_pre_restrict(
     const int32_t b = (J == Jt ? sb : seg[J]) - f0, e = (J == Jt ? se : seg[J + 1]) - f0;
     TV s = 0;
     for (int32_t m = b; m < e; ++m) s += sh[m];
+    rc[J] = s;
+  }
+}
+
+// k_pre_restrict (one sweep, A M^-1, one row per thread) of r1 = b - s1 v1, which is formed at
+// each entry that is gathered and stored in r1 for the kernels that follow:
+// k_kresid and its launch less in the second step of a K-cycle level
+template <typename TV>
+__global__ void __launch_bounds__(kBlock) k_kdown(
+    int32_t nc, int32_t G, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
+    const int32_t *__restrict__ col, const TV *__restrict__ val, const TV *__restrict__ minv,
+    const TV *__restrict__ pp, KSub<TV> sub, TV *__restrict__ r1, TV *__restrict__ z,
+    TV *__restrict__ rc, const int32_t *__restrict__ done) {
+  __shared__ TV sh[kBlock];
+  if (*done) return;
+  const TV *__restrict__ b = sub.b, *__restrict__ v1 = sub.v1;
+  const int32_t J0 = blockIdx.x * G;
+  const int32_t J1 = min(nc, J0 + G);
+  const int32_t f0 = seg[J0], f1 = seg[J1];
+  const int32_t Jt = J0 + (int32_t)threadIdx.x;
+  const int32_t sb = Jt < J1 ? seg[Jt] : 0, se = Jt < J1 ? seg[Jt + 1] : 0;
+  const TV s1 = (TV)first_step(sub);
+  const int32_t row = f0 + (int32_t)threadIdx.x;
+  if (row < f1) {
+    const TV ri = b[row] - s1 * v1[row];
+    const TV mi = minv[row], pv = pp[row];
+    int32_t base, w;
+    sell_row(sptr, row, &base, &w);
+    const TV acc =
+        sell_dot_t<TV, TV>(col, val, base, w, [&](int32_t c) { return b[c] - s1 * v1[c]; });
+    r1[row] = ri;
+    z[row] = ri * mi;
+    sh[threadIdx.x] = pv * (ri - acc);
+  }
+  __syncthreads();
+  for (int32_t J = Jt; J < J1; J += kBlock) {
+    const int32_t m0 = (J == Jt ? sb : seg[J]) - f0, e = (J == Jt ? se : seg[J + 1]) - f0;
+    TV s = 0;
+    for (int32_t m = m0; m < e; ++m) s += sh[m];
     rc[J] = s;
   }
 }
@@ -1249,6 +1335,11 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 constexpr int32_t kFoldParts = 512;
 constexpr int32_t kDirRows = 1 << 21;
 constexpr int32_t kMergeRows = 1 << 20;
+// K-cycle levels of up to so many rows take the prolongation in the post-sweep
+// (k_kpost) and r1 = b - s1 v1 in the down step (k_kdown): 80^3 to 1e-6 in FP64
+// 3797 -> 3318 us with limit 131 k, 3304 with 1 M and 3348 with 16 k rows, 160^3
+// 10655, 10738 and 10759: where launches cost more than the larger gathers.
+constexpr int32_t kUpRows = 131072;
 
 // beta, the old and the new p; FOLD: beta from the partials of (r, z), summed
 // here. false: done, or a breakdown.
@@ -1437,11 +1528,70 @@ __global__ void __launch_bounds__(kBlock) k_spmv_dots(
   block_partial<NV>(d, partials);
 }
 
-// One block: the level's second flexible-CG step scalars from the block
-// partials (rho1 and s1 = (c1, b) / rho1 come from k_kresid): gamma =
-// (c2, v1), rho2 = (c2, v2) - gamma^2 / rho1, s2 = (c2, r1) / rho2,
-// a1 = s1 - s2 (gamma / rho1); x = a1 c1 + s2 c2. rho1 <= 0 gives x = 0,
-// rho2 <= 0 gives x = s1 c1.
+// The scalars of a level's second flexible-CG step from beta = (c2, v2), gamma =
+// (c2, v1) and a2 = (c2, r1) (rho1 and s1 = (c1, b) / rho1 come from the first):
+// rho2 = beta - gamma^2 / rho1, s2 = a2 / rho2, a1 = s1 - s2 (gamma / rho1);
+// x = a1 c1 + s2 c2. rho1 <= 0 gives x = 0, rho2 <= 0 gives x = s1 c1.
+__device__ __forceinline__ void second_step(const double *ks, double beta, double gamma, double a2,
+                                            double *a1, double *s2) {
+  const double rho1 = ks[kRho1], s1 = ks[kS1];
+  *a1 = *s2 = 0.0;
+  if (!(rho1 > 0.0)) return;
+  const double rho2 = beta - gamma * gamma / rho1;
+  *a1 = s1;
+  if (!(rho2 > 0.0)) return;
+  *s2 = a2 / rho2;
+  *a1 = s1 - *s2 * (gamma / rho1);
+}
+
+// The sums of N planes of at most 1024 partials by a block of kBlock threads:
+// those of sum_partials, with all loads before the first barrier.
+template <int N>
+__device__ __forceinline__ void sum_planes(const double *__restrict__ partials, int32_t nparts,
+                                           double (&out)[N]) {
+  constexpr int kRuns = 1024 / kBlock, kWaves = kBlock / kWave;
+  __shared__ double wsum[N][kRuns * kWaves];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  double v[N][kRuns];
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) {
+      const int32_t b = (int32_t)threadIdx.x + k * kBlock;
+      v[q][k] = b < nparts ? partials[(int64_t)q * kMaxParts + b] : 0.0;
+    }
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) {
+      if (k * kBlock < nparts)
+        for (int o = kWave / 2; o > 0; o >>= 1) v[q][k] += __shfl_down(v[q][k], o, kWave);
+      if (lane == 0) wsum[q][k * kWaves + wid] = v[q][k];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    out[q] = wsum[q][0];
+    for (int k = 1; k < kRuns * kWaves; ++k) out[q] += wsum[q][k];
+  }
+}
+
+// a1 and s2 of a level: those k_kfin or k_ktail stored, or, with nparts > 0,
+// from the partials of the second step, summed here by every block
+__device__ __forceinline__ void step_scalars(const double *__restrict__ partials, int32_t nparts,
+                                             const double *ks, double *a1, double *s2) {
+  if (nparts == 0) {
+    *a1 = ks[kA1];
+    *s2 = ks[kS2];
+    return;
+  }
+  double t[3];
+  sum_planes(partials, nparts, t);
+  second_step(ks, t[0], t[1], t[2], a1, s2);
+}
+
+// One block: the level's second step from its block partials, where there are
+// more of them than kFoldParts
 __global__ void __launch_bounds__(1024) k_kfin(int32_t nparts,
                                                const double *__restrict__ partials,
                                                double *__restrict__ ks,
@@ -1475,47 +1625,44 @@ __global__ void __launch_bounds__(1024) k_kfin(int32_t nparts,
     for (int k = 1; k < (int)(blockDim.x / kWave); ++k) t += sh[q][k];
     tot[q] = t;
   }
-  const double rho1 = ks[kRho1], s1 = ks[kS1];
-  const double beta = tot[0], gamma = tot[1], a2 = tot[2];
-  if (!(rho1 > 0.0)) {
-    ks[kA1] = 0.0;
-    ks[kS2] = 0.0;
-    return;
-  }
-  const double rho2 = beta - gamma * gamma / rho1;
-  ks[kGamma] = gamma;
-  ks[kRho2] = rho2;
-  if (!(rho2 > 0.0)) {
-    ks[kA1] = s1;
-    ks[kS2] = 0.0;
-  } else {
-    const double s2 = a2 / rho2;
-    ks[kS2] = s2;
-    ks[kA1] = s1 - s2 * (gamma / rho1);
-  }
+  double a1, s2;
+  second_step(ks, tot[0], tot[1], tot[2], &a1, &s2);
+  ks[kA1] = a1;
+  ks[kS2] = s2;
 }
 
 // ---- the deepest flexible-CG step in one block ----
 // For the level t just above the coarsest (pre = post = 1), the K-cycle's two
 // flexible-CG iterations, each with its cycle (down step, A_L^-1, up step),
-// the products, the dot products and the prolongation of x = a1 c1 + s2 c2
-// into the level above, in one 1024-thread block with the level's vectors in
-// LDS. Same arithmetic as the multi-kernel form; the dot products are summed
-// in a fixed order of their own.
-constexpr int kKTailMax = 1536;   // largest level t in LDS (five vectors)
-constexpr int kKTailCoarse = 128; // coarsest size for the one-pass A_L^-1 product
+// the products and the dot products, in one 1024-thread block with the level's
+// vectors in LDS. The prolongation of x = a1 c1 + s2 c2 is left to the post-sweep
+// of the level above (k_kpost), or done here where that level has its own (one
+// block's 8 rows per thread took 4 us). Same arithmetic as the multi-kernel form; the dot
+// products are summed in a fixed order of their own. A chain of latencies: what
+// both cycles read is loaded at the start (24.2 -> 20 us at 1000 rows in FP64).
+// Against the multi-kernel form a level of 1331 rows over 166 took 974 -> 916 us
+// a solve of 22^3, one of 1728 over 216 the same: larger ones gain nothing.
+constexpr int kKTailMax = 2048;   // largest level t in LDS (five vectors)
+constexpr int kKTailCoarse = 256; // largest coarsest size
 
-// sum over the block; every thread gets the same value (fixed order)
-__device__ __forceinline__ double block_sum_all(double v, double *red) {
+// N sums over the block at once; every thread gets them (fixed order)
+template <int N>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*red)[1024 / kWave]) {
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   const int nw = blockDim.x / kWave;
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_down(v, o, kWave);
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    for (int o = kWave / 2; o > 0; o >>= 1) v[q] += __shfl_down(v[q], o, kWave);
   __syncthreads();
-  if (lane == 0) red[wid] = v;
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < N; ++q) red[q][wid] = v[q];
   __syncthreads();
-  double t = red[0];
-  for (int k = 1; k < nw; ++k) t += red[k];
-  return t;
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    v[q] = red[q][0];
+    for (int k = 1; k < nw; ++k) v[q] += red[q][k];
+  }
 }
 
 // One SELL row of the level held in registers (w <= kRowBatch entries):
@@ -1552,59 +1699,79 @@ struct RegRow {
   }
 };
 
+// What a thread uses in both cycles, loaded once at the start of the launch:
+// the segment of its coarse position, its entries of its row of A_L^-1 and,
+// with REG, its row of level t.
+template <typename TV>
+struct KTailRegs {
+  RegRow<TV> rr;
+  TV mi = 0, p = 0;
+  int32_t agg = 0, sb = 0, se = 0;
+  double a[kTailRow];  // (n_L <= kTailRow kCoarseSplit)
+};
+
 // one K-cycle on level t (iv -> out; the coarse correction is A_L^-1)
 template <typename TV, bool REG>
 __device__ void ktail_cycle(int32_t nt, const int32_t *__restrict__ sptr,
                             const int32_t *__restrict__ col, const TV *__restrict__ sval,
                             const TV *__restrict__ val, const TV *__restrict__ minv,
-                            const TV *__restrict__ pp, const int32_t *__restrict__ seg,
-                            const int32_t *__restrict__ aggp, int32_t nL,
+                            const TV *__restrict__ pp, const int32_t *__restrict__ aggp, int32_t nL,
                             const double *__restrict__ Ainv, const TV *iv, TV *zs, TV *ys,
-                            TV *out, double *rl, double *zl, const RegRow<TV> &rr) {
+                            TV *out, double *rl, double *zl,
+                            const KTailRegs<TV> &T) {
   const int32_t tid = threadIdx.x, nth = blockDim.x;
-  for (int32_t k = tid; k < nt; k += nth) zs[k] = iv[k] * minv[k];
+  for (int32_t k = tid; k < nt; k += nth) zs[k] = iv[k] * (REG ? T.mi : minv[k]);
   for (int32_t k = tid; k < nt; k += nth) {
     TV acc;
     if (REG) {
-      acc = rr.template dot<true>(iv);
+      acc = T.rr.template dot<true>(iv);
     } else {
       const int32_t s = k / kSlice, base = sptr[s] + k % kSlice,
                     w = (sptr[s + 1] - sptr[s]) / kSlice;
       acc = sell_dot(col, sval, base, w, [&](int32_t c) { return iv[c]; });
     }
-    ys[k] = pp[k] * (iv[k] - acc);
+    ys[k] = (REG ? T.p : pp[k]) * (iv[k] - acc);
   }
   __syncthreads();
-  for (int32_t J = tid; J < nL; J += nth) {
+  if (tid < nL) {
     TV a = 0;
-    for (int32_t m = seg[J]; m < seg[J + 1]; ++m) a += ys[m];
-    rl[J] = (double)a;
-  }
-  __syncthreads();
-  {
-    const int32_t part = tid % kCoarseSplit, i = tid / kCoarseSplit;
-    double a = 0.0;
-    if (i < nL) {
-      const double *row = Ainv + (int64_t)i * nL;
 #pragma unroll 8
-      for (int32_t k = part; k < nL; k += kCoarseSplit) a += row[k] * rl[k];
-    }
-    for (int o = kCoarseSplit / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kCoarseSplit);
-    if (i < nL && part == 0) zl[i] = a;
+    for (int32_t m = T.sb; m < T.se; ++m) a += ys[m];
+    rl[tid] = (double)a;
   }
   __syncthreads();
-  for (int32_t k = tid; k < nt; k += nth) zs[k] += pp[k] * (TV)zl[aggp[k]];
+  const int32_t part = tid % kCoarseSplit, irow = tid / kCoarseSplit;
+  if (nL <= kTailRow * kCoarseSplit) {
+    double a = 0.0;  // (entries past n_L are 0 in both factors)
+#pragma unroll
+    for (int m = 0; m < kTailRow; ++m) a += T.a[m] * rl[part + m * kCoarseSplit];
+    for (int o = kCoarseSplit / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kCoarseSplit);
+    if (irow < nL && part == 0) zl[irow] = a;
+  } else {
+    for (int32_t i = irow; i - irow < nL; i += nth / kCoarseSplit) {
+      double a = 0.0;
+      if (i < nL) {
+        const double *row = Ainv + (int64_t)i * nL;
+#pragma unroll 8
+        for (int32_t k = part; k < nL; k += kCoarseSplit) a += row[k] * rl[k];
+      }
+      for (int o = kCoarseSplit / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kCoarseSplit);
+      if (i < nL && part == 0) zl[i] = a;
+    }
+  }
+  __syncthreads();
+  for (int32_t k = tid; k < nt; k += nth) zs[k] += (REG ? T.p : pp[k]) * (TV)zl[REG ? T.agg : aggp[k]];
   __syncthreads();
   for (int32_t k = tid; k < nt; k += nth) {
     TV acc;
     if (REG) {
-      acc = rr.template dot<false>(zs);
+      acc = T.rr.template dot<false>(zs);
     } else {
       const int32_t s = k / kSlice, base = sptr[s] + k % kSlice,
                     w = (sptr[s + 1] - sptr[s]) / kSlice;
       acc = sell_dot(col, val, base, w, [&](int32_t c) { return zs[c]; });
     }
-    out[k] = zs[k] + (iv[k] - acc) * minv[k];
+    out[k] = zs[k] + (iv[k] - acc) * (REG ? T.mi : minv[k]);
   }
   __syncthreads();
 }
@@ -1616,23 +1783,39 @@ __global__ void __launch_bounds__(1024) k_ktail(
     const TV *__restrict__ pp, const int32_t *__restrict__ seg, const int32_t *__restrict__ aggp,
     int32_t nL, const double *__restrict__ Ainv, const TV *__restrict__ b, int32_t nf,
     const int32_t *__restrict__ aggp_f, const TV *__restrict__ pp_f, TV *__restrict__ zf,
-    double *__restrict__ ks, const int32_t *__restrict__ done) {
+    TV *__restrict__ c1, TV *__restrict__ c2, double *__restrict__ ks,
+    const int32_t *__restrict__ done) {
   __shared__ TV IV[kKTailMax], ZS[kKTailMax], YS[kKTailMax], C1[kKTailMax], C2[kKTailMax];
-  __shared__ double rl[kKTailCoarse], zl[kKTailCoarse], red[1024 / kWave];
+  __shared__ double rl[kKTailCoarse], zl[kKTailCoarse], red[3][1024 / kWave];
   if (*done) return;
   const int32_t tid = threadIdx.x, nth = blockDim.x;
   constexpr int kRows = kKTailMax / 1024 + 1;  // rows per thread
   // REG: one row per thread (nt <= blockDim.x, rows of at most kRowBatch
   // entries), held in registers for every product of the step
-  RegRow<TV> rr;
-  if (REG && tid < nt) rr.load(sptr, col, val, sval, tid);
+  KTailRegs<TV> T;
+  if (REG && tid < nt) {
+    T.rr.load(sptr, col, val, sval, tid);
+    T.mi = minv[tid];
+    T.p = pp[tid];
+    T.agg = aggp[tid];
+  }
+  if (tid < nL) {
+    T.sb = seg[tid];
+    T.se = seg[tid + 1];
+  }
+  if (tid < kKTailCoarse) rl[tid] = 0.0;
+#pragma unroll
+  for (int m = 0; m < kTailRow; ++m) {
+    const int32_t i = tid / kCoarseSplit, k = tid % kCoarseSplit + m * kCoarseSplit;
+    T.a[m] = nL <= kTailRow * kCoarseSplit && i < nL && k < nL ? Ainv[(int64_t)i * nL + k] : 0.0;
+  }
   for (int32_t k = tid; k < nt; k += nth) IV[k] = b[k];
   __syncthreads();
-  ktail_cycle<TV, REG>(nt, sptr, col, sval, val, minv, pp, seg, aggp, nL, Ainv, IV, ZS, YS, C1,
-                       rl, zl, rr);
+  ktail_cycle<TV, REG>(nt, sptr, col, sval, val, minv, pp, aggp, nL, Ainv, IV, ZS, YS, C1, rl, zl,
+                       T);
   // v1 = A c1, rho1 = (c1, v1), s1 = (c1, b) / rho1
   TV v1[kRows];
-  double d0 = 0.0, d1 = 0.0;
+  double d[2] = {0.0, 0.0};
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
     const int32_t k = tid + u * nth;
@@ -1640,19 +1823,19 @@ __global__ void __launch_bounds__(1024) k_ktail(
     if (k < nt) {
       TV acc;
       if (REG) {
-        acc = rr.template dot<false>(C1);
+        acc = T.rr.template dot<false>(C1);
       } else {
         const int32_t s = k / kSlice, base = sptr[s] + k % kSlice,
                       w = (sptr[s + 1] - sptr[s]) / kSlice;
         acc = sell_dot(col, val, base, w, [&](int32_t c) { return C1[c]; });
       }
       v1[u] = acc;
-      d0 += (double)C1[k] * (double)acc;
-      d1 += (double)C1[k] * (double)IV[k];
+      d[0] += (double)C1[k] * (double)acc;
+      d[1] += (double)C1[k] * (double)IV[k];
     }
   }
-  const double rho1 = block_sum_all(d0, red);
-  const double cb = block_sum_all(d1, red);
+  block_sums(d, red);
+  const double rho1 = d[0], cb = d[1];
   const double s1 = rho1 > 0.0 ? cb / rho1 : 0.0;
   // r1 = b - s1 v1 (in IV)
   __syncthreads();
@@ -1662,31 +1845,30 @@ __global__ void __launch_bounds__(1024) k_ktail(
     if (k < nt) IV[k] = IV[k] - (TV)s1 * v1[u];
   }
   __syncthreads();
-  ktail_cycle<TV, REG>(nt, sptr, col, sval, val, minv, pp, seg, aggp, nL, Ainv, IV, ZS, YS, C2,
-                       rl, zl, rr);
+  ktail_cycle<TV, REG>(nt, sptr, col, sval, val, minv, pp, aggp, nL, Ainv, IV, ZS, YS, C2, rl, zl,
+                       T);
   // v2 = A c2; (c2, v2), gamma = (c2, v1), (c2, r1)
-  double e0 = 0.0, e1 = 0.0, e2 = 0.0;
+  double e[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
     const int32_t k = tid + u * nth;
     if (k < nt) {
       TV acc;
       if (REG) {
-        acc = rr.template dot<false>(C2);
+        acc = T.rr.template dot<false>(C2);
       } else {
         const int32_t s = k / kSlice, base = sptr[s] + k % kSlice,
                       w = (sptr[s + 1] - sptr[s]) / kSlice;
         acc = sell_dot(col, val, base, w, [&](int32_t c) { return C2[c]; });
       }
       const double c2 = (double)C2[k];
-      e0 += c2 * (double)acc;
-      e1 += c2 * (double)v1[u];
-      e2 += c2 * (double)IV[k];
+      e[0] += c2 * (double)acc;
+      e[1] += c2 * (double)v1[u];
+      e[2] += c2 * (double)IV[k];
     }
   }
-  const double beta = block_sum_all(e0, red);
-  const double gamma = block_sum_all(e1, red);
-  const double a2 = block_sum_all(e2, red);
+  block_sums(e, red);
+  const double beta = e[0], gamma = e[1], a2 = e[2];
   double a1 = 0.0, s2 = 0.0;
   if (rho1 > 0.0) {
     const double rho2 = beta - gamma * gamma / rho1;
@@ -1703,9 +1885,30 @@ __global__ void __launch_bounds__(1024) k_ktail(
     ks[kA1] = a1;
     ks[kS2] = s2;
   }
+  if (c1) {  // left to the kernel that smooths the level above
+    for (int32_t k = tid; k < nt; k += nth) {
+      c1[k] = C1[k];
+      c2[k] = C2[k];
+    }
+    return;
+  }
   // z_f += P x, x = a1 c1 + s2 c2
   const TV ta1 = (TV)a1, ts2 = (TV)s2;
-  for (int32_t k = tid; k < nf; k += nth) {
+  constexpr int kU = 4;  // positions per thread in flight
+  int32_t k = tid;
+  for (; k + (kU - 1) * nth < nf; k += kU * nth) {
+    int32_t J[kU];
+    TV p[kU], z[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      J[u] = aggp_f[k + u * nth];
+      p[u] = pp_f[k + u * nth];
+      z[u] = zf[k + u * nth];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) zf[k + u * nth] = z[u] + p[u] * (ta1 * C1[J[u]] + ts2 * C2[J[u]]);
+  }
+  for (; k < nf; k += nth) {
     const int32_t J = aggp_f[k];
     zf[k] += pp_f[k] * (ta1 * C1[J] + ts2 * C2[J]);
   }
@@ -1833,63 +2036,70 @@ inline int32_t coarse_pcg_threads(int32_t nL) {
   return t < kWave ? kWave : (t > 1024 ? 1024 : t);
 }
 
-// r1 = b - s1 v1, with s1 = (c1, b) / (c1, v1) from the first step's partials
+// r1 = b - s1 v1, with s1 from the first step's partials
 template <typename TV>
-__global__ void __launch_bounds__(kBlock) k_kresid(
-    int32_t n, const TV *__restrict__ b, const TV *__restrict__ v1,
-    const double *__restrict__ partials, int32_t nparts, double *__restrict__ ks,
-    TV *__restrict__ r1, const int32_t *__restrict__ done) {
+__global__ void __launch_bounds__(kBlock) k_kresid(int32_t n, KSub<TV> sub, TV *__restrict__ r1,
+                                                   const int32_t *__restrict__ done) {
   if (*done) return;
-  // rho1 = (c1, v1) and (c1, b) from the block partials, summed by every
-  // block in the same order (so all blocks hold the same s1); block 0 keeps
-  // them for the second step and the prolongation
-  __shared__ double sh[2][kBlock / kWave];
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  for (int q = 0; q < 2; ++q) {
-    const double *src = partials + (int64_t)q * kMaxParts;
-    double a = 0.0;
-    for (int32_t b0 = threadIdx.x; b0 < nparts; b0 += 16 * kBlock) {
-      double v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int32_t bb = b0 + u * kBlock;
-        v[u] = bb < nparts ? src[bb] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (b0 + u * kBlock < nparts) a += v[u];
-    }
-    for (int o = kWave / 2; o > 0; o >>= 1) a += __shfl_down(a, o, kWave);
-    if (lane == 0) sh[q][wid] = a;
-  }
-  __syncthreads();
-  double rho1 = sh[0][0], cb = sh[1][0];
-  for (int k = 1; k < kBlock / kWave; ++k) {
-    rho1 += sh[0][k];
-    cb += sh[1][k];
-  }
-  const double s1 = rho1 > 0.0 ? cb / rho1 : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ks[kRho1] = rho1;
-    ks[kS1] = s1;
-  }
+  const TV s1 = (TV)first_step(sub);
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) r1[i] = b[i] - (TV)s1 * v1[i];
+  if (i < n) r1[i] = sub.b[i] - s1 * sub.v1[i];
 }
 
 // z_f += P x with x = a1 c1 + s2 c2 formed per coarse position
 template <typename TV>
-__global__ void k_kprolong(int32_t nf, const int32_t *__restrict__ aggp,
-                           const TV *__restrict__ pp, const TV *__restrict__ c1,
-                           const TV *__restrict__ c2, const double *__restrict__ ks,
-                           TV *__restrict__ zf, const int32_t *__restrict__ done) {
+__global__ void __launch_bounds__(kBlock) k_kprolong(
+    int32_t nf, const int32_t *__restrict__ aggp, const TV *__restrict__ pp,
+    const TV *__restrict__ c1, const TV *__restrict__ c2, const double *__restrict__ partials,
+    int32_t nparts, const double *__restrict__ ks, TV *__restrict__ zf,
+    const int32_t *__restrict__ done) {
   if (*done) return;
-  const TV a1 = (TV)ks[kA1], s2 = (TV)ks[kS2];
   const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+  int32_t J = 0;
+  TV p = 0, z = 0;
   if (k < nf) {
-    const int32_t J = aggp[k];
-    zf[k] += pp[k] * (a1 * c1[J] + s2 * c2[J]);
+    J = aggp[k];
+    p = pp[k];
+    z = zf[k];
   }
+  double a1, s2;
+  step_scalars(partials, nparts, ks, &a1, &s2);
+  if (k < nf) zf[k] = z + p * ((TV)a1 * c1[J] + (TV)s2 * c2[J]);
+}
+
+// The up step of the K-cycle in one kernel: y = z' + M^-1 (r - A z') with z' =
+// z + P (a1 c1 + s2 c2) formed at each entry of z that is gathered (k_post after
+// k_kprolong, without the launch between them)
+template <typename TV, typename TR, typename TO, bool DOT>
+__global__ void __launch_bounds__(kBlock) k_kpost(
+    int32_t n, int32_t chunk, const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
+    const TV *__restrict__ val, const TV *__restrict__ minv, const TR *__restrict__ r,
+    const TV *__restrict__ z, const int32_t *__restrict__ aggp, const TV *__restrict__ pp,
+    const TV *__restrict__ c1, const TV *__restrict__ c2, double *__restrict__ partials,
+    int32_t nparts, const double *__restrict__ ks, TO *__restrict__ y,
+    const int32_t *__restrict__ done, const double *__restrict__ dv) {
+  if (*done) return;
+  double a1, s2;
+  step_scalars(partials, DOT ? 0 : nparts, ks, &a1, &s2);  // (with DOT they are written below)
+  const TV ta1 = (TV)a1, ts2 = (TV)s2;
+  auto zx = [&](int32_t k) {
+    const int32_t J = aggp[k];
+    return z[k] + pp[k] * (ta1 * c1[J] + ts2 * c2[J]);
+  };
+  int32_t rb, re;
+  rows_of_block(n, chunk, &rb, &re);
+  double d[1] = {0.0};
+  for (int32_t row = rb + threadIdx.x; row < re; row += kBlock) {
+    const TR rr = r[row];
+    const TV mr = minv[row], zr = zx(row);
+    int32_t base, w;
+    sell_row(sptr, row, &base, &w);
+    const TV acc = sell_dot_t<TV, TV>(col, val, base, w, zx);
+    const TO yo = (TO)(zr + ((TV)rr - acc) * mr);
+    y[row] = yo;
+    if (DOT) d[0] += (dv ? dv[row] : (double)rr) * (double)yo;
+  }
+  if (DOT) block_partial<1>(d, partials);
 }
 
 // ---------------------------------------------------------------------------
@@ -2374,18 +2584,33 @@ void vcycle_t(amg_hierarchy *h, const double *r0, double *z0, bool dot, const do
 // ---- K-cycle (Section 3.1) ----
 
 template <typename TV>
-void fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done);
+int32_t fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done);
 
 // K-cycle on level l < L. in: the level's right-hand side (level 0: the FP64
 // CG residual); out: the result (level 0: FP64). With a dot partner dv the
-// last post-sweep also writes the block partials of (dv, out).
+// last post-sweep also writes the block partials of (dv, out). zdown: the level's
+// z where its down step has been done.
 template <typename TV, typename TR, typename TO>
 void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *dv,
-              const int32_t *done) {
+              const int32_t *done, TV *zdown = nullptr) {
   hipStream_t s = h->stream;
   const int32_t L = (int32_t)h->lv.size() - 1;
   Level &F = h->lv[l];
-  TV *z = launch_down<TV, TR>(h, l, in, done);
+  TV *z = zdown ? zdown : launch_down<TV, TR>(h, l, in, done);
+  const Geom g = geom(F.n);
+  const bool a32 = reads32<TV>(F, l);
+  double *ks = h->kscal + (int64_t)(l + 1) * kKScal;
+  // the prolongation in the one post-sweep
+  const bool up = l > 0 && h->params.post == 1 && F.n <= kUpRows;
+  auto kpost = [&](int32_t nparts) {
+    const Level &C = h->lv[l + 1];
+    if constexpr (std::is_same<TR, TV>::value && std::is_same<TO, TV>::value)
+      if (!dv) {
+        k_kpost<TV, TR, TO, false><<<g.grid, kBlock, 0, s>>>(
+            F.n, g.chunk, F.S.sptr, F.S.col, vals<TV>(F), minv<TV>(F), in, z, F.aggp, ppv<TV>(F),
+            (const TV *)C.c1, (const TV *)C.c2, h->partials, nparts, ks, out, done, nullptr);
+      }
+  };
   if (l + 1 == L) {
     const int32_t nL = h->C.n;
     if (coarse_is_pcg(h))
@@ -2400,20 +2625,27 @@ void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *
     auto kt = T.n <= 1024 && T.S.max_width <= kRowBatch ? k_ktail<TV, true> : k_ktail<TV, false>;
     kt<<<1, 1024, 0, s>>>(T.n, T.S.sptr, T.S.col, svals<TV>(T), vals<TV>(T), minv<TV>(T),
                           ppv<TV>(T), T.seg, T.aggp, h->C.n, h->C.Ainv, (const TV *)T.r, F.n,
-                          F.aggp, ppv<TV>(F), z, h->kscal + (int64_t)(l + 1) * kKScal, done);
+                          F.aggp, ppv<TV>(F), z, up ? (TV *)T.c1 : nullptr,
+                          up ? (TV *)T.c2 : nullptr, ks, done);
+    if (up) {
+      kpost(0);
+      return;
+    }
   } else {
     const Level &C = h->lv[l + 1];
-    fcg2_t<TV>(h, l + 1, done);
+    const int32_t nparts = fcg2_t<TV>(h, l + 1, done);
+    if (up) {
+      kpost(nparts);
+      return;
+    }
     k_kprolong<TV><<<grid1(F.n), kBlock, 0, s>>>(F.n, F.aggp, ppv<TV>(F), (const TV *)C.c1,
-                                                 (const TV *)C.c2,
-                                                 h->kscal + (int64_t)(l + 1) * kKScal, z, done);
+                                                 (const TV *)C.c2, h->partials, nparts, ks, z,
+                                                 done);
   }
   // post-smoothing: post - 1 sweeps alternating two level buffers, the last
   // into out
   TV *tmp = (TV *)F.y;
   if (tmp == z) tmp = (TV *)F.z;
-  const Geom g = geom(F.n);
-  const bool a32 = reads32<TV>(F, l);
   for (int32_t k = 1; k < h->params.post; ++k) {
     if (a32)
       k_post<TV, TR, TV, false, float><<<g.grid, kBlock, 0, s>>>(
@@ -2442,10 +2674,11 @@ void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *
 
 // Two flexible-CG iterations on level m (0 < m < L) for the right-hand side
 // the level above restricted into lv[m].r, from zero; the result stays as
-// x = a1 c1 + s2 c2 (vectors c1, c2 of the level, scalars in its kscal slot)
-// for the prolongation to combine.
+// x = a1 c1 + s2 c2 (vectors c1, c2 of the level) for the prolongation to
+// combine: scalars in the level's kscal slot, or, where a number of partials
+// is returned, to be summed from them.
 template <typename TV>
-void fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done) {
+int32_t fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done) {
   hipStream_t s = h->stream;
   Level &M = h->lv[m];
   const int32_t n = M.n;
@@ -2456,14 +2689,26 @@ void fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done) {
   k_spmv_dots<TV, 2><<<g.grid, kBlock, 0, s>>>(n, g.chunk, M.S.sptr, M.S.col, vals<TV>(M),
                                                (const TV *)M.c1, (TV *)M.v1, b, nullptr,
                                                h->partials, done);
-  k_kresid<TV><<<grid1(n), kBlock, 0, s>>>(n, b, (const TV *)M.v1, h->partials, g.grid, ks,
-                                           (TV *)M.r1, done);
-  kcycle_t<TV, TV, TV>(h, m, (const TV *)M.r1, (TV *)M.c2, nullptr, done);
+  const KSub<TV> sub{b, (const TV *)M.v1, h->partials, g.grid, ks};
+  TV *z1 = nullptr;  // of the second cycle, where its down step is done here
+  if (h->params.pre == 1 && n <= kUpRows && !M.hseg.ok()) {
+    const Level &C = h->lv[m + 1];
+    const int32_t G = coarse_per_block(h);
+    z1 = (TV *)M.z;
+    k_kdown<TV><<<ceil_div(C.n, G), kBlock, 0, s>>>(C.n, G, M.seg, M.S.sptr, M.S.col, svals<TV>(M),
+                                                    minv<TV>(M), ppv<TV>(M), sub, (TV *)M.r1, z1,
+                                                    (TV *)C.r, done);
+  } else {
+    k_kresid<TV><<<grid1(n), kBlock, 0, s>>>(n, sub, (TV *)M.r1, done);
+  }
+  kcycle_t<TV, TV, TV>(h, m, (const TV *)M.r1, (TV *)M.c2, nullptr, done, z1);
   k_spmv_dots<TV, 3><<<g.grid, kBlock, 0, s>>>(n, g.chunk, M.S.sptr, M.S.col, vals<TV>(M),
                                                (const TV *)M.c2, (TV *)M.v2,
                                                (const TV *)M.v1, (const TV *)M.r1,
                                                h->partials, done);
+  if (g.grid <= kFoldParts) return g.grid;
   k_kfin<<<1, 1024, 0, s>>>(g.grid, h->partials, ks, done);
+  return 0;
 }
 
 // z0 = K r0 on the aggregate-major level-0 vectors (with dv: the partials of
