@@ -957,6 +957,128 @@ __global__ void __launch_bounds__(kBlock) k_post_prolong(
               [&](int32_t a) { return sh[a - J0]; });
 }
 
+// ---- levels of wide rows ----
+//
+// The coarse levels of an irregular matrix have few rows, some of them of
+// hundreds of entries: with a thread per row a kernel takes what one thread's
+// chain of gathers takes. Here a block takes kWideRows rows, its 256 threads load
+// kWideStep entries of each and the gathered values into LDS, a step ahead of
+// their use, and a lane per row adds up the products: the same sums in the same
+// order as sell_dot. A random graph of 100003 rows and degree 9 (levels of 14101
+// rows of 52 entries and of 1908 of 331): 31.9 -> 8 us a kernel, 3.53 -> 2.04 ms a
+// solve; one of 50000 and degree 4.5, whose last 25 levels hold a row of all 1200
+// columns: 45.3 -> 15.6 ms. 64 entries a step: 15.9. (32 entries in flight per
+// thread instead, still a thread per row: 7.3 ms for the 3.53.)
+// Where the level above the coarsest is of that kind, its kernels in this form and
+// the coarsest product also beat k_tail, one block for all its rows: 2.04 -> 1.73 ms;
+// 10000 rows, degree 9: 1.18 -> 0.69 ms.
+// kWideMean: stored entries per row, padding included, from which a level takes it
+// (16, 24 and 32 are the same on these; stencils' levels store fewer than 24).
+constexpr int kWideMean = 32;
+constexpr int kWideRows = 16;
+constexpr int kWideStep = 128;
+constexpr int kWideLanes = kBlock / kWideRows;
+
+// the product of row f0 + threadIdx.x % kWideRows (rows below f1) with x: the
+// result is threads 0 .. kWideRows - 1's
+template <typename TV, typename X>
+__device__ __forceinline__ TV wide_dot(const int32_t *__restrict__ sptr,
+                                       const int32_t *__restrict__ col,
+                                       const TV *__restrict__ val, int32_t f0, int32_t f1, X x) {
+  constexpr int kPer = kWideStep / kWideLanes;
+  __shared__ TV sv[2][kWideStep][kWideRows], sg[2][kWideStep][kWideRows];
+  const int32_t rl = (int32_t)threadIdx.x % kWideRows, el = (int32_t)threadIdx.x / kWideRows;
+  const int32_t row = f0 + rl;
+  int32_t base = 0, w = 0, b0, w0, w1;
+  if (row < f1) sell_row(sptr, row, &base, &w);
+  sell_row(sptr, f0, &b0, &w0);  // (the rows are in at most two slices)
+  sell_row(sptr, f1 - 1, &b0, &w1);
+  const int32_t steps = (max(w0, w1) + kWideStep - 1) / kWideStep;
+  int32_t c[kPer];
+  TV v[kPer], g[kPer];
+  auto entries = [&](int32_t k0) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int32_t e = k0 + el + u * kWideLanes;
+      c[u] = -1;
+      v[u] = 0;
+      if (e < w) {
+        c[u] = ld_stream(&col[base + e * kSlice]);
+        v[u] = ld_stream(&val[base + e * kSlice]);
+      }
+    }
+  };
+  auto gather = [&](int32_t b) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) g[u] = c[u] >= 0 ? x(c[u]) : TV(0);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      sv[b][el + u * kWideLanes][rl] = v[u];
+      sg[b][el + u * kWideLanes][rl] = g[u];
+    }
+  };
+  TV acc = 0;
+  entries(0);
+  gather(0);
+  for (int32_t st = 0; st < steps; ++st) {
+    __syncthreads();  // step st is in LDS, and the one before it has been added
+    const int32_t b = st & 1, k0 = st * kWideStep;
+    if (st + 1 < steps) entries(k0 + kWideStep);
+    if (threadIdx.x < kWideRows) {
+      const int32_t m = min(w - k0, kWideStep);
+#pragma unroll 8
+      for (int32_t e = 0; e < m; ++e) acc += sv[b][e][rl] * sg[b][e][rl];
+    }
+    if (st + 1 < steps) gather(b ^ 1);
+  }
+  return acc;
+}
+
+// k_pre_restrict (one sweep, A M^-1) and k_post_prolong in that form; G coarse
+// positions hold at most kWideRows rows
+template <typename TV>
+__global__ void __launch_bounds__(kBlock) k_pre_restrict_wide(
+    int32_t nc, int32_t G, const int32_t *__restrict__ seg, const int32_t *__restrict__ sptr,
+    const int32_t *__restrict__ col, const TV *__restrict__ val, const TV *__restrict__ minv,
+    const TV *__restrict__ pp, const TV *__restrict__ r, TV *__restrict__ z, TV *__restrict__ rc,
+    const int32_t *__restrict__ done) {
+  __shared__ TV sh[kWideRows];
+  if (*done) return;
+  const int32_t J0 = blockIdx.x * G, J1 = min(nc, J0 + G);
+  const int32_t f0 = seg[J0], f1 = seg[J1];
+  const TV acc = wide_dot(sptr, col, val, f0, f1, [&](int32_t c) { return r[c]; });
+  const int32_t row = f0 + (int32_t)threadIdx.x;
+  if (threadIdx.x < kWideRows && row < f1) {
+    const TV ri = r[row];
+    z[row] = ri * minv[row];
+    sh[threadIdx.x] = pp[row] * (ri - acc);
+  }
+  __syncthreads();
+  const int32_t J = J0 + (int32_t)threadIdx.x;
+  if (J < J1) {
+    TV s = 0;
+    for (int32_t m = seg[J]; m < seg[J + 1]; ++m) s += sh[m - f0];
+    rc[J] = s;
+  }
+}
+
+template <typename TV>
+__global__ void __launch_bounds__(kBlock) k_post_prolong_wide(
+    int32_t nc, const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
+    const TV *__restrict__ val, const TV *__restrict__ minv, const TV *__restrict__ rcv,
+    const TV *__restrict__ zc, const int32_t *__restrict__ seg, const int32_t *__restrict__ aggp,
+    const TV *__restrict__ pp, TV *__restrict__ zf, const int32_t *__restrict__ done) {
+  __shared__ TV sh[kWideRows];
+  if (*done) return;
+  const int32_t J0 = blockIdx.x * kWideRows, J1 = min(nc, J0 + kWideRows);
+  const TV acc = wide_dot(sptr, col, val, J0, J1, [&](int32_t c) { return zc[c]; });
+  const int32_t J = J0 + (int32_t)threadIdx.x;
+  if (J < J1) sh[threadIdx.x] = zc[J] + (rcv[J] - acc) * minv[J];
+  __syncthreads();
+  prolong_add(seg[J0], seg[J1], (int32_t)threadIdx.x, kBlock, aggp, pp, zf,
+              [&](int32_t c) { return sh[c - J0]; });
+}
+
 // Coarsest level with prolongation: z_L = A_L^-1 r_L, then z_f += P z_L over
 // all fine positions; one block of 1024 threads. Eight consecutive threads
 // share a row (coalesced 64-byte pieces of it), each summing every eighth
@@ -2190,6 +2312,11 @@ int32_t coarse_per_block(const amg_hierarchy *h) {
 // held more registers than they hid latency)
 int32_t staged_down_G(const amg_hierarchy *h) { return coarse_per_block(h); }
 
+// whether a level's products take a block per kWideRows rows
+bool wide_rows(const amg_hierarchy *h, const Level &L) {
+  return h->max_seg <= kWideRows && L.S.nnz_padded >= (int64_t)kWideMean * L.n;
+}
+
 // Down step of level F into C: LDS-staged gathers where the level has tiles of
 // that geometry, else down_rows(n) fine rows per thread gathering from memory.
 template <typename TV, typename TR, int MODE, typename TA, bool FIN>
@@ -2206,6 +2333,13 @@ void pre_restrict_fin(const amg_hierarchy *h, const Level &F, const Level &C, co
              pp, r, z, rc, done, fin);
     return;
   }
+  if constexpr (MODE == kPreScaled && std::is_same<TR, TV>::value && !FIN)
+    if (wide_rows(h, F)) {
+      const int32_t Gw = kWideRows / h->max_seg;
+      launch_k(h, k_pre_restrict_wide<TV>, dim3(ceil_div(C.n, Gw)), dim3(kBlock), 0u, s, C.n, Gw,
+               F.seg, F.S.sptr, F.S.col, val, mv, pp, r, z, rc, done);
+      return;
+    }
   const int R = down_rows(F.n);
   const int32_t G = coarse_per_block(h) * R;
   const int32_t grid = ceil_div(C.n, G);
@@ -2360,9 +2494,14 @@ void launch_up(amg_hierarchy *h, int32_t c, TV *zc, TV *zf, const int32_t *done)
                                                        zc, tmp, nullptr, done);
     std::swap(zc, tmp);
   }
-  k_post_prolong<TV><<<grid1(C.n), kBlock, 0, s>>>(C.n, C.S.sptr, C.S.col, vals<TV>(C),
-                                                   minv<TV>(C), (const TV *)C.r, zc, F.seg,
-                                                   F.aggp, ppv<TV>(F), zf, done);
+  if (wide_rows(h, C))
+    k_post_prolong_wide<TV><<<ceil_div(C.n, kWideRows), kBlock, 0, s>>>(
+        C.n, C.S.sptr, C.S.col, vals<TV>(C), minv<TV>(C), (const TV *)C.r, zc, F.seg, F.aggp,
+        ppv<TV>(F), zf, done);
+  else
+    k_post_prolong<TV><<<grid1(C.n), kBlock, 0, s>>>(C.n, C.S.sptr, C.S.col, vals<TV>(C),
+                                                     minv<TV>(C), (const TV *)C.r, zc, F.seg,
+                                                     F.aggp, ppv<TV>(F), zf, done);
 }
 
 inline bool coarse_is_pcg(const amg_hierarchy *h) {
@@ -2553,7 +2692,8 @@ void vcycle_t(amg_hierarchy *h, const double *r0, double *z0, bool dot, const do
   }
   std::vector<TV *> zb(L);
   const bool tail = L >= 2 && h->params.pre == 1 && h->params.post == 1 &&
-                    h->lv[L - 1].n <= kTailMax && h->C.n <= kTailCoarseMax && !coarse_is_pcg(h);
+                    h->lv[L - 1].n <= kTailMax && h->C.n <= kTailCoarseMax && !coarse_is_pcg(h) &&
+                    !wide_rows(h, h->lv[L - 1]);
   const int32_t down_end = tail ? L - 1 : L;  // levels [0, down_end) take the down step
   arm_probe(h, 0);
   zb[0] = launch_down<TV, double>(h, 0, r0, done);
