@@ -965,10 +965,10 @@ __global__ void __launch_bounds__(kBlock) k_post_prolong(
 // kWideStep entries of each and the gathered values into LDS, a step ahead of
 // their use, and a lane per row adds up the products: the same sums in the same
 // order as sell_dot. A random graph of 100003 rows and degree 9 (levels of 14101
-// rows of 52 entries and of 1908 of 331): 31.9 -> 8 us a kernel, 3.53 -> 2.04 ms a
-// solve; one of 50000 and degree 4.5, whose last 25 levels hold a row of all 1200
-// columns: 45.3 -> 15.6 ms. 64 entries a step: 15.9. (32 entries in flight per
-// thread instead, still a thread per row: 7.3 ms for the 3.53.)
+// rows of 52 entries and of 1908 of 331): 3.53 -> 2.04 ms a solve; one of 50000 and
+// degree 4.5, whose last 25 levels hold a row of all 1200 columns: 43 -> 12 us a
+// kernel, 45.3 -> 15.6 ms a solve, 15.9 with 64 entries a step. (32 entries in
+// flight per thread instead, still a thread per row: 7.3 ms for the 3.53.)
 // Where the level above the coarsest is of that kind, its kernels in this form and
 // the coarsest product also beat k_tail, one block for all its rows: 2.04 -> 1.73 ms;
 // 10000 rows, degree 9: 1.18 -> 0.69 ms.
@@ -1110,6 +1110,41 @@ __global__ void __launch_bounds__(1024) k_coarse_prolong(
   __syncthreads();
   prolong_add(0, nf, (int32_t)threadIdx.x, (int32_t)blockDim.x, aggp, pp, zf,
               [&](int32_t a) { return (TV)zs[a]; });
+}
+
+// The two halves of k_coarse_prolong with many blocks, the same sums in the same
+// order, for n_L above kCoarseOne: one block reads A_L^-1 at the rate of one CU
+// (n_L = 1155: 123 us, these two 11.7 + 4.0; at 256 the read is 0.5 MB, 6 us).
+constexpr int kCoarseOne = 256;
+template <typename TV>
+__global__ void __launch_bounds__(kBlock) k_coarse_rows(int32_t nL,
+                                                        const double *__restrict__ Ainv,
+                                                        const TV *__restrict__ rL,
+                                                        TV *__restrict__ zL,
+                                                        const int32_t *__restrict__ done) {
+  if (*done) return;
+  const int32_t part = threadIdx.x % kCoarseSplit;
+  const int32_t i = (int32_t)(blockIdx.x * kBlock + threadIdx.x) / kCoarseSplit;
+  double s = 0.0;
+  if (i < nL) {
+    const double *row = Ainv + (int64_t)i * nL;
+#pragma unroll 8
+    for (int32_t k = part; k < nL; k += kCoarseSplit) s += row[k] * (double)rL[k];
+  }
+  for (int o = kCoarseSplit / 2; o > 0; o >>= 1) s += __shfl_down(s, o, kCoarseSplit);
+  if (i < nL && part == 0) zL[i] = (TV)s;
+}
+
+// z_f += P y
+template <typename TV>
+__global__ void __launch_bounds__(kBlock) k_prolong(int32_t nf, const int32_t *__restrict__ aggp,
+                                                    const TV *__restrict__ pp,
+                                                    const TV *__restrict__ y,
+                                                    TV *__restrict__ zf,
+                                                    const int32_t *__restrict__ done) {
+  if (*done) return;
+  prolong_add(0, nf, (int32_t)(blockIdx.x * kBlock + threadIdx.x), (int32_t)(gridDim.x * kBlock),
+              aggp, pp, zf, [&](int32_t a) { return y[a]; });
 }
 
 // Tail of the V-cycle in one block, for a level t = L - 1 small enough for
@@ -2478,6 +2513,23 @@ TV *launch_down(amg_hierarchy *h, int32_t l, const TR *r, const int32_t *done) {
   return z;
 }
 
+// A_L^-1 r_L and its prolongation into the z of the level above, F
+template <typename TV>
+void launch_coarse_prolong(amg_hierarchy *h, const Level &F, TV *z, const int32_t *done) {
+  hipStream_t s = h->stream;
+  const Level &C = h->lv.back();
+  const int32_t nL = h->C.n;
+  if (nL <= kCoarseOne) {
+    k_coarse_prolong<TV><<<1, 1024, 2 * sizeof(double) * nL, s>>>(
+        nL, h->C.Ainv, (const TV *)C.r, F.n, F.aggp, ppv<TV>(F), z, done);
+    return;
+  }
+  k_coarse_rows<TV><<<ceil_div((int64_t)nL * kCoarseSplit, kBlock), kBlock, 0, s>>>(
+      nL, h->C.Ainv, (const TV *)C.r, (TV *)C.z, done);
+  k_prolong<TV><<<ceil_div(F.n, 4 * kBlock), kBlock, 0, s>>>(F.n, F.aggp, ppv<TV>(F),
+                                                           (const TV *)C.z, z, done);
+}
+
 // up step on coarse level c >= 1: extra post sweeps, then the last sweep
 // fused with the prolongation into the finer level's z (zf)
 template <typename TV>
@@ -2709,13 +2761,11 @@ void vcycle_t(amg_hierarchy *h, const double *r0, double *z0, bool dot, const do
     for (int32_t c = L - 2; c >= 1; --c) launch_up<TV>(h, c, zb[c], zb[c - 1], done);
   } else {
     Level &F = h->lv[L - 1];
-    const int32_t nL = h->C.n;
     if (coarse_is_pcg(h))
       launch_coarse_pcg<TV, TV>(h, (const TV *)h->lv[L].r, nullptr, F.n, F.aggp, ppv<TV>(F),
                                 zb[L - 1], done);
     else
-      k_coarse_prolong<TV><<<1, 1024, 2 * sizeof(double) * nL, s>>>(
-          nL, h->C.Ainv, (const TV *)h->lv[L].r, F.n, F.aggp, ppv<TV>(F), zb[L - 1], done);
+      launch_coarse_prolong<TV>(h, F, zb[L - 1], done);
     for (int32_t c = L - 1; c >= 1; --c) launch_up<TV>(h, c, zb[c], zb[c - 1], done);
   }
   level0_post<TV>(h, r0, zb[0], z0, dot, dv, done);
@@ -2752,13 +2802,11 @@ void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *
       }
   };
   if (l + 1 == L) {
-    const int32_t nL = h->C.n;
     if (coarse_is_pcg(h))
       launch_coarse_pcg<TV, TV>(h, (const TV *)h->lv[L].r, nullptr, F.n, F.aggp, ppv<TV>(F), z,
                                 done);
     else
-      k_coarse_prolong<TV><<<1, 1024, 2 * sizeof(double) * nL, s>>>(
-          nL, h->C.Ainv, (const TV *)h->lv[L].r, F.n, F.aggp, ppv<TV>(F), z, done);
+      launch_coarse_prolong<TV>(h, F, z, done);
   } else if (l + 2 == L && h->params.pre == 1 && h->params.post == 1 &&
              h->lv[l + 1].n <= kKTailMax && h->C.n <= kKTailCoarse && !coarse_is_pcg(h)) {
     const Level &T = h->lv[l + 1];
