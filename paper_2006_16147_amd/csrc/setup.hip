@@ -7,11 +7,11 @@
 //
 // Per level l (until n_l <= max_coarse):
 //   for each of `sweeps` pairwise sweeps on (A_k, w_k):
-//     1. edge weights, eq. (weights), one value per stored entry
-//     2. matching: rounds of locally-dominant proposals under the strict key
-//        (weight desc, lo asc, hi asc) -- the half-approximate
-//        maximum-weight matching class of the paper; under a strict key it
-//        equals the greedy matching
+//     1. edge weights, eq. (weights), sorted into a preference list per vertex
+//     2. matching of locally dominant edges under the strict key (weight
+//        desc, lo asc, hi asc), in one asynchronous kernel -- the
+//        half-approximate maximum-weight matching class of the paper; under
+//        a strict key it equals the greedy matching, in whatever order
 //     3. aggregate numbering by smallest member (prefix scan)
 //     4. pairwise prolongator, eq. (prolongator)
 //     5. A_{k+1} = P_k^T A_k P_k, w_{k+1} = P_k^T w_k
@@ -28,9 +28,7 @@ namespace amg {
 
 namespace {
 
-constexpr int32_t kFree = -2;
 constexpr int32_t kDead = -1;
-constexpr int kRapCap = 48;     // per-thread Galerkin row buffer
 constexpr int kRapLongCap = 2048;  // per-block buffer for long rows
 constexpr int kScanBlock = 1024;
 constexpr int kScanPer = 4;
