@@ -973,8 +973,13 @@ __global__ void __launch_bounds__(kBlock) k_post_prolong(
 // the coarsest product also beat k_tail, one block for all its rows: 2.04 -> 1.73 ms;
 // 10000 rows, degree 9: 1.18 -> 0.69 ms.
 // kWideMean: stored entries per row, padding included, from which a level takes it
-// (16, 24 and 32 are the same on these; stencils' levels store fewer than 24).
+// (16, 24 and 32 are the same on these), at up to kWideMany rows; with 64 blocks of
+// 96^3 and 128^3, whose coarse levels store 32 to 64, take 7.16 and 12.25 ms for 6.61
+// and 11.69. Above kWideMany rows a thread per row fills the chip, and only rows of
+// twice as many entries pay for the LDS: 256^3 in blocks 95.0 -> 93.9 ms without them on
+// its fourth level, the graph of 200000 and degree 13 (29000 rows) 3.14 -> 2.99 with.
 constexpr int kWideMean = 32;
+constexpr int32_t kWideMany = 32768;
 constexpr int kWideRows = 16;
 constexpr int kWideStep = 128;
 constexpr int kWideLanes = kBlock / kWideRows;
@@ -2349,7 +2354,8 @@ int32_t staged_down_G(const amg_hierarchy *h) { return coarse_per_block(h); }
 
 // whether a level's products take a block per kWideRows rows
 bool wide_rows(const amg_hierarchy *h, const Level &L) {
-  return h->max_seg <= kWideRows && L.S.nnz_padded >= (int64_t)kWideMean * L.n;
+  const int64_t mean = L.n <= kWideMany ? kWideMean : 2 * kWideMean;
+  return h->max_seg <= kWideRows && L.S.nnz_padded >= mean * L.n;
 }
 
 // Down step of level F into C: LDS-staged gathers where the level has tiles of
