@@ -229,6 +229,7 @@ struct amg_hierarchy {
   // p = z + beta p is formed by the product with A into the other p buffer
   bool fold = false;
   double *p2 = nullptr;
+  double *z_out = nullptr;  // while a V-cycle is queued: the caller's z, stored by its last sweep
   bool rr_in_down = false;  // the level-0 down step being launched sums (r, r)
   bool rr_with_rz = false;  // the V-cycle being launched ends with both sums
   int32_t max_seg = 1;            // largest aggregate (segment) of any level
