@@ -72,10 +72,12 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
 
 // Control block of a pairwise sweep (device), and what the host reads of it:
 // the kernel that knows a total writes it, with the block's words, to pinned
-// host memory, which saves a copy of its own.
+// host memory, which saves a copy of its own. Errors have one word for all
+// sweeps of a setup (Report::err): a product's error is known only after the
+// host has gone on to the next sweep, and is read there.
 constexpr int kCtl = 16;
 enum : int32_t {
-  kCtlErr = 0,       // kErr*
+  kCtlErr = 0,       // kErr* (in the host's copy)
   kCtlRounds = 1,    // largest matching round
   kCtlPrefLong = 2,  // rows listed for k_pref_long
   kCtlRapLong = 3,   // rows listed for k_rap_long
@@ -88,13 +90,15 @@ constexpr int kMatchQueue = 4;  // launches of k_match between host checks, at m
 static_assert(kCtlFlags + kMatchQueue * kMatchFlags <= kCtl, "control block");
 struct Report {
   const int32_t *from = nullptr;  // kCtl words
+  const int32_t *err = nullptr;   // the setup's kErr* so far
   int32_t *to = nullptr;          // kCtl + 1 words, the total last; null: no report
 };
 
 __device__ __forceinline__ void report(const Report &R, int32_t total) {
   if (!R.to) return;
   for (int k = 0; k < kCtl; ++k)
-    R.to[k] = __hip_atomic_load(&R.from[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    R.to[k] = __hip_atomic_load(k == kCtlErr ? R.err : &R.from[k], __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
   R.to[kCtl] = total;
 }
 
@@ -1342,26 +1346,24 @@ struct SweepOut {
   int32_t *lead = nullptr;  // coarse -> smallest member (nc)
   int32_t *mate = nullptr;  // n
   int32_t rounds = 0;
-  const int32_t *err = nullptr;  // control block: kErr* of the product
 };
 
 template <int G>
 void launch_pref(const Mat &A, int32_t *pref, uint64_t *st, int32_t *ovf, int32_t *ctl,
-                 hipStream_t s) {
+                 int32_t *err, hipStream_t s) {
   k_pref<G><<<grid((int64_t)A.n * G), kBlock, 0, s>>>(A.n, A.rows, A.w, A.dg, pref, st, ovf,
                                                       ctl + kCtlPrefLong);
   if (A.longest == 0 || A.longest > 2 * G)
     k_pref_long<<<A.n < 2048 ? A.n : 2048, kBlock, 0, s>>>(A.rows, A.w, A.dg, pref, st, ovf,
-                                                           ctl + kCtlPrefLong, ctl + kCtlErr);
+                                                           ctl + kCtlPrefLong, err);
 }
 
 template <int G>
 void launch_rap(int32_t nc, const RowsOf &A, const Coarsened &C, int32_t longest, int32_t *ovf,
-                int32_t *ctl, hipStream_t s) {
+                int32_t *ctl, int32_t *err, hipStream_t s) {
   k_rap<G><<<grid((int64_t)nc * G), kBlock, 0, s>>>(nc, A, C, ovf, ctl + kCtlRapLong);
   if (longest > 2 * G)
-    k_rap_long<<<nc < 1024 ? nc : 1024, kBlock, 0, s>>>(A, C, ovf, ctl + kCtlRapLong,
-                                                        ctl + kCtlErr);
+    k_rap_long<<<nc < 1024 ? nc : 1024, kBlock, 0, s>>>(A, C, ovf, ctl + kCtlRapLong, err);
 }
 
 // the host's copy of the control block and of the total scanned last
@@ -1371,12 +1373,12 @@ amg_status read_ctl(const int32_t *pinned, int32_t *host, hipStream_t s) {
   return AMG_OK;
 }
 
-// (ctl: a zeroed control block)
-amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl, SweepOut &o,
-                          double *t_match, double *t_rap) {
+// (ctl: a zeroed control block; err: the setup's error word)
+amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl, int32_t *err,
+                          SweepOut &o, double *t_match, double *t_rap) {
   hipStream_t s = h->stream;
   const int32_t n = A.n;
-  const Report R{ctl, reinterpret_cast<int32_t *>(h->scal_host)};
+  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host)};
   const double t0 = now_ms();
   int32_t *pref, *id, *bsum, *ovf;
   uint64_t *st;
@@ -1388,10 +1390,10 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   AMG_TRY(tmp.get(&o.mate, n));
   // lanes per row: the mean row (of a sweep's matrix: of the one before it)
   // fills half of a group's places, so that most rows still fit
-  if (A.mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, s);
-  else if (A.mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, s);
-  else if (A.mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, s);
-  else launch_pref<64>(A, pref, st, ovf, ctl, s);
+  if (A.mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, err, s);
+  else if (A.mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, err, s);
+  else if (A.mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, err, s);
+  else launch_pref<64>(A, pref, st, ovf, ctl, err, s);
   // matching, and the numbering of what it gives; where it takes more than
   // the launches queued, both again from there on
   int32_t hc[kCtl + 1];
@@ -1406,7 +1408,9 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
     if (scan_blocks(n) > 1) k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), R);
     AMG_HIP(hipGetLastError());
     AMG_TRY(read_ctl(R.to, hc, s));
-    if (hc[kCtlErr]) return AMG_ERR_ARG;  // a row too long for the Galerkin product
+    // a row too long for this sweep's product, or one that was for the sweep
+    // before it (whose product left that row empty: nothing else here holds then)
+    if (hc[kCtlErr]) return AMG_ERR_ARG;
     const int32_t *last = hc + kCtlFlags + (queue - 1) * kMatchFlags;
     if (!last[kLeft]) break;  // (the last launch does nothing once one before it left nothing)
     if (!last[kMoved]) return AMG_ERR_HIP;  // cannot happen on a symmetric matrix
@@ -1451,10 +1455,10 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   // 7-point stencil's 14 terms take the 16 places of eight lanes)
   const double terms = 1.125 * nnz / nc;
   const int32_t longest = hc[kCtlLongest] > kRapLongCap ? 2 * kRapLongCap : 2 * hc[kCtlLongest];
-  if (terms <= 16.0) launch_rap<8>(nc, A.rows, C, longest, ovf, ctl, s);
-  else if (terms <= 32.0) launch_rap<16>(nc, A.rows, C, longest, ovf, ctl, s);
-  else if (terms <= 64.0) launch_rap<32>(nc, A.rows, C, longest, ovf, ctl, s);
-  else launch_rap<64>(nc, A.rows, C, longest, ovf, ctl, s);
+  if (terms <= 16.0) launch_rap<8>(nc, A.rows, C, longest, ovf, ctl, err, s);
+  else if (terms <= 32.0) launch_rap<16>(nc, A.rows, C, longest, ovf, ctl, err, s);
+  else if (terms <= 64.0) launch_rap<32>(nc, A.rows, C, longest, ovf, ctl, err, s);
+  else launch_rap<64>(nc, A.rows, C, longest, ovf, ctl, err, s);
   AMG_HIP(hipGetLastError());
   o.Ac.n = nc;
   o.Ac.most = nnz;
@@ -1464,15 +1468,15 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   o.Ac.w = C.wc;
   o.Ac.dg = C.dg;
   o.Ac.size = C.csize;
-  o.err = ctl + kCtlErr;
   *t_rap += now_ms() - t1;
   return AMG_OK;
 }
 
 // the last sweep's matrix, packed into level storage
-amg_status adopt_level(amg_hierarchy *h, Tmp &tmp, const Mat &M, const int32_t *ctl, Level &L) {
+amg_status adopt_level(amg_hierarchy *h, Tmp &tmp, const Mat &M, const int32_t *ctl,
+                       const int32_t *err, Level &L) {
   hipStream_t s = h->stream;
-  const Report R{ctl, reinterpret_cast<int32_t *>(h->scal_host)};
+  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host)};
   int32_t *bsum;
   AMG_TRY(tmp.get(&bsum, (size_t)scan_blocks(M.n) + 1));
   L.n = M.n;
@@ -1555,7 +1559,7 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   static_assert(sizeof(PcgScal) >= sizeof(int32_t) * (kCtl + 1), "control block and total");
 
   // validation
-  int32_t *err;
+  int32_t *err;  // kErr*, one word for the whole setup: read, and 0, after each stage
   AMG_TRY(tmp.get(&err, 1));
   k_fill<int32_t><<<1, 1, 0, s>>>(err, 0, 1);
   if (!(P.flags & AMG_FLAG_SKIP_CHECKS))
@@ -1641,10 +1645,11 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     cur.dg = dg;
     int32_t done = 0, rounds = 0;
     SweepMaps maps{};
-    const int32_t *err_ctl = nullptr;
+    const int32_t *last_ctl = nullptr;
     for (int32_t k = 0; k < P.sweeps; ++k) {
       SweepOut o;
-      AMG_TRY(pairwise_sweep(h, tmp, cur, ctls, o, &t_match, &t_rap));
+      AMG_TRY(pairwise_sweep(h, tmp, cur, ctls, err, o, &t_match, &t_rap));
+      last_ctl = ctls;
       ctls += kCtl;
       --ctl_left;
       rounds += o.rounds;
@@ -1653,7 +1658,6 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       maps.p[k] = o.p;
       maps.lead[k] = o.lead;
       maps.mate[k] = o.mate;
-      err_ctl = o.err;
       cur = o.Ac;
       ++done;
     }
@@ -1674,7 +1678,7 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       // the tentative product chose the aggregates and restricted w; the
       // next level is the Galerkin product with the smoothed prolongator
       int32_t herr = 0;
-      AMG_TRY(read_i32(h, err_ctl, &herr));
+      AMG_TRY(read_i32(h, err, &herr));
       if (herr) return AMG_ERR_ARG;
       const double tr = now_ms();
       Cn.n = cur.n;
@@ -1691,7 +1695,7 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       dg = nullptr;
       longest = 0;
     } else {
-      AMG_TRY(adopt_level(h, tmp, cur, err_ctl, Cn));
+      AMG_TRY(adopt_level(h, tmp, cur, last_ctl, err, Cn));
       dg = cur.dg;
       longest = cur.longest;
     }
