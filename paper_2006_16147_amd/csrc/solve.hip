@@ -256,10 +256,16 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
 
 // The sum of nparts partials by a block of kBlock threads, every one of which
 // gets it: k_finalize's sum in its order, thread t adding up what the threads
-// t, t + kBlock, ... of its 1024 would.
-__device__ __forceinline__ double sum_partials(const double *__restrict__ src, int32_t nparts) {
+// t, t + kBlock, ... of its 1024 would. *stopped: whether *done was set, one
+// look for the whole block. Block 0 of the same launch may be setting it, and
+// waves that looked for themselves could part ways in a block that starts late:
+// those that go on would add up slots of the sum that nobody has written.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ src, int32_t nparts,
+                                               const int32_t *done, bool *stopped) {
   constexpr int kRuns = 1024 / kBlock, kWaves = kBlock / kWave;
   __shared__ double wsum[kRuns * kWaves];
+  __shared__ int32_t seen;
+  if (threadIdx.x == 0) seen = *done;
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
 #pragma unroll
   for (int k = 0; k < kRuns; ++k) {
@@ -277,6 +283,7 @@ __device__ __forceinline__ double sum_partials(const double *__restrict__ src, i
     if (lane == 0) wsum[k * kWaves + wid] = a;
   }
   __syncthreads();
+  *stopped = seen != 0;
   double t = wsum[0];
   for (int k = 1; k < kRuns * kWaves; ++k) t += wsum[k];
   return t;
@@ -284,7 +291,8 @@ __device__ __forceinline__ double sum_partials(const double *__restrict__ src, i
 
 // (r, r) and the stop test, by the level-0 down step of a folded iteration:
 // true if the solve goes on. Only block 0 writes, and nothing that a block
-// still starting reads but the flag, which then says what it would find.
+// still starting reads but the flag, which then says what it would find (and
+// is read once per block, see sum_partials).
 struct FinRR {
   PcgScal *scal;
   const double *partials;
@@ -293,7 +301,9 @@ struct FinRR {
 __device__ __forceinline__ bool stop_test(const FinRR &F) {
   const int32_t iter = F.scal->iter1, maxit = F.scal->maxit;
   const double bb = F.scal->bb, rtol = F.scal->rtol;
-  const double rr = sum_partials(F.partials, F.nparts);
+  bool stopped;
+  const double rr = sum_partials(F.partials, F.nparts, &F.scal->done, &stopped);
+  if (stopped) return false;
   const int32_t done = converged(rr, bb, rtol) ? 1 : (iter >= maxit ? 2 : 0);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     F.scal->rr = rr;
@@ -529,8 +539,7 @@ __global__ void __launch_bounds__(kBlock) k_pre_restrict(
     const TV *__restrict__ pp, const TR *__restrict__ r, TV *__restrict__ z,
     TV *__restrict__ rc, const int32_t *__restrict__ done, FinRR fin = FinRR{}) {
   __shared__ TV sh[kBlock * R];
-  if (*done) return;
-  if (FIN && !stop_test(fin)) return;
+  if (FIN ? !stop_test(fin) : *done != 0) return;
   const int32_t J0 = blockIdx.x * G;
   const int32_t J1 = min(nc, J0 + G);
   const int32_t f0 = seg[J0], f1 = seg[J1];
@@ -697,8 +706,7 @@ __global__ void __launch_bounds__(kBlock) k_pre_restrict_lds(
   extern __shared__ double lds_d[];
   TV *xs = reinterpret_cast<TV *>(lds_d);
   __shared__ TV sh[kBlock * R];
-  if (*done) return;
-  if (FIN && !stop_test(fin)) return;
+  if (FIN ? !stop_test(fin) : *done != 0) return;
   const int32_t tb = xcd_block(blockIdx.x, gridDim.x);
   const int32_t J0 = tb * G;
   const int32_t J1 = min(nc, J0 + G);
@@ -1485,8 +1493,8 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 // as the partials are few (kFoldParts). And p = z + beta p joins the product
 // with A, which forms the entries it gathers from z and the old p and writes
 // the new p beside it, in the buffer of the other parity. What a kernel's
-// blocks read of the scalars its block 0 does not write, except the flag.
-
+// blocks read of the scalars its block 0 does not write, except the flag,
+// which each block reads once (sum_partials).
 //
 // Measured with every form at 8^3 to 192^3 (FP64, 1e-8; us a solve): all of it
 // 20^3 922 -> 739, 32^3 1263 -> 1040, 48^3 1885 -> 1715; up to 512 partials
@@ -1518,7 +1526,7 @@ template <bool FOLD>
 __device__ __forceinline__ bool next_direction(PcgScal *scal, const double *partials,
                                                int32_t nparts, double *p0, double *p1,
                                                Direction *D) {
-  if (scal->done) return false;
+  if (!FOLD && scal->done) return false;
   const int32_t iter = scal->iter;
   D->po = iter & 1 ? p1 : p0;
   D->pn = iter & 1 ? p0 : p1;
@@ -1528,7 +1536,10 @@ __device__ __forceinline__ bool next_direction(PcgScal *scal, const double *part
     return true;
   }
   const double rho = scal->rho;
-  const double rz = sum_partials(partials + (int64_t)kRZPlane * kMaxParts, nparts);
+  bool stopped;
+  const double rz =
+      sum_partials(partials + (int64_t)kRZPlane * kMaxParts, nparts, &scal->done, &stopped);
+  if (stopped) return false;
   if (!(rz > 0.0)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) scal->done = 3;
     return false;
@@ -1609,10 +1620,12 @@ __global__ void __launch_bounds__(kBlock) k_update_fold(int32_t n, int32_t chunk
                                                         const double *__restrict__ q,
                                                         double *__restrict__ partials,
                                                         PcgScal *scal) {
-  if (scal->done) return;
   const double rho = scal->rho1;
   const int32_t iter = scal->iter;
-  const double pq = sum_partials(partials + (int64_t)kPQPlane * kMaxParts, gridDim.x);
+  bool stopped;
+  const double pq =
+      sum_partials(partials + (int64_t)kPQPlane * kMaxParts, gridDim.x, &scal->done, &stopped);
+  if (stopped) return;
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
   if (!(pq > 0.0)) {
     if (lead) scal->done = 3;
