@@ -231,7 +231,6 @@ struct amg_hierarchy {
   double *p2 = nullptr;
   double *z_out = nullptr;  // while a V-cycle is queued: the caller's z, stored by its last sweep
   bool rr_in_down = false;  // the level-0 down step being launched sums (r, r)
-  bool rr_with_rz = false;  // the V-cycle being launched ends with both sums
   int32_t max_seg = 1;            // largest aggregate (segment) of any level
   double *partials = nullptr;     // kPartPlanes x kMaxParts block partial sums
   double *kscal = nullptr;  // K-cycle scalars, kKScal per level

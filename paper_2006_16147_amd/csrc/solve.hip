@@ -149,8 +149,7 @@ enum FinOp : int32_t {
   kFinRZ = 3,    // CG: (r, z), beta
   kFinTrue = 4,  // true residual
   kFinPQR = 5,   // flexible CG: (p, q), (p, r), alpha = (p, r) / (p, q)
-  kFinZQ = 6,    // flexible CG: beta = -(z, q) / (p, q)
-  kFinRRZ = 7    // CG: (r, z) and (r, r): the stop test, then beta
+  kFinZQ = 6     // flexible CG: beta = -(z, q) / (p, q)
 };
 
 __device__ __forceinline__ bool converged(double rr, double bb, double rtol) {
@@ -167,7 +166,7 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
   PcgScal sc;
   if (threadIdx.x == 0) sc = *scal;
   __shared__ double sh[2][1024 / kWave];
-  const int nv = op == kFinInit || op == kFinPQR || op == kFinRRZ ? 2 : 1;
+  const int nv = op == kFinInit || op == kFinPQR ? 2 : 1;
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   for (int q = 0; q < nv; ++q) {
     // this thread's partials in index order, sixteen loads at a time
@@ -217,18 +216,6 @@ __global__ void __launch_bounds__(1024) k_finalize(int32_t op, int32_t nparts,
       if (converged(tot[0], sc.bb, sc.rtol)) scal->done = 1;
       else if (sc.iter + 1 >= sc.maxit) scal->done = 2;
       break;
-    case kFinRRZ:
-      scal->rr = tot[1];
-      scal->iter = sc.iter + 1;
-      if (converged(tot[1], sc.bb, sc.rtol)) {
-        scal->done = 1;
-        break;
-      }
-      if (sc.iter + 1 >= sc.maxit) {
-        scal->done = 2;
-        break;
-      }
-      [[fallthrough]];
     case kFinRZ:
       if (!(tot[0] > 0.0)) {
         scal->done = 3;
@@ -1502,12 +1489,11 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 // with 4000 10 % more. The direction in the product alone: 64^3 2552 -> 2480,
 // 96^3 4982 -> 4895, 128^3 8727 -> 8604, 160^3 15874 -> 15919 and 192^3 31449 ->
 // 31554 (it gathers two vectors and staging costs more than the kernel saved):
-// up to kDirRows. With it, (r, r) summed by the kernel that sums (r, z), one
-// kernel less for a V-cycle too many at the end: 64^3 -> 2459, 96^3 -> 4892,
-// 128^3 8621: up to kMergeRows.
+// up to kDirRows. ((r, r) summed by the kernel that sums (r, z), one kernel less
+// for a V-cycle too many at the end, gave 64^3 2480 -> 2459 and 96^3 4895 -> 4892,
+// and cost a solve of one iteration at 96^3 258 -> 307.)
 constexpr int32_t kFoldParts = 512;
 constexpr int32_t kDirRows = 1 << 21;
-constexpr int32_t kMergeRows = 1 << 20;
 // K-cycle levels of up to so many rows take the prolongation in the post-sweep
 // (k_kpost) and r1 = b - s1 v1 in the down step (k_kdown): 80^3 to 1e-6 in FP64
 // 3797 -> 3318 us with limit 131 k, 3304 with 1 M and 3348 with 16 k rows, 160^3
@@ -1651,8 +1637,7 @@ __global__ void __launch_bounds__(kBlock) k_update_fold(int32_t n, int32_t chunk
   block_partial<1>(d, partials + (int64_t)kRRPlane * kMaxParts);
 }
 
-// x += alpha p, r -= alpha q with alpha in the scalars, partials of (r, r) in
-// plane 1, beside the (r, z) to come
+// x += alpha p, r -= alpha q with alpha in the scalars, partials of (r, r)
 __global__ void __launch_bounds__(kBlock) k_update_dir(int32_t n, int32_t chunk,
                                                        double *__restrict__ x,
                                                        double *__restrict__ r, const double *p0,
@@ -1672,7 +1657,7 @@ __global__ void __launch_bounds__(kBlock) k_update_dir(int32_t n, int32_t chunk,
     r[i] = ri;
     d[0] += ri * ri;
   }
-  block_partial<1>(d, partials + kMaxParts);
+  block_partial<1>(d, partials + (int64_t)kRRPlane * kMaxParts);
 }
 
 // ---------------------------------------------------------------------------
@@ -2642,7 +2627,7 @@ void level0_post(amg_hierarchy *h, const double *r0, TV *z, double *z0, bool dot
       post_sweep<TV, double, double, true, TV>(h, F, vals<TV>(F), minv<TV>(F), r0, z, z0,
                                                h->partials, done, dv);
     h->probe_armed = false;
-    if (!dv && !h->fold) finalize(h, h->rr_with_rz ? kFinRRZ : kFinRZ, g.grid, done);
+    if (!dv && !h->fold) finalize(h, kFinRZ, g.grid, done);
   } else if (h->z_out) {
     if (a32)
       post_sweep<TV, double, double, false, float, true>(h, F, F.S.v32, minv<TV>(F), r0, z,
@@ -3488,10 +3473,8 @@ void cg_iteration(amg_hierarchy *h) {
     finalize(h, kFinPQ, g.grid, done, kPQPlane);
     k_update_dir<<<g.grid, kBlock, 0, s>>>(n, g.chunk, h->x, h->r, h->p, h->p2, h->q,
                                            h->partials, h->scal);
-    h->rr_with_rz = n <= kMergeRows;
-    if (!h->rr_with_rz) finalize(h, kFinRR, g.grid, done, 1);
+    finalize(h, kFinRR, g.grid, done, kRRPlane);
     vcycle_perm(h, h->r, h->z, true, done);
-    h->rr_with_rz = false;
     return;
   }
   arm_probe(h, 4);
