@@ -319,10 +319,11 @@ amg_status amg_matching_rounds(const amg_hierarchy *h, int32_t l, int32_t *round
  * without the graph, rtol 0, so every launch does its full work); *ms is
  * the mean of its dispatches' own start-to-end times, which the runtime
  * stamps into events given to the launch (hipExtLaunchKernelGGL), as a
- * profiler's kernel trace measures them. On systems of up to 2^21 rows the
- * solve's kernel 4 also forms p = z + beta p (*bytes: the product's). AMG_ERR_ARG before any solve, and
- * for a hierarchy with the K-cycle, the iterative coarsest solve, smoothed
- * prolongators, or more than one pre- or post-sweep. */
+ * profiler's kernel trace measures them. On systems of up to 2^20 rows the
+ * solve's kernel 4 also forms p = z + beta p (*bytes: the product's).
+ * AMG_ERR_ARG before any solve, and for a hierarchy with the K-cycle, the
+ * iterative coarsest solve, smoothed prolongators, or more than one pre- or
+ * post-sweep. */
 #define AMG_TIME_IN_SOLVE 16
 amg_status amg_time_kernel(amg_hierarchy *h, int32_t kernel, int32_t level, int32_t reps,
                            double *ms, double *bytes);

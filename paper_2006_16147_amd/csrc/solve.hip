@@ -1486,14 +1486,15 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 // Measured with every form at 8^3 to 192^3 (FP64, 1e-8; us a solve): all of it
 // 20^3 922 -> 739, 32^3 1263 -> 1040, 48^3 1885 -> 1715; up to 512 partials
 // (131 k rows): with 1024 (64^3) the blocks' sums cost what the kernels did, and
-// with 4000 10 % more. The direction in the product alone: 64^3 2552 -> 2480,
-// 96^3 4982 -> 4895, 128^3 8727 -> 8604, 160^3 15874 -> 15919 and 192^3 31449 ->
-// 31554 (it gathers two vectors and staging costs more than the kernel saved):
-// up to kDirRows. ((r, r) summed by the kernel that sums (r, z), one kernel less
+// with 4000 10 % more. The direction in the product alone: 64^3 2570 -> 2497,
+// 75^3 5178 -> 5106, 100^3 5614 -> 5546; above 2^20 rows, where a block takes two
+// rows per thread, 102^3 6111 -> 6158, 116^3 7127 -> 7075, 124^3 8394 -> 8433,
+// 128^3 8908 -> 8855, 160^3 15874 -> 15919 and 192^3 31449 -> 31554 (it gathers
+// two vectors, and staging them costs what the kernel saved): up to kDirRows. ((r, r) summed by the kernel that sums (r, z), one kernel less
 // for a V-cycle too many at the end, gave 64^3 2480 -> 2459 and 96^3 4895 -> 4892,
 // and cost a solve of one iteration at 96^3 258 -> 307.)
 constexpr int32_t kFoldParts = 512;
-constexpr int32_t kDirRows = 1 << 21;
+constexpr int32_t kDirRows = 1 << 20;
 // K-cycle levels of up to so many rows take the prolongation in the post-sweep
 // (k_kpost) and r1 = b - s1 v1 in the down step (k_kdown): 80^3 to 1e-6 in FP64
 // 3797 -> 3318 us with limit 131 k, 3304 with 1 M and 3348 with 16 k rows, 160^3
