@@ -278,13 +278,14 @@ void destroy(amg_hierarchy *h) {
   if (!h) return;
   join_async(h);
   if (h->stream) (void)hipStreamSynchronize(h->stream);
-  if (h->iter_exec) (void)hipGraphExecDestroy(h->iter_exec);
-  if (h->iter_graph) (void)hipGraphDestroy(h->iter_graph);
-  if (h->iter_exec4) (void)hipGraphExecDestroy(h->iter_exec4);
-  if (h->iter_graph4) (void)hipGraphDestroy(h->iter_graph4);
+  for (int i = 0; i < kIterGraphs; ++i) {
+    if (h->iter_exec[i]) (void)hipGraphExecDestroy(h->iter_exec[i]);
+    if (h->iter_graph[i]) (void)hipGraphDestroy(h->iter_graph[i]);
+  }
   if (h->batch) free_batch(h->batch, h->device, h->stream);
   stream_free(h->device, h->stream, h->allocs);
   if (h->scal_host) (void)hipHostFree(h->scal_host);
+  if (h->look_event) (void)hipEventDestroy(h->look_event);
   if (h->join_event) (void)hipEventDestroy(h->join_event);
   if (h->stream) (void)hipStreamDestroy(h->stream);
   delete h;

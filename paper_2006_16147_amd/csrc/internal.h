@@ -70,6 +70,7 @@ struct PcgScal {
   double rho1;
   int32_t iter1;
 };
+constexpr int kIterGraphs = 2;  // see solve.hip
 
 // Sliced ELLPACK, 64 rows per slice, column-major inside a slice so that
 // lane i of a wavefront reads row i's k-th entry at consecutive addresses.
@@ -235,18 +236,17 @@ struct amg_hierarchy {
   double *partials = nullptr;     // kPartPlanes x kMaxParts block partial sums
   double *kscal = nullptr;  // K-cycle scalars, kKScal per level
   amg::PcgScal *scal = nullptr;   // device
-  amg::PcgScal *scal_host = nullptr;  // pinned mirror
+  amg::PcgScal *scal_host = nullptr;  // two pinned mirrors
+  hipEvent_t look_event = nullptr;    // after the copy into the second
   void *setup_arena = nullptr;  // the running setup's temporaries (setup.hip), else null
   int32_t *zero_flag = nullptr;   // device int 0 (for kernels outside CG)
   // batch (multi-right-hand-side) solve state, allocated for the last k used
   amg::Batch *batch = nullptr;
   size_t batch_bytes = 0;
-  // graph of one CG iteration
-  hipGraphExec_t iter_exec = nullptr;  // one CG iteration
-  hipGraph_t iter_graph = nullptr;
-  hipGraphExec_t iter_exec4 = nullptr;  // a group of CG iterations
-  hipGraph_t iter_graph4 = nullptr;
-  bool graph_failed = false;
+  // graphs of one and of more CG iterations
+  hipGraphExec_t iter_exec[amg::kIterGraphs] = {};
+  hipGraph_t iter_graph[amg::kIterGraphs] = {};
+  bool graph_failed[amg::kIterGraphs] = {};
   // in-solve kernel timing (amg_time_kernel with AMG_TIME_IN_SOLVE): while
   // probe_id names a kernel, events are recorded right before and after each
   // of its launches, pairwise into probe_ev

@@ -1555,7 +1555,8 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   Tmp tmp(h);
   // (pinned: the scalars of a solve later, small results of the setup's kernels now)
   if (!h->scal_host)
-    AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), sizeof(PcgScal)));
+    AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), 2 * sizeof(PcgScal)));
+  if (!h->look_event) AMG_HIP(hipEventCreateWithFlags(&h->look_event, hipEventDisableTiming));
   static_assert(sizeof(PcgScal) >= sizeof(int32_t) * (kCtl + 1), "control block and total");
 
   // validation

@@ -1494,6 +1494,10 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 // for a V-cycle too many at the end, gave 64^3 2480 -> 2459 and 96^3 4895 -> 4892,
 // and cost a solve of one iteration at 96^3 258 -> 307.)
 constexpr int32_t kFoldParts = 512;
+// iterations queued while the host looks at the first ones, where the
+// hierarchy has so few levels that they are of at most nine kernels (see pcg)
+constexpr int32_t kAhead = 4;
+constexpr size_t kAheadLevels = 5;
 constexpr int32_t kDirRows = 1 << 20;
 // K-cycle levels of up to so many rows take the prolongation in the post-sweep
 // (k_kpost) and r1 = b - s1 v1 in the down step (k_kdown): 80^3 to 1e-6 in FP64
@@ -3514,20 +3518,33 @@ bool capture_iterations(amg_hierarchy *h, int32_t count, hipGraph_t *graph, hipG
   return true;
 }
 
-// Graphs of one and of iter_group() CG iterations (once per hierarchy): a
-// group replay saves the launch gap between consecutive graphs.
-// (folded iterations have about half the kernels: groups of eight)
-int32_t iter_group(const amg_hierarchy *h) { return h->fold ? 8 : 4; }
-amg_status ensure_iteration_graph(amg_hierarchy *h) {
-  if (h->iter_exec || h->graph_failed || (h->params.flags & AMG_FLAG_NO_GRAPH)) return AMG_OK;
-  if (!capture_iterations(h, 1, &h->iter_graph, &h->iter_exec)) {
-    h->graph_failed = true;
-    return AMG_OK;
-  }
-  if (!capture_iterations(h, iter_group(h), &h->iter_graph4, &h->iter_exec4)) {
-    h->iter_graph4 = nullptr;
-    h->iter_exec4 = nullptr;
-  }
+// The graph of kIterGroups[i] CG iterations, made when it is first wanted: a
+// group replay saves the launch gap between consecutive graphs. Null without
+// graphs. (With one of eight too, 20^3 to 1e-6 takes 601 us for 606, and the first
+// solve, which makes the graphs, 80 us more.)
+constexpr int32_t kIterGroups[kIterGraphs] = {1, 4};
+hipGraphExec_t iteration_graph(amg_hierarchy *h, int i) {
+  if (h->iter_exec[i] || h->graph_failed[i] || (h->params.flags & AMG_FLAG_NO_GRAPH))
+    return h->iter_exec[i];
+  if (!capture_iterations(h, kIterGroups[i], &h->iter_graph[i], &h->iter_exec[i]))
+    h->graph_failed[i] = true;
+  return h->iter_exec[i];
+}
+
+// `count` iterations onto the stream
+amg_status launch_iterations(amg_hierarchy *h, int32_t count, bool use_graph) {
+  int32_t k = 0;
+  // (the graphs hold the hierarchy's own scratch buffers: launched only when the
+  // solve uses them)
+  for (int i = kIterGraphs - 1; i >= 0; --i)
+    while (use_graph && k + kIterGroups[i] <= count) {
+      hipGraphExec_t exec = iteration_graph(h, i);
+      if (!exec) break;
+      AMG_HIP(hipGraphLaunch(exec, h->stream));
+      k += kIterGroups[i];
+    }
+  for (; k < count; ++k) cg_iteration(h);
+  AMG_HIP(hipGetLastError());
   return AMG_OK;
 }
 
@@ -3541,11 +3558,6 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
   const int32_t n = L0.n;
   const int32_t *done = &h->scal->done;
   const Geom g = geom(n);
-  if (use_graph) AMG_TRY(ensure_iteration_graph(h));
-  // the graphs hold the hierarchy's own scratch buffers: launched only when
-  // the solve uses them
-  hipGraphExec_t exec1 = use_graph ? h->iter_exec : nullptr;
-  hipGraphExec_t exec4 = use_graph ? h->iter_exec4 : nullptr;
   k_permute_in<<<grid1(n), kBlock, 0, s>>>(n, L0.perm, b_user, h->b);
   h->has_rhs = true;
   k_permute_in<<<grid1(n), kBlock, 0, s>>>(n, L0.perm, x_user, h->x);
@@ -3562,18 +3574,19 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
   if (flexible(h)) AMG_TRY(precond_perm(h, h->r, h->z, nullptr, done));
   else AMG_TRY(vcycle_perm(h, h->r, h->z, true, done));
   if (!h->p2) launch_xpay(h, n, 1, done);
-  // iterations in chunks; the chunk length follows the observed convergence
-  // (folded ones queued after the last cost 10 us, a look at the scalars 50)
-  const int32_t group = iter_group(h);
-  int32_t queued = 0, chunk = h->fold ? 16 : 4;
+  // Iterations in chunks, whose length follows the observed convergence; after
+  // each chunk the host looks at the scalars.
+  int32_t queued = 0, chunk = 0;
   double rr_prev = -1.0;
   int32_t it_prev = 0;
-  for (;;) {
-    AMG_HIP(hipMemcpyAsync(h->scal_host, h->scal, sizeof(PcgScal), hipMemcpyDeviceToHost, s));
-    AMG_HIP(hipStreamSynchronize(s));
-    const PcgScal sc = *h->scal_host;
-    if (sc.done) break;
-    if (queued >= maxit) break;  // not reached: the maxit test sets done
+  auto queue = [&](int32_t count) -> amg_status {
+    const int32_t c = std::min(count, maxit - queued);
+    queued += c > 0 ? c : 0;
+    return c > 0 ? launch_iterations(h, c, use_graph) : AMG_OK;
+  };
+  // the iterations still wanted, seen from scalars that the host has looked at
+  auto wanted = [&](const PcgScal &sc) -> int32_t {
+    if (rr_prev < 0.0) chunk = 4;
     if (rr_prev > 0.0 && sc.iter > it_prev && sc.rr > 0.0 && sc.rr < rr_prev) {
       const double rate = std::pow(sc.rr / rr_prev, 1.0 / (sc.iter - it_prev));
       const double need = std::log(sc.tol2 / sc.rr) / std::log(rate);
@@ -3581,16 +3594,40 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
     }
     rr_prev = sc.rr;
     it_prev = sc.iter;
-    const int32_t c = std::min(chunk, maxit - queued);
-    int32_t k = 0;
-    if (exec4)
-      for (; k + group <= c; k += group) AMG_HIP(hipGraphLaunch(exec4, s));
-    for (; k < c; ++k) {
-      if (exec1) AMG_HIP(hipGraphLaunch(exec1, s));
-      else cg_iteration(h);
+    return chunk - (queued - sc.iter);
+  };
+  // A look costs 50 us in which the GPU waits, more than an iteration of few
+  // kernels. Where the solve has such, and the residual has to fall further
+  // than four iterations bring it (a tenth each, which is fast), the first chunk
+  // is of eight, and four more run while the host looks at its result. Queued in
+  // vain, an iteration costs its launches, 1.7 us a kernel: with 16 in the first
+  // chunk of every folded solve, 20^3 took 587 us to 1e-6 and 364 to 1e-2, 48^3 1344
+  // and 583, 50^3 with 2 + 2 sweeps 2042 and 1074; now 606 and 293, 1314 and 497,
+  // 2125 and 743. (With kernels for the scalars, in chunks of four: 705 and 316,
+  // 1452 and 521, 2168 and 761.)
+  const bool few = h->fold && h->params.pre == 1 && h->params.post == 1 &&
+                   !h->params.smooth_p && h->lv.size() <= kAheadLevels;
+  bool ahead = false;
+  for (int32_t next = 0;;) {
+    AMG_TRY(queue(next));
+    if (ahead) {
+      ahead = false;
+      AMG_HIP(hipMemcpyAsync(h->scal_host + 1, h->scal, sizeof(PcgScal), hipMemcpyDeviceToHost, s));
+      AMG_HIP(hipEventRecord(h->look_event, s));
+      AMG_TRY(queue(kAhead));
+      AMG_HIP(hipEventSynchronize(h->look_event));
+      const PcgScal sc = h->scal_host[1];
+      if (sc.done) break;
+      AMG_TRY(queue(wanted(sc)));
     }
-    AMG_HIP(hipGetLastError());
-    queued += c;
+    AMG_HIP(hipMemcpyAsync(h->scal_host, h->scal, sizeof(PcgScal), hipMemcpyDeviceToHost, s));
+    AMG_HIP(hipStreamSynchronize(s));
+    const PcgScal sc = *h->scal_host;
+    if (sc.done) break;
+    if (queued >= maxit) break;  // not reached: the maxit test sets done
+    ahead = few && rr_prev < 0.0 && std::log10(sc.rr / sc.tol2) > 8.0;
+    next = wanted(sc);
+    if (ahead) next = 8;
   }
   if (L0.S.exact32)
     k_residual_norms<1, float><<<g.grid, kBlock, 0, s>>>(n, g.chunk, L0.S.sptr, L0.S.col,
