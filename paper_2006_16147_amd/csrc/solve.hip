@@ -1502,8 +1502,16 @@ constexpr int32_t kDirRows = 1 << 20;
 // K-cycle levels of up to so many rows take the prolongation in the post-sweep
 // (k_kpost) and r1 = b - s1 v1 in the down step (k_kdown): 80^3 to 1e-6 in FP64
 // 3797 -> 3318 us with limit 131 k, 3304 with 1 M and 3348 with 16 k rows, 160^3
-// 10655, 10738 and 10759: where launches cost more than the larger gathers.
+// 10655, 10738 and 10759: where launches cost more than the larger gathers. And
+// where rows are as short as a 7-point level's (kUpMean stored entries a row): the
+// chain of gathers per entry grows with them, and levels of long rows have kernels
+// of their own. Random graphs of 10000 rows, degree 9, 1994 us on every level, 1238
+// so (1392 without the two kernels); 60000, degree 11, 16.1, 7.64 and 10.1 ms;
+// 100^3 anisotropic 12.37, 12.05 and 12.34; 96^3 in blocks 23.4, 21.1 and 22.3.
+// (With 10 to 14 entries the same but for the anisotropic one, 12.35; with 20
+// 64^3 in blocks 10.68 for 10.34.)
 constexpr int32_t kUpRows = 131072;
+constexpr int32_t kUpMean = 8;
 
 // beta, the old and the new p; FOLD: beta from the partials of (r, z), summed
 // here. false: done, or a breakdown.
@@ -1809,9 +1817,14 @@ __global__ void __launch_bounds__(1024) k_kfin(int32_t nparts,
 // products are summed in a fixed order of their own. A chain of latencies: what
 // both cycles read is loaded at the start (24.2 -> 20 us at 1000 rows in FP64).
 // Against the multi-kernel form a level of 1331 rows over 166 took 974 -> 916 us
-// a solve of 22^3, one of 1728 over 216 the same: larger ones gain nothing.
+// a solve of 22^3, one of 1728 over 216 the same: larger ones gain nothing. Levels
+// of more than kKTailAny rows or over more than kKTailAnyCoarse unknowns take it up
+// to kKTailEntries stored entries, which one block goes through six times: a random
+// graph of 3000 rows, degree 4, 836 for 967 us; of 10000, degree 9, 1994 for 1238.
 constexpr int kKTailMax = 2048;   // largest level t in LDS (five vectors)
 constexpr int kKTailCoarse = 256; // largest coarsest size
+constexpr int kKTailAny = 1536, kKTailAnyCoarse = 128;
+constexpr int64_t kKTailEntries = 24576;
 
 // N sums over the block at once; every thread gets them (fixed order)
 template <int N>
@@ -2364,6 +2377,17 @@ bool wide_rows(const amg_hierarchy *h, const Level &L) {
   return h->max_seg <= kWideRows && L.S.nnz_padded >= mean * L.n;
 }
 
+// whether a K-cycle level's steps may form a vector at every entry they gather
+bool short_rows(const Level &L) {
+  return L.n <= kUpRows && L.S.nnz_padded <= (int64_t)kUpMean * L.n;
+}
+
+// whether the level above the coarsest goes into the one-block step
+bool ktail_fits(const Level &T, int32_t nL) {
+  return (T.n <= kKTailAny && nL <= kKTailAnyCoarse) ||
+         (T.n <= kKTailMax && nL <= kKTailCoarse && T.S.nnz_padded <= kKTailEntries);
+}
+
 // Down step of level F into C: LDS-staged gathers where the level has tiles of
 // that geometry, else down_rows(n) fine rows per thread gathering from memory.
 template <typename TV, typename TR, int MODE, typename TA, bool FIN>
@@ -2810,7 +2834,7 @@ void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *
   const bool a32 = reads32<TV>(F, l);
   double *ks = h->kscal + (int64_t)(l + 1) * kKScal;
   // the prolongation in the one post-sweep
-  const bool up = l > 0 && h->params.post == 1 && F.n <= kUpRows;
+  const bool up = l > 0 && h->params.post == 1 && short_rows(F);
   auto kpost = [&](int32_t nparts) {
     const Level &C = h->lv[l + 1];
     if constexpr (std::is_same<TR, TV>::value && std::is_same<TO, TV>::value)
@@ -2827,7 +2851,7 @@ void kcycle_t(amg_hierarchy *h, int32_t l, const TR *in, TO *out, const double *
     else
       launch_coarse_prolong<TV>(h, F, z, done);
   } else if (l + 2 == L && h->params.pre == 1 && h->params.post == 1 &&
-             h->lv[l + 1].n <= kKTailMax && h->C.n <= kKTailCoarse && !coarse_is_pcg(h)) {
+             ktail_fits(h->lv[l + 1], h->C.n) && !coarse_is_pcg(h)) {
     const Level &T = h->lv[l + 1];
     auto kt = T.n <= 1024 && T.S.max_width <= kRowBatch ? k_ktail<TV, true> : k_ktail<TV, false>;
     kt<<<1, 1024, 0, s>>>(T.n, T.S.sptr, T.S.col, svals<TV>(T), vals<TV>(T), minv<TV>(T),
@@ -2898,7 +2922,7 @@ int32_t fcg2_t(amg_hierarchy *h, int32_t m, const int32_t *done) {
                                                h->partials, done);
   const KSub<TV> sub{b, (const TV *)M.v1, h->partials, g.grid, ks};
   TV *z1 = nullptr;  // of the second cycle, where its down step is done here
-  if (h->params.pre == 1 && n <= kUpRows && !M.hseg.ok()) {
+  if (h->params.pre == 1 && short_rows(M) && !M.hseg.ok()) {
     const Level &C = h->lv[m + 1];
     const int32_t G = coarse_per_block(h);
     z1 = (TV *)M.z;
