@@ -174,6 +174,10 @@ void stream_free(int device, hipStream_t s, const std::vector<void *> &blocks) {
   drop_idle(device, s, kPoolKeepBytes);
 }
 
+void release_kept(int device, hipStream_t s) {
+  if (device >= 0 && device < kMaxDevices) drop_idle(device, s, 0);
+}
+
 // The hierarchy's arrays are cut in order from pool blocks of 64 bytes per
 // level-0 row (1 to 64 MB), larger arrays getting blocks of their own: a pool
 // allocation costs tens of microseconds of host time, and a setup makes about

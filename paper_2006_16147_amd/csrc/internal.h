@@ -276,12 +276,14 @@ namespace amg {
 // (allocation and release are ordered on the given stream and never wait for
 // the whole device, unlike hipFree). Freed blocks are kept, up to
 // kPoolKeepBytes per device, and given out again to any hierarchy; over that
-// the oldest go back to the device, all of them when an allocation fails.
-// Without pool support: hipMalloc / hipFree.
+// the oldest go back to the device, all of them when an allocation of the
+// library's fails. Without pool support: hipMalloc / hipFree.
 constexpr uint64_t kPoolKeepBytes = 8ull << 30;
 amg_status stream_alloc(int device, hipStream_t s, void **p, size_t bytes);
 // waits for the stream, the blocks' only user, first
 void stream_free(int device, hipStream_t s, const std::vector<void *> &blocks);
+// all kept blocks back to the device (for allocations made elsewhere)
+void release_kept(int device, hipStream_t s);
 // allocation owned by the hierarchy (freed in amg_free)
 amg_status dev_alloc(amg_hierarchy *h, void **p, size_t bytes);
 template <typename T>
@@ -292,8 +294,10 @@ inline amg_status dalloc(amg_hierarchy *h, T **p, size_t count) {
 // orders the work stream after everything queued so far on the caller's stream
 amg_status join_user_stream(amg_hierarchy *h);
 
-// exclusive prefix sum of n int32 values; writes n + 1 outputs (out[n] = total)
-amg_status scan_exclusive_i32(const int32_t *in, int32_t *out, int32_t n, hipStream_t s);
+// exclusive prefix sum of n int32 values; writes n + 1 outputs (out[n] = total);
+// bsum: scan_sums(n) ints of scratch
+size_t scan_sums(int32_t n);
+void scan_exclusive_i32(const int32_t *in, int32_t *out, int32_t n, int32_t *bsum, hipStream_t s);
 
 // temporaries of a setup step: cut from the running setup's arena (releasing
 // them is then a no-op), else stream-ordered pool memory; and the same scan

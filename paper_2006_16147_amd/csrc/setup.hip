@@ -1513,13 +1513,11 @@ amg_status setup_scan(amg_hierarchy *h, const int32_t *in, int32_t *out, int32_t
   return AMG_OK;
 }
 
-amg_status scan_exclusive_i32(const int32_t *in, int32_t *out, int32_t n, hipStream_t s) {
-  const int32_t nb = scan_blocks(n);
-  int32_t *bsum = nullptr;
-  AMG_HIP(hipMallocAsync(reinterpret_cast<void **>(&bsum), sizeof(int32_t) * (nb + 1), s));
+size_t scan_sums(int32_t n) { return (size_t)scan_blocks(n) + 1; }
+
+void scan_exclusive_i32(const int32_t *in, int32_t *out, int32_t n, int32_t *bsum,
+                        hipStream_t s) {
   scan_exclusive_i32_with(in, nullptr, out, n, bsum, s);
-  AMG_HIP(hipFreeAsync(bsum, s));
-  return AMG_OK;
 }
 
 // Cholesky by panels (k_chol_panel, k_chol_update)

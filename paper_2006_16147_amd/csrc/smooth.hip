@@ -68,12 +68,13 @@ Workspace &workspace(int device) {
 }
 
 struct Scratch {
+  int device;
   hipStream_t s;
   Workspace &ws;
   std::unique_lock<std::mutex> lock;
   size_t block = 0, used = 0;  // current block and bytes taken from it
   explicit Scratch(const amg_hierarchy *h)
-      : s(h->stream), ws(workspace(h->device)), lock(ws.m) {}
+      : device(h->device), s(h->stream), ws(workspace(h->device)), lock(ws.m) {}
   Scratch(const Scratch &) = delete;
   Scratch &operator=(const Scratch &) = delete;
   ~Scratch() { (void)hipStreamSynchronize(s); }  // the next user may be another stream
@@ -89,7 +90,13 @@ struct Scratch {
       for (const auto &b : ws.blocks) sz = b.second * 2 > sz ? b.second * 2 : sz;
       if (bytes > sz) sz = bytes;
       void *q = nullptr;
-      AMG_HIP(hipMalloc(&q, sz));
+      hipError_t e = hipMalloc(&q, sz);
+      if (e == hipErrorOutOfMemory) {  // the blocks kept for hierarchies first
+        (void)hipGetLastError();
+        release_kept(device, s);
+        e = hipMalloc(&q, sz);
+      }
+      AMG_HIP(e);
       ws.blocks.emplace_back(reinterpret_cast<char *>(q), sz);
       used = 0;
     }
@@ -186,14 +193,15 @@ amg_status radix_sort(Scratch &S, int32_t count, int bits, uint64_t **key, doubl
   if ((int64_t)nblocks * kRadix >= INT32_MAX) return AMG_ERR_ARG;
   uint64_t *k2;
   double *v2;
-  int32_t *hist, *offs;
+  int32_t *hist, *offs, *bsum;
   AMG_TRY(S.get(&k2, (size_t)count));
   AMG_TRY(S.get(&v2, (size_t)count));
   AMG_TRY(S.get(&hist, (size_t)nblocks * kRadix));
   AMG_TRY(S.get(&offs, (size_t)nblocks * kRadix + 1));
+  AMG_TRY(S.get(&bsum, scan_sums(nblocks * kRadix)));
   for (int shift = 0; shift < bits; shift += kRadixBits) {
     k_radix_hist<<<nblocks, kSortThreads, 0, s>>>(count, *key, shift, nblocks, hist);
-    AMG_TRY(scan_exclusive_i32(hist, offs, nblocks * kRadix, s));
+    scan_exclusive_i32(hist, offs, nblocks * kRadix, bsum, s);
     k_radix_scatter<<<nblocks, kSortThreads, 0, s>>>(count, *key, *val, shift, nblocks, offs, k2,
                                                      v2);
     std::swap(*key, k2);
@@ -259,11 +267,12 @@ template <typename Alloc>
 amg_status reduce_sorted(Scratch &S, int32_t count, const uint64_t *key, const double *val,
                          int32_t nrows, int cb, Alloc alloc, CsrOut *out) {
   hipStream_t s = S.s;
-  int32_t *h, *run;
+  int32_t *h, *run, *bsum;
   AMG_TRY(S.get(&h, (size_t)count + 1));
   AMG_TRY(S.get(&run, (size_t)count + 1));
+  AMG_TRY(S.get(&bsum, scan_sums(count)));
   k_heads<<<grid(count), kBlock, 0, s>>>(count, key, h);
-  AMG_TRY(scan_exclusive_i32(h, run, count, s));
+  scan_exclusive_i32(h, run, count, bsum, s);
   int32_t nrun = 0;
   AMG_HIP(hipMemcpyAsync(&nrun, run + count, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   AMG_HIP(hipStreamSynchronize(s));
