@@ -252,8 +252,17 @@ amg_status amg_query(amg_hierarchy *h, int32_t *done);
  * on it. Lets a serving loop reuse a cached hierarchy from any slot. */
 amg_status amg_set_stream(amg_hierarchy *h, void *stream);
 
-/* Releases the hierarchy and all its device memory. NULL is a no-op. */
+/* Releases the hierarchy and all its device memory, after waiting for its
+ * work. NULL is a no-op. Up to 8 GiB per device of the freed blocks stay with
+ * the library, which gives them to later hierarchies; it returns them to the
+ * device when an allocation of its own fails, and with amg_release_memory. */
 void amg_free(amg_hierarchy *h);
+
+/* Returns to `device` (-1: the current device) the blocks of freed hierarchies
+ * that the library keeps for later ones. *bytes (may be NULL): how many.
+ * Hierarchies in use, and the workspace of smoothed setups, stay. May be
+ * called from any thread. */
+amg_status amg_release_memory(int32_t device, size_t *bytes);
 
 /* ---- introspection (tests, serving, benchmarks) ------------------------ */
 

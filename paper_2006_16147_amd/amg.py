@@ -18,7 +18,8 @@ __all__ = [
     "lib_path", "load_library", "Params", "SolveInfo", "Hierarchy",
     "amg_params_default", "amg_setup", "amg_pcg_solve", "amg_pcg_solve_batch",
     "amg_vcycle_apply", "amg_free", "amg_estimate_footprint", "amg_status_string",
-    "amg_wait", "amg_query", "amg_pcg_solve_noalloc", "FLAG_ASYNC", "EXPORTED_SYMBOLS",
+    "amg_wait", "amg_query", "amg_pcg_solve_noalloc", "amg_release_memory", "FLAG_ASYNC",
+    "EXPORTED_SYMBOLS",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -35,7 +36,7 @@ EXPORTED_SYMBOLS = (
     "amg_get_transfer", "amg_get_l1diag", "amg_get_w", "amg_footprint_bytes",
     "amg_estimate_footprint", "amg_setup_times", "amg_matching_rounds", "amg_time_kernel",
     "amg_batch_tile", "amg_status_string", "amg_get_prolongator", "amg_get_aggregates",
-    "amg_wait", "amg_query", "amg_pcg_solve_noalloc",
+    "amg_wait", "amg_query", "amg_pcg_solve_noalloc", "amg_release_memory",
 )
 
 
@@ -113,6 +114,7 @@ def load_library():
         "amg_query": (C.c_int, [V, P(I32)]),
         "amg_get_aggregates": (C.c_int, [V, I32, V]),
         "amg_free": (None, [V]),
+        "amg_release_memory": (C.c_int, [I32, P(C.c_size_t)]),
         "amg_num_levels": (C.c_int, [V, P(I32)]),
         "amg_level_info": (C.c_int, [V, I32, P(I64), P(I64)]),
         "amg_get_level_csr": (C.c_int, [V, I32, V, V, V]),
@@ -172,6 +174,15 @@ def amg_status_string(status: int) -> str:
 def amg_estimate_footprint(n: int, nnz: int, params: Params | None = None) -> int:
     p = params if params is not None else amg_params_default()
     return int(load_library().amg_estimate_footprint(int(n), int(nnz), C.byref(p)))
+
+
+def amg_release_memory(device: int = -1) -> int:
+    """Bytes of freed hierarchies' memory given back to the device (-1: current)."""
+    n = C.c_size_t()
+    st = load_library().amg_release_memory(int(device), C.byref(n))
+    if st != Status.OK:
+        raise AmgError(st, "amg_release_memory")
+    return int(n.value)
 
 
 class Hierarchy:

@@ -78,10 +78,10 @@ void device_free(int device, hipStream_t s, void *p) {
 }
 
 // Gives idle blocks back to the device, the oldest first, until at most `keep`
-// bytes are left.
-void drop_idle(int device, hipStream_t s, size_t keep) {
+// bytes are left; returns the bytes given back.
+size_t drop_idle(int device, hipStream_t s, size_t keep) {
   BlockCache &C = g_blocks[device];
-  bool any = false;
+  size_t given = 0;
   for (;;) {
     void *p;
     {
@@ -92,16 +92,17 @@ void drop_idle(int device, hipStream_t s, size_t keep) {
         if (it->second.second < old->second.second) old = it;
       p = old->second.first;
       C.bytes -= old->first;
+      given += old->first;
       C.size.erase(p);
       C.idle.erase(old);
     }
     device_free(device, s, p);
-    any = true;
   }
-  if (!any) return;
+  if (!given) return 0;
   (void)hipStreamSynchronize(s);
   hipMemPool_t pool = lib_pool(device);
   if (pool && hipMemPoolTrimTo(pool, 0) != hipSuccess) (void)hipGetLastError();
+  return given;
 }
 
 }  // namespace
@@ -174,8 +175,8 @@ void stream_free(int device, hipStream_t s, const std::vector<void *> &blocks) {
   drop_idle(device, s, kPoolKeepBytes);
 }
 
-void release_kept(int device, hipStream_t s) {
-  if (device >= 0 && device < kMaxDevices) drop_idle(device, s, 0);
+size_t release_kept(int device, hipStream_t s) {
+  return device >= 0 && device < kMaxDevices ? drop_idle(device, s, 0) : 0;
 }
 
 // The hierarchy's arrays are cut in order from pool blocks of 64 bytes per
@@ -504,6 +505,27 @@ void amg_free(amg_hierarchy *h) {
   if (!h) return;
   DeviceGuard guard(h->device);
   destroy(h);
+}
+
+amg_status amg_release_memory(int32_t device, size_t *bytes) {
+  if (bytes) *bytes = 0;
+  if (device < -1) return AMG_ERR_ARG;
+  int current = 0, count = 0;
+  if (hipGetDeviceCount(&count) != hipSuccess) return AMG_ERR_HIP;
+  if (device < 0) {
+    if (hipGetDevice(&current) != hipSuccess) return AMG_ERR_HIP;
+    device = current;
+  }
+  if (device >= count) return AMG_ERR_ARG;
+  DeviceGuard guard(device);
+  if (!guard.ok) return AMG_ERR_HIP;
+  // (a stream of its own: nothing of the caller's is waited for)
+  hipStream_t s = nullptr;
+  AMG_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+  const size_t given = release_kept(device, s);
+  (void)hipStreamDestroy(s);
+  if (bytes) *bytes = given;
+  return AMG_OK;
 }
 
 amg_status amg_num_levels(const amg_hierarchy *h, int32_t *nlev) {

@@ -277,13 +277,14 @@ namespace amg {
 // the whole device, unlike hipFree). Freed blocks are kept, up to
 // kPoolKeepBytes per device, and given out again to any hierarchy; over that
 // the oldest go back to the device, all of them when an allocation of the
-// library's fails. Without pool support: hipMalloc / hipFree.
+// library's fails or the caller asks for it (amg_release_memory). Without pool
+// support: hipMalloc / hipFree.
 constexpr uint64_t kPoolKeepBytes = 8ull << 30;
 amg_status stream_alloc(int device, hipStream_t s, void **p, size_t bytes);
 // waits for the stream, the blocks' only user, first
 void stream_free(int device, hipStream_t s, const std::vector<void *> &blocks);
-// all kept blocks back to the device (for allocations made elsewhere)
-void release_kept(int device, hipStream_t s);
+// all kept blocks back to the device (for allocations made elsewhere): their bytes
+size_t release_kept(int device, hipStream_t s);
 // allocation owned by the hierarchy (freed in amg_free)
 amg_status dev_alloc(amg_hierarchy *h, void **p, size_t bytes);
 template <typename T>

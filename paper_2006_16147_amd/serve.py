@@ -23,7 +23,9 @@ are started on other slots and their GPU work overlaps:
   test before each admission: free memory, less the reservations of the
   requests in flight and a margin, must cover the request; if it does not,
   the backend's caches are released and idle hierarchies evicted before the
-  request waits.
+  request waits. A backend that keeps the memory of released hierarchies gives
+  it back before each look, so that no hierarchy is evicted for memory that
+  the one before it has already left.
 * Two requests on the same operator never run at once (a hierarchy is used
   by one thread at a time); the second waits for the first.
 
@@ -206,7 +208,10 @@ class Server:
         if rel is not None and (running == 0 or now - self._last_release >= 0.5):
             rel()
             self._last_release = now
+        freed = getattr(self.backend, "release_freed", None)
         while True:
+            if freed is not None:
+                freed()
             room = self._device_room()
             if need <= room:
                 return True
@@ -449,6 +454,10 @@ class GpuBackend:
         # blocks the torch allocator keeps from earlier requests' operator
         # builds and vectors
         self.torch.cuda.empty_cache()
+
+    def release_freed(self):
+        # blocks the library keeps from released hierarchies
+        self.amg.amg_release_memory(self.dev.index)
 
     def make_slot(self, i):
         torch = self.torch

@@ -56,3 +56,30 @@ def run(script):
 
 def test_smoothed_setup_gets_the_kept_blocks():
     assert "levels" in run(_WORKSPACE)
+
+
+_GIVEN_BACK = _START + r"""
+live = amg.amg_setup(*operator(48))
+before = free_bytes()
+leave_blocks()
+kept = before - free_bytes()
+given = amg.amg_release_memory()
+after = free_bytes()
+print("kept", kept >> 20, "given", given >> 20, "missing", (before - after) >> 20, flush=True)
+assert given > 4 * G and abs(kept - given) < G // 4
+assert before - after < G // 4
+assert amg.amg_release_memory(0) == 0
+b = torch.ones(48 ** 3, dtype=torch.float64, device="cuda:0")
+x = torch.zeros_like(b)
+st, info = amg.amg_pcg_solve(live, b, x)
+assert st == 0 and info["converged"]
+L = amg.load_library()
+assert L.amg_release_memory(-2, None) == amg.Status.ERR_ARG
+assert L.amg_release_memory(torch.cuda.device_count(), None) == amg.Status.ERR_ARG
+assert L.amg_release_memory(-1, None) == amg.Status.OK
+print("given back", flush=True)
+"""
+
+
+def test_caller_has_the_kept_blocks_back():
+    assert "given back" in run(_GIVEN_BACK)
