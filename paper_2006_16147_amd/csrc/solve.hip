@@ -3133,14 +3133,18 @@ void launch_halo(amg_hierarchy *h, const Level &L, const Tiling &T, int32_t pass
                                                      H.hptr, H.hidx, H.lcol);
 }
 
-// the tiles' starts and list lengths (the lengths on their way to the host)
+amg_status alloc_tiling(amg_hierarchy *h, Tiling *T) {
+  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&T->tb),
+                          sizeof(int32_t) * ((size_t)T->ntiles + 1)));
+  return setup_tmp_alloc(h, reinterpret_cast<void **>(&T->count),
+                         sizeof(int32_t) * ((size_t)T->ntiles + 1));
+}
+
+// the tiles' starts and list lengths (the lengths on their way to T->hc: the
+// caller waits for the stream before that goes, whatever is returned)
 amg_status count_halo(amg_hierarchy *h, const Level &L, int32_t step, int32_t nmax,
                       const int32_t *seg, Tiling *T) {
   hipStream_t s = h->stream;
-  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&T->tb),
-                          sizeof(int32_t) * ((size_t)T->ntiles + 1)));
-  AMG_TRY(setup_tmp_alloc(h, reinterpret_cast<void **>(&T->count),
-                          sizeof(int32_t) * ((size_t)T->ntiles + 1)));
   k_tile_starts<<<ceil_div(T->ntiles + 1, kBlock), kBlock, 0, s>>>(T->ntiles, step, nmax, seg,
                                                                    T->tb);
   launch_halo(h, L, *T, 0, Halo{});
@@ -3195,9 +3199,12 @@ amg_status build_level0_halos(amg_hierarchy *h) {
   segs.ntiles = ceil_div(C.n, G);
   segs.param = G;
   segs.rows = (int64_t)G * h->max_seg;
-  AMG_TRY(count_halo(h, F, g.chunk, F.n, nullptr, &rows));
-  AMG_TRY(count_halo(h, F, G, C.n, F.seg, &segs));
+  AMG_TRY(alloc_tiling(h, &rows));
+  AMG_TRY(alloc_tiling(h, &segs));
+  amg_status st = count_halo(h, F, g.chunk, F.n, nullptr, &rows);
+  if (st == AMG_OK) st = count_halo(h, F, G, C.n, F.seg, &segs);
   AMG_HIP(hipStreamSynchronize(h->stream));
+  AMG_TRY(st);
   AMG_TRY(build_halo(h, F, rows, &F.hrow));
   return build_halo(h, F, segs, &F.hseg);
 }
