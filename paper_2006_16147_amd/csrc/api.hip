@@ -9,6 +9,7 @@
 #include <new>
 #include <system_error>
 #include <thread>
+#include <type_traits>
 #include <unordered_map>
 #include <utility>
 
@@ -70,7 +71,10 @@ struct BlockCache {
   size_t bytes = 0;                                         // of the idle ones
   uint64_t age = 0;
 };
-BlockCache g_blocks[kMaxDevices];
+// never destroyed: threads of the caller's may still free hierarchies while the
+// process ends
+BlockCache *const g_blocks = new BlockCache[kMaxDevices];
+static_assert(std::is_trivially_destructible<decltype(g_blocks)>::value, "kept at exit");
 
 void device_free(int device, hipStream_t s, void *p) {
   if (lib_pool(device)) (void)hipFreeAsync(p, s);
