@@ -302,10 +302,9 @@ size_t amg_footprint_bytes(const amg_hierarchy *h);
 size_t amg_estimate_footprint(int64_t n, int64_t nnz, const amg_params *params);
 /* Milliseconds of the last amg_setup, split by stage (host array of 8):
  * validate, weights+matching, numbering+prolongator, Galerkin, compose,
- * smoother+coarsest, solve-format conversion, total. Stages that the host does
- * not wait for count with the next one it waits for: a pairwise sweep is
- * waited for once, when its aggregates are counted, so weights+matching holds
- * most of the numbering and Galerkin kernels too (numbering reads 0). */
+ * smoother+coarsest, solve-format conversion, total. Numbering and (without
+ * smoothing) Galerkin are the times of their kernels on the device; the others
+ * are the host's, weights+matching (with its waits) without those two. */
 amg_status amg_setup_times(const amg_hierarchy *h, double *ms_host);
 /* Number of matching rounds run when building level l (sum over sweeps). */
 amg_status amg_matching_rounds(const amg_hierarchy *h, int32_t l, int32_t *rounds);

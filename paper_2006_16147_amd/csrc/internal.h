@@ -236,7 +236,7 @@ struct amg_hierarchy {
   double *partials = nullptr;     // kPartPlanes x kMaxParts block partial sums
   double *kscal = nullptr;  // K-cycle scalars, kKScal per level
   amg::PcgScal *scal = nullptr;   // device
-  amg::PcgScal *scal_host = nullptr;  // two pinned mirrors
+  amg::PcgScal *scal_host = nullptr;  // two pinned mirrors (and the setup's stamps)
   hipEvent_t look_event = nullptr;    // after the copy into the second
   void *setup_arena = nullptr;  // the running setup's temporaries (setup.hip), else null
   int32_t *zero_flag = nullptr;   // device int 0 (for kernels outside CG)

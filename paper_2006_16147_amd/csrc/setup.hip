@@ -19,8 +19,10 @@
 // Then the l1-Jacobi diagonal (Section 3.3) and, on the coarsest level, a
 // dense Cholesky factor and its triangular inverse.
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstring>
 
 #include "internal.h"
 
@@ -70,6 +72,17 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
   return off + x - v;
 }
 
+// When a sweep's stages begin on the device, in ticks of its wall clock: kernels
+// write it to pinned host memory as they start (no event or wait between them;
+// a store of 8 bytes). Numbering is the count of the aggregates and, after the
+// host has read it, their assignment.
+struct Stamps {
+  uint64_t count, counted, assign, product, end;
+};
+__device__ __forceinline__ void stamp(uint64_t *at) {
+  if (at && blockIdx.x == 0 && threadIdx.x == 0) *at = wall_clock64();
+}
+
 // Control block of a pairwise sweep (device), and what the host reads of it:
 // the kernel that knows a total writes it, with the block's words, to pinned
 // host memory, which saves a copy of its own. Errors have one word for all
@@ -92,6 +105,7 @@ struct Report {
   const int32_t *from = nullptr;  // kCtl words
   const int32_t *err = nullptr;   // the setup's kErr* so far
   int32_t *to = nullptr;          // kCtl + 1 words, the total last; null: no report
+  uint64_t *when = nullptr;       // stamp of the report
 };
 
 __device__ __forceinline__ void report(const Report &R, int32_t total) {
@@ -100,6 +114,7 @@ __device__ __forceinline__ void report(const Report &R, int32_t total) {
     R.to[k] = __hip_atomic_load(k == kCtlErr ? R.err : &R.from[k], __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_AGENT);
   R.to[kCtl] = total;
+  if (R.when) *R.when = wall_clock64();
 }
 
 // the end of a block's part of a scan (one thread): its sum; a scan of one
@@ -327,7 +342,8 @@ __global__ void __launch_bounds__(kBlock) k_pref(int32_t n, RowsOf A, const doub
                                                  const double *__restrict__ dg,
                                                  int32_t *__restrict__ pref,
                                                  uint64_t *__restrict__ st, int32_t *ovf,
-                                                 int32_t *novf) {
+                                                 int32_t *novf, uint64_t *began) {
+  stamp(began);
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int32_t i = (int32_t)(t / G);
   const int lane = (int)(t % G);
@@ -583,8 +599,10 @@ __global__ void __launch_bounds__(kMatchThreads, 8) k_match(int32_t n,
 __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint64_t *st,
                                                           const int32_t *rb, const int32_t *re,
                                                           int32_t *mate, int32_t *id,
-                                                          int32_t *bsum, int32_t *ctl, Report R) {
+                                                          int32_t *bsum, int32_t *ctl, Report R,
+                                                          uint64_t *began) {
   __shared__ int32_t most, sum, wide;
+  stamp(began);
   if (threadIdx.x == 0) most = sum = wide = 0;
   const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
   int32_t lead[kScanPer];
@@ -632,7 +650,9 @@ __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint6
 // aggregates by their smallest member, and the pairwise prolongator:
 // pair {i < j}: p_v = w_v / sqrt(w_i w_i + w_j w_j); singleton: w_s / |w_s|
 __global__ void k_assign(int32_t n, const int32_t *mate, const int32_t *id, const int32_t *bsum,
-                         const double *w, int32_t *agg, int32_t *lead, double *p) {
+                         const double *w, int32_t *agg, int32_t *lead, double *p,
+                         uint64_t *began) {
+  stamp(began);
   const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
   const int32_t m = mate[v];
@@ -663,7 +683,8 @@ __global__ void k_assign(int32_t n, const int32_t *mate, const int32_t *id, cons
 __global__ void __launch_bounds__(kScanBlock) k_terms_scan(int32_t nc, const int32_t *lead,
                                                            const int32_t *mate, const int32_t *rb,
                                                            const int32_t *re, int32_t *off,
-                                                           int32_t *bsum) {
+                                                           int32_t *bsum, uint64_t *began) {
+  stamp(began);
   const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
   int32_t len[kScanPer];
   int32_t s = 0;
@@ -905,7 +926,9 @@ struct SweepMaps {
   const double *p[kMaxSweeps];
   const int32_t *lead[kMaxSweeps], *mate[kMaxSweeps];  // coarse -> members
 };
-__global__ void k_compose(int32_t n, int32_t sweeps, SweepMaps M, int32_t *agg, double *p) {
+__global__ void k_compose(int32_t n, int32_t sweeps, SweepMaps M, int32_t *agg, double *p,
+                          uint64_t *began) {
+  stamp(began);
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int32_t a = M.agg[0][i];
@@ -1350,9 +1373,9 @@ struct SweepOut {
 
 template <int G>
 void launch_pref(const Mat &A, int32_t *pref, uint64_t *st, int32_t *ovf, int32_t *ctl,
-                 int32_t *err, hipStream_t s) {
+                 int32_t *err, uint64_t *began, hipStream_t s) {
   k_pref<G><<<grid((int64_t)A.n * G), kBlock, 0, s>>>(A.n, A.rows, A.w, A.dg, pref, st, ovf,
-                                                      ctl + kCtlPrefLong);
+                                                      ctl + kCtlPrefLong, began);
   if (A.longest == 0 || A.longest > 2 * G)
     k_pref_long<<<A.n < 2048 ? A.n : 2048, kBlock, 0, s>>>(A.rows, A.w, A.dg, pref, st, ovf,
                                                            ctl + kCtlPrefLong, err);
@@ -1373,13 +1396,13 @@ amg_status read_ctl(const int32_t *pinned, int32_t *host, hipStream_t s) {
   return AMG_OK;
 }
 
-// (ctl: a zeroed control block; err: the setup's error word)
+// (ctl: a zeroed control block; err: the setup's error word; when: the sweep's
+// stamps, before: where the sweep before it takes its end from, may be null)
 amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl, int32_t *err,
-                          SweepOut &o, double *t_match, double *t_rap) {
+                          Stamps *when, uint64_t *before, SweepOut &o) {
   hipStream_t s = h->stream;
   const int32_t n = A.n;
-  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host)};
-  const double t0 = now_ms();
+  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host), &when->counted};
   int32_t *pref, *id, *bsum, *ovf;
   uint64_t *st;
   AMG_TRY(tmp.get(&pref, A.most));
@@ -1390,10 +1413,10 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   AMG_TRY(tmp.get(&o.mate, n));
   // lanes per row: the mean row (of a sweep's matrix: of the one before it)
   // fills half of a group's places, so that most rows still fit
-  if (A.mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, err, s);
-  else if (A.mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, err, s);
-  else if (A.mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, err, s);
-  else launch_pref<64>(A, pref, st, ovf, ctl, err, s);
+  if (A.mean <= 8.0) launch_pref<8>(A, pref, st, ovf, ctl, err, before, s);
+  else if (A.mean <= 16.0) launch_pref<16>(A, pref, st, ovf, ctl, err, before, s);
+  else if (A.mean <= 32.0) launch_pref<32>(A, pref, st, ovf, ctl, err, before, s);
+  else launch_pref<64>(A, pref, st, ovf, ctl, err, before, s);
   // matching, and the numbering of what it gives; where it takes more than
   // the launches queued, both again from there on
   int32_t hc[kCtl + 1];
@@ -1404,7 +1427,7 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
           n, A.rows.b, A.rows.e, pref, st, r > 0 ? f - kMatchFlags : nullptr, f);
     }
     k_lead_scan<<<scan_blocks(n), kScanBlock, 0, s>>>(n, st, A.rows.b, A.rows.e, o.mate, id, bsum,
-                                                      ctl, R);
+                                                      ctl, R, &when->count);
     if (scan_blocks(n) > 1) k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), R);
     AMG_HIP(hipGetLastError());
     AMG_TRY(read_ctl(R.to, hc, s));
@@ -1419,13 +1442,12 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   o.rounds = hc[kCtlRounds] > 0 ? hc[kCtlRounds] - 1 : 0;
   const int32_t nc = hc[kCtl], nnz = hc[kCtlEntries];
   o.nc = nc;
-  const double t1 = now_ms();
-  *t_match += t1 - t0;
   if (nc == n) return AMG_OK;
   AMG_TRY(tmp.get(&o.agg, n));
   AMG_TRY(tmp.get(&o.lead, nc));
   AMG_TRY(tmp.get(&o.p, n));
-  k_assign<<<grid(n), kBlock, 0, s>>>(n, o.mate, id, bsum, A.w, o.agg, o.lead, o.p);
+  k_assign<<<grid(n), kBlock, 0, s>>>(n, o.mate, id, bsum, A.w, o.agg, o.lead, o.p,
+                                      &when->assign);
 
   // Galerkin product and restricted w
   Coarsened C{};
@@ -1448,7 +1470,7 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   C.bsum = bsum2;
   C.size = A.size;
   k_terms_scan<<<scan_blocks(nc), kScanBlock, 0, s>>>(nc, o.lead, o.mate, A.rows.b, A.rows.e, off,
-                                                      bsum2);
+                                                      bsum2, &when->product);
   if (scan_blocks(nc) > 1)
     k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum2, scan_blocks(nc), Report{});
   // lanes per coarse row: room for the mean row's terms and an eighth more (the
@@ -1468,7 +1490,6 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
   o.Ac.w = C.wc;
   o.Ac.dg = C.dg;
   o.Ac.size = C.csize;
-  *t_rap += now_ms() - t1;
   return AMG_OK;
 }
 
@@ -1551,11 +1572,17 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   } attach{h};
   h->setup_arena = &arena;
   Tmp tmp(h);
-  // (pinned: the scalars of a solve later, small results of the setup's kernels now)
+  // pinned: the scalars of a solve later, small results of the setup's kernels
+  // now, and behind them the sweeps' stamps
+  const size_t stamps = sizeof(Stamps) * (size_t)P.max_levels * P.sweeps;
+  static_assert(2 * sizeof(PcgScal) % alignof(Stamps) == 0, "stamps behind the scalars");
   if (!h->scal_host)
-    AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), 2 * sizeof(PcgScal)));
+    AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), 2 * sizeof(PcgScal) + stamps));
+  Stamps *const when = reinterpret_cast<Stamps *>(h->scal_host + 2);
+  std::memset(when, 0, stamps);
   if (!h->look_event) AMG_HIP(hipEventCreateWithFlags(&h->look_event, hipEventDisableTiming));
   static_assert(sizeof(PcgScal) >= sizeof(int32_t) * (kCtl + 1), "control block and total");
+  int32_t ran = 0;
 
   // validation
   int32_t *err;  // kErr*, one word for the whole setup: read, and 0, after each stage
@@ -1610,7 +1637,8 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     }
   }
 
-  double t_match = 0, t_rap = 0, t_compose = 0;
+  double t_sweeps = 0, t_smooth = 0, t_compose = 0;
+  std::vector<int32_t> last_of_level;  // sweeps whose product the host waits for as composition
   // control blocks of the sweeps to come, zeroed a level's worth or more at a time
   constexpr int kCtlBlocks = 32;
   static_assert(kCtlBlocks >= kMaxSweeps, "a level's sweeps");
@@ -1647,7 +1675,11 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     const int32_t *last_ctl = nullptr;
     for (int32_t k = 0; k < P.sweeps; ++k) {
       SweepOut o;
-      AMG_TRY(pairwise_sweep(h, tmp, cur, ctls, err, o, &t_match, &t_rap));
+      const double t0 = now_ms();
+      AMG_TRY(pairwise_sweep(h, tmp, cur, ctls, err, when + ran,
+                             k > 0 ? &when[ran - 1].end : nullptr, o));
+      t_sweeps += now_ms() - t0;
+      ++ran;
       last_ctl = ctls;
       ctls += kCtl;
       --ctl_left;
@@ -1669,7 +1701,10 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     AMG_TRY(dalloc(h, &F.p64, (size_t)n));
     AMG_TRY(dalloc(h, &F.mptr, (size_t)cur.n + 1));
     AMG_TRY(dalloc(h, &F.mem, (size_t)n));
-    k_compose<<<grid(n), kBlock, 0, s>>>(n, done, maps, F.agg, F.p64);
+    const bool all = done == P.sweeps;  // (else one more sweep began after the last product)
+    if (all) last_of_level.push_back(ran - 1);
+    k_compose<<<grid(n), kBlock, 0, s>>>(n, done, maps, F.agg, F.p64,
+                                         all ? &when[ran - 1].end : nullptr);
     AMG_TRY(tmp.scan(cur.size, F.mptr, cur.n));
     k_members<<<grid(cur.n), kBlock, 0, s>>>(cur.n, done, maps, F.mptr, F.mem);
     Level Cn;
@@ -1690,7 +1725,7 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
       AMG_TRY(dalloc(h, &Cn.w, (size_t)cur.n));
       AMG_HIP(hipMemcpyAsync(Cn.w, cur.w, sizeof(double) * cur.n, hipMemcpyDeviceToDevice, s));
       tc += now_ms() - tr;  // counted as Galerkin time, not composition
-      t_rap += now_ms() - tr;
+      t_smooth += now_ms() - tr;
       dg = nullptr;
       longest = 0;
     } else {
@@ -1701,9 +1736,6 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     h->lv.push_back(Cn);
     t_compose += now_ms() - tc;
   }
-  T[1] = t_match;
-  T[3] = t_rap;
-  T[4] = t_compose;
 
   // smoother diagonals
   double ts = now_ms();
@@ -1756,6 +1788,22 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
   AMG_TRY(build_solve_formats(h));
   AMG_HIP(hipStreamSynchronize(s));
   T[6] = now_ms() - tf;
+  // numbering and Galerkin product as the device saw them; what is left of the
+  // host's time in the sweeps is the matching's
+  int khz = 0;
+  AMG_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->device));
+  const auto ms = [&](uint64_t from, uint64_t to) {
+    return khz > 0 && from && to > from ? (double)(to - from) / khz : 0.0;
+  };
+  for (int32_t k = 0; k < ran; ++k) {
+    T[2] += ms(when[k].count, when[k].counted) + ms(when[k].assign, when[k].product);
+    T[3] += ms(when[k].product, when[k].end);
+  }
+  double waited = 0;
+  for (int32_t k : last_of_level) waited += ms(when[k].product, when[k].end);
+  T[1] = std::max(0.0, t_sweeps - T[2] - (T[3] - waited));
+  T[4] = std::max(0.0, t_compose - waited);
+  T[3] += t_smooth;
   T[7] = now_ms() - t_start;
   for (int k = 0; k < 8; ++k) h->setup_ms[k] = T[k];
   return AMG_OK;
