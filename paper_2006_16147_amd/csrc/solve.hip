@@ -3605,6 +3605,8 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
   if (flexible(h)) AMG_TRY(precond_perm(h, h->r, h->z, nullptr, done));
   else AMG_TRY(vcycle_perm(h, h->r, h->z, true, done));
   if (!h->p2) launch_xpay(h, n, 1, done);
+  // (the first solve makes it while the device is busy with the above)
+  if (use_graph && maxit >= kIterGroups[1]) (void)iteration_graph(h, 1);
   // Iterations in chunks, whose length follows the observed convergence; after
   // each chunk the host looks at the scalars.
   int32_t queued = 0, chunk = 0;
