@@ -637,7 +637,9 @@ __global__ void kb_permute_rows(int32_t n, int32_t k, const int32_t *__restrict_
 // Z = A_L^-1 R on the coarsest level, one thread per (row, column). A chain of
 // load latencies: kTerms terms are asked for before the first is used, without
 // a test of each while that many are left (against eight with tests,
-// a solve of 40^3 at k = 16 took 2.82 for 3.32 ms, of 64^3 at k = 32 11.6 for 12.1).
+// a solve of 40^3 at k = 16 took 2.82 for 3.32 ms, of 64^3 at k = 32 11.6 for 12.1),
+// and the rest together too (one by one, a solve of 14^3, 45 unknowns, at k = 16
+// took 920 for 888 us).
 template <typename TI, typename TO>
 __global__ void kb_coarse(int32_t nL, int32_t k, const double *__restrict__ Ainv,
                           const TI *__restrict__ R, TO *__restrict__ Z,
@@ -661,7 +663,19 @@ __global__ void kb_coarse(int32_t nL, int32_t k, const double *__restrict__ Ainv
 #pragma unroll
     for (int u = 0; u < kTerms; ++u) s += av[u] * (double)rv[u];
   }
-  for (; m0 < nL; ++m0) s += row[m0] * (double)R[(int64_t)m0 * k + j];
+  if (m0 < nL) {  // (what is left, the last term in place of those past it)
+    double av[kTerms];
+    TI rv[kTerms];
+#pragma unroll
+    for (int u = 0; u < kTerms; ++u) {
+      const int32_t m = m0 + u < nL ? m0 + u : nL - 1;
+      av[u] = row[m];
+      rv[u] = R[(int64_t)m * k + j];
+    }
+#pragma unroll
+    for (int u = 0; u < kTerms; ++u)
+      if (m0 + u < nL) s += av[u] * (double)rv[u];
+  }
   Z[e] = (TO)s;
 }
 
