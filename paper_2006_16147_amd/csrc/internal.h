@@ -48,7 +48,7 @@ constexpr int kMaxRowsPerThread = 4;
 constexpr int64_t kManyRows = int64_t(1) << 23;
 constexpr int kPartPlanes = 3;  // partial-sum planes (dot products per reduction)
 // K-cycle scalars of one level's two flexible-CG iterations
-enum KScal : int32_t { kRho1 = 0, kS1, kGamma, kRho2, kS2, kA1, kKScal = 8 };
+enum KScal : int32_t { kRho1 = 0, kS1, kS2, kA1, kKScal = 8 };
 constexpr int kNumXcd = 8;       // MI355X: 8 XCDs, blocks dispatched round-robin
 
 // Solve-phase PCG scalars, resident on the device.

@@ -468,7 +468,8 @@ __global__ void __launch_bounds__(kBlock) k_pref_long(
 // states (29 us at 160^3, 444 rounds, 12.9 ms). Here a block owns a run of
 // consecutive vertices, their words in LDS and the next entries of their lists
 // in registers, so a step inside it touches no memory; between blocks it costs
-// a store and a poll (3.3 ms). A wave looks outside when nothing moved inside,
+// a store and a poll (2.4 ms; 3.3 in the version that the variants here were
+// measured against). A wave looks outside when nothing moved inside,
 // and waves that wait sleep 2048 clocks between their looks and yield the
 // issue slots to those that move: with 64 clocks it was 4.4 ms, and with every
 // waiting wave polling all the time the polls filled the fabric and a step
