@@ -1494,8 +1494,8 @@ __global__ void k_xpay(int32_t n, const double *__restrict__ z, double *__restri
 // for a V-cycle too many at the end, gave 64^3 2480 -> 2459 and 96^3 4895 -> 4892,
 // and cost a solve of one iteration at 96^3 258 -> 307.)
 constexpr int32_t kFoldParts = 512;
-// iterations queued while the host looks at the first ones, where the
-// hierarchy has so few levels that they are of at most nine kernels (see pcg)
+// iterations that run while the host looks at the first ones; levels up to which
+// an iteration is of at most nine kernels (see pcg)
 constexpr int32_t kAhead = 4;
 constexpr size_t kAheadLevels = 5;
 constexpr int32_t kDirRows = 1 << 20;
@@ -3632,12 +3632,14 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
   // A look costs 50 us in which the GPU waits, more than an iteration of few
   // kernels. Where the solve has such, and the residual has to fall further
   // than four iterations bring it (a tenth each, which is fast), the first chunk
-  // is of eight, and four more run while the host looks at its result. Queued in
-  // vain, an iteration costs its launches, 1.7 us a kernel: with 16 in the first
-  // chunk of every folded solve, 20^3 took 587 us to 1e-6 and 364 to 1e-2, 48^3 1344
-  // and 583, 50^3 with 2 + 2 sweeps 2042 and 1074; now 606 and 293, 1314 and 497,
-  // 2125 and 743. (With kernels for the scalars, in chunks of four: 705 and 316,
-  // 1452 and 521, 2168 and 761.)
+  // is of twelve; where it has to fall further than seven tenths, four of them
+  // run while the host looks at the first eight. Queued in vain, an iteration
+  // costs its launches, 1.7 us a kernel: with 16 in the first chunk of every
+  // folded solve, 20^3 took 576 us to 1e-6 and 364 to 1e-2, 48^3 1344 and 583,
+  // 50^3 with 2 + 2 sweeps 2042 and 1074; now 600 and 293, 1314 and 497, 2125 and
+  // 743. (With kernels for the scalars, in chunks of four: 727 and 316, 1452 and
+  // 521, 2168 and 761. Four ahead in every first chunk: 16^3 to 1e-6 548 for 524,
+  // in none: 8^3 to 1e-8 454 for 432.)
   const bool few = h->fold && h->params.pre == 1 && h->params.post == 1 &&
                    !h->params.smooth_p && h->lv.size() <= kAheadLevels;
   bool ahead = false;
@@ -3658,9 +3660,12 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
     const PcgScal sc = *h->scal_host;
     if (sc.done) break;
     if (queued >= maxit) break;  // not reached: the maxit test sets done
-    ahead = few && rr_prev < 0.0 && std::log10(sc.rr / sc.tol2) > 8.0;
+    const double tenths = few && rr_prev < 0.0 ? std::log10(sc.rr / sc.tol2) / 2.0 : 0.0;
     next = wanted(sc);
-    if (ahead) next = 8;
+    if (tenths > 4.0) {
+      ahead = tenths > 7.0;
+      next = ahead ? 12 - kAhead : 12;
+    }
   }
   if (L0.S.exact32)
     k_residual_norms<1, float><<<g.grid, kBlock, 0, s>>>(n, g.chunk, L0.S.sptr, L0.S.col,
