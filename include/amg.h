@@ -304,7 +304,8 @@ size_t amg_estimate_footprint(int64_t n, int64_t nnz, const amg_params *params);
  * validate, weights+matching, numbering+prolongator, Galerkin, compose,
  * smoother+coarsest, solve-format conversion, total. Numbering and (without
  * smoothing) Galerkin are the times of their kernels on the device; the others
- * are the host's, weights+matching (with its waits) without those two. */
+ * are the host's, weights+matching (with the count of the aggregates and the
+ * waits) without those two. */
 amg_status amg_setup_times(const amg_hierarchy *h, double *ms_host);
 /* Number of matching rounds run when building level l (sum over sweeps). */
 amg_status amg_matching_rounds(const amg_hierarchy *h, int32_t l, int32_t *rounds);

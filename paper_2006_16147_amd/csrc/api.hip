@@ -294,7 +294,6 @@ void destroy(amg_hierarchy *h) {
   if (h->batch) free_batch(h->batch, h->device, h->stream);
   stream_free(h->device, h->stream, h->allocs);
   if (h->scal_host) (void)hipHostFree(h->scal_host);
-  if (h->look_event) (void)hipEventDestroy(h->look_event);
   if (h->join_event) (void)hipEventDestroy(h->join_event);
   if (h->stream) (void)hipStreamDestroy(h->stream);
   delete h;

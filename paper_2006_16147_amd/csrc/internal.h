@@ -219,7 +219,9 @@ struct amg_hierarchy {
   int device = 0;
   hipStream_t stream = nullptr;       // the library's own work stream
   hipStream_t user_stream = nullptr;  // amg_params.stream (NULL: default stream)
-  hipEvent_t join_event = nullptr;    // orders the work stream after the caller's
+  // orders the work stream after the caller's; in a solve, after the copy into
+  // the second of scal_host
+  hipEvent_t join_event = nullptr;
   amg_params params{};
   std::vector<amg::Level> lv;
   amg::Coarse C;
@@ -237,7 +239,6 @@ struct amg_hierarchy {
   double *kscal = nullptr;  // K-cycle scalars, kKScal per level
   amg::PcgScal *scal = nullptr;   // device
   amg::PcgScal *scal_host = nullptr;  // two pinned mirrors (and the setup's stamps)
-  hipEvent_t look_event = nullptr;    // after the copy into the second
   void *setup_arena = nullptr;  // the running setup's temporaries (setup.hip), else null
   int32_t *zero_flag = nullptr;   // device int 0 (for kernels outside CG)
   // batch (multi-right-hand-side) solve state, allocated for the last k used

@@ -73,11 +73,12 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
 }
 
 // When a sweep's stages begin on the device, in ticks of its wall clock: kernels
-// write it to pinned host memory as they start (no event or wait between them;
-// a store of 8 bytes). Numbering is the count of the aggregates and, after the
-// host has read it, their assignment.
+// write it to pinned host memory as they start: no event, wait or copy, and less
+// than a microsecond for each of the three per sweep (in device memory, cleared at
+// the start and copied at the end, 9 to 17 us a set-up more). The count of the aggregates,
+// which the host waits for, goes with the matching.
 struct Stamps {
-  uint64_t count, counted, assign, product, end;
+  uint64_t assign, product, end;
 };
 __device__ __forceinline__ void stamp(uint64_t *at) {
   if (at && blockIdx.x == 0 && threadIdx.x == 0) *at = wall_clock64();
@@ -105,7 +106,6 @@ struct Report {
   const int32_t *from = nullptr;  // kCtl words
   const int32_t *err = nullptr;   // the setup's kErr* so far
   int32_t *to = nullptr;          // kCtl + 1 words, the total last; null: no report
-  uint64_t *when = nullptr;       // stamp of the report
 };
 
 __device__ __forceinline__ void report(const Report &R, int32_t total) {
@@ -114,7 +114,6 @@ __device__ __forceinline__ void report(const Report &R, int32_t total) {
     R.to[k] = __hip_atomic_load(k == kCtlErr ? R.err : &R.from[k], __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_AGENT);
   R.to[kCtl] = total;
-  if (R.when) *R.when = wall_clock64();
 }
 
 // the end of a block's part of a scan (one thread): its sum; a scan of one
@@ -600,10 +599,8 @@ __global__ void __launch_bounds__(kMatchThreads, 8) k_match(int32_t n,
 __global__ void __launch_bounds__(kScanBlock) k_lead_scan(int32_t n, const uint64_t *st,
                                                           const int32_t *rb, const int32_t *re,
                                                           int32_t *mate, int32_t *id,
-                                                          int32_t *bsum, int32_t *ctl, Report R,
-                                                          uint64_t *began) {
+                                                          int32_t *bsum, int32_t *ctl, Report R) {
   __shared__ int32_t most, sum, wide;
-  stamp(began);
   if (threadIdx.x == 0) most = sum = wide = 0;
   const int64_t base = ((int64_t)blockIdx.x * kScanBlock + threadIdx.x) * kScanPer;
   int32_t lead[kScanPer];
@@ -1403,7 +1400,7 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
                           Stamps *when, uint64_t *before, SweepOut &o) {
   hipStream_t s = h->stream;
   const int32_t n = A.n;
-  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host), &when->counted};
+  const Report R{ctl, err, reinterpret_cast<int32_t *>(h->scal_host)};
   int32_t *pref, *id, *bsum, *ovf;
   uint64_t *st;
   AMG_TRY(tmp.get(&pref, A.most));
@@ -1428,7 +1425,7 @@ amg_status pairwise_sweep(amg_hierarchy *h, Tmp &tmp, const Mat &A, int32_t *ctl
           n, A.rows.b, A.rows.e, pref, st, r > 0 ? f - kMatchFlags : nullptr, f);
     }
     k_lead_scan<<<scan_blocks(n), kScanBlock, 0, s>>>(n, st, A.rows.b, A.rows.e, o.mate, id, bsum,
-                                                      ctl, R, &when->count);
+                                                      ctl, R);
     if (scan_blocks(n) > 1) k_scan_sums<<<1, kScanBlock, 0, s>>>(bsum, scan_blocks(n), R);
     AMG_HIP(hipGetLastError());
     AMG_TRY(read_ctl(R.to, hc, s));
@@ -1581,7 +1578,6 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->scal_host), 2 * sizeof(PcgScal) + stamps));
   Stamps *const when = reinterpret_cast<Stamps *>(h->scal_host + 2);
   std::memset(when, 0, stamps);
-  if (!h->look_event) AMG_HIP(hipEventCreateWithFlags(&h->look_event, hipEventDisableTiming));
   static_assert(sizeof(PcgScal) >= sizeof(int32_t) * (kCtl + 1), "control block and total");
   int32_t ran = 0;
 
@@ -1797,7 +1793,7 @@ amg_status build_hierarchy(amg_hierarchy *h, const amg_csr *A) {
     return khz > 0 && from && to > from ? (double)(to - from) / khz : 0.0;
   };
   for (int32_t k = 0; k < ran; ++k) {
-    T[2] += ms(when[k].count, when[k].counted) + ms(when[k].assign, when[k].product);
+    T[2] += ms(when[k].assign, when[k].product);
     T[3] += ms(when[k].product, when[k].end);
   }
   double waited = 0;

@@ -3648,9 +3648,9 @@ amg_status pcg(amg_hierarchy *h, const double *b_user, double *x_user, double rt
     if (ahead) {
       ahead = false;
       AMG_HIP(hipMemcpyAsync(h->scal_host + 1, h->scal, sizeof(PcgScal), hipMemcpyDeviceToHost, s));
-      AMG_HIP(hipEventRecord(h->look_event, s));
+      AMG_HIP(hipEventRecord(h->join_event, s));
       AMG_TRY(queue(kAhead));
-      AMG_HIP(hipEventSynchronize(h->look_event));
+      AMG_HIP(hipEventSynchronize(h->join_event));
       const PcgScal sc = h->scal_host[1];
       if (sc.done) break;
       AMG_TRY(queue(wanted(sc)));
